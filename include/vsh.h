@@ -94,7 +94,7 @@ enum {
 #define VSH_SUMMARY 0x1u           /* return per-event summaries                       */
 #define VSH_RECORDS 0x2u           /* return the final partons of every event (CSR)     */
 #define VSH_FORM_PLAIN 0x0u        /* one launch; each wave keeps its events (one lane
-                                      each, or 64 with their trials spread over the
+                                      each, or up to 64 with their trials spread over the
                                       lanes) from start to the cutoff                   */
 #define VSH_FORM_PERSISTENT 0x4u   /* persistent waves with ballot compaction + refill,
                                       events evolving in their output records           */

@@ -46,13 +46,15 @@ __device__ __forceinline__ uint32_t find_segment(const Segment* segs, uint32_t n
 // kGranule = 16 every claim starts on a 16-event boundary and each 128-byte
 // line of a record column (16 doubles of consecutive events) belongs to one
 // wave: needed when the events evolve in place, where neighbouring events of
-// one line would otherwise be written by waves on different XCDs.
+// one line would otherwise be written by waves on different XCDs.  A wave of
+// fewer than 64 events (wave_lanes, see events_per_wave) takes them all in
+// one claim: such launches hold every event at once.
 template <uint32_t kGranule>
 __device__ __forceinline__ bool refill(const PersistArgs& A, bool busy, uint32_t wave_lanes, uint32_t lane,
                                       uint32_t& since, bool& drained, uint32_t& req, uint64_t& ev) {
-  const uint64_t idle = __ballot(!busy);
+  const uint64_t idle = __ballot(!busy && lane < wave_lanes);
   const uint32_t n_idle = __popcll(idle);
-  const uint32_t take = n_idle / kGranule * kGranule;
+  const uint32_t take = wave_lanes < 64 ? n_idle : n_idle / kGranule * kGranule;
   if (drained || take == 0 || (n_idle != wave_lanes && (since < A.period || n_idle < A.threshold)))
     return false;
   since = 0;
@@ -61,7 +63,7 @@ __device__ __forceinline__ bool refill(const PersistArgs& A, bool busy, uint32_t
   if (lane == leader) base = atomicAdd(A.next, (unsigned long long)take);
   base = __shfl(base, leader);
   if (base + take >= A.total) drained = true;
-  if (busy) return false;
+  if (!(idle >> lane & 1ull)) return false;
   const uint32_t rank = __popcll(idle & ((1ull << lane) - 1));
   const uint64_t w = base + rank;
   if (rank >= take || w >= A.total) return false;
@@ -893,24 +895,47 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
   if (busy && !pend && s.status == kRunning && s.cycle >= climit_of(lane)) s.status = kCycleLimitHit;
 }
 
-// Plain one-launch form with the flattened mapping: wave w owns events
-// 64w .. 64w+63 of the batch (already started by k_me) from start to cutoff,
-// with no refill; finished lanes only stop contributing trial work.
+// Waves that a launch of the flattened kernels spreads its events over: the
+// resident ones of 256 compute units (sixteen blocks per CU up to 64 partons
+// per record, fourteen up to 128, eleven above: LDS).  With quark masses one
+// per SIMD: those waves evaluate one veto cycle at a time, so a sparse wave
+// saves less than a second one costs.
+static uint32_t flat_waves(uint32_t cap, bool massive) {
+  constexpr uint32_t kCUs = 256;
+  return kCUs * (massive ? 4u : cap <= 64 ? 16u : cap <= kFourMaxCap ? 14u : 11u);
+}
+
+// Events that a wave holds at once.  A small launch is bound by the chain of
+// wave cycles of its longest wave, and 64 events to a wave left most of the
+// chip idle (100 events: two waves): a wave of few events runs shorter cycles
+// and evaluates up to eight veto cycles ahead from the start, so the events
+// are spread until every resident wave has some.  Plain LEP shower, 64 events
+// per wave and this rule: 100 events 392 and 114 us, 5003 events 509 and 195,
+// 20000 events 532 and 272, 140000 events 743 and 666; from 64 events per
+// resident wave on (262144) both are the same.  Past the resident waves the
+// spreading costs throughput (20000 events, 2 per wave: 375 us).
+static uint32_t events_per_wave(uint64_t n, uint64_t waves) {
+  return (uint32_t)std::min<uint64_t>(64, (n + waves - 1) / waves);
+}
+
+// Plain one-launch form with the flattened mapping: wave w owns per_wave
+// consecutive events of the batch (already started by k_me) from start to
+// cutoff, with no refill; finished lanes only stop contributing trial work.
 // kFour (massless, at most 128 partons): four resident waves per SIMD (128
 // registers, a few spilled; 9.2 + 1 KB of LDS), the trial constants
 // reloaded from LDS after the rounds (kAhead); otherwise three waves, the
 // massive instantiation reloading them too to fit without spilling.
 template <bool kMassive, bool kOne, bool kFour = false>
 __global__ void __launch_bounds__(64, kFour ? 4 : 3)
-    k_shower_plain_flat(Records r, Summary sm, EventInputs in, uint32_t n, EndCache ec) {
+    k_shower_plain_flat(Records r, Summary sm, EventInputs in, uint32_t n, EndCache ec, uint32_t per_wave) {
   __shared__ FlatShared<kOne, kFour> sh;
   const OneRequest one{in.seed, in.first, in.cycle_limit};
   const uint32_t lane = threadIdx.x;
   const uint32_t words = mask_words(r.cap);
-  const uint64_t e = (uint64_t)blockIdx.x * 64 + lane;
+  const uint64_t e = (uint64_t)blockIdx.x * per_wave + lane;
   EvState s = {};
   s.status = kDone;
-  bool busy = e < n;
+  bool busy = lane < per_wave && e < n;
   bool pend = false;
   Pending pd{};
   if (busy) {
@@ -939,7 +964,8 @@ void launch_shower_plain_flat(const Records& r, const Summary& s, const EventInp
                               uint64_t* cache, hipStream_t st) {
   if (!n) return;
   const EndCache ec{cache, r.cap};
-  const dim3 g((n + 63) / 64), b(64);
+  const uint32_t pw = events_per_wave(n, flat_waves(r.cap, in.massive != 0));
+  const dim3 g((n + pw - 1) / pw), b(64);
   const size_t lds = flat_lds_bytes(r.cap);
   // Massless events: the single-request LDS layout; up to 128 partons per
   // record it leaves room for 3.5 to 4 blocks per SIMD, which the four-wave
@@ -949,11 +975,11 @@ void launch_shower_plain_flat(const Records& r, const Summary& s, const EventInp
   // build is faster.  With quark masses: the per-event layout up to 64
   // partons, single-request above.
   if (in.massive) {
-    if (r.cap > kOneAboveCap) hipLaunchKernelGGL((k_shower_plain_flat<true, true>), g, b, lds, st, r, s, in, n, ec);
-    else hipLaunchKernelGGL((k_shower_plain_flat<true, false>), g, b, lds, st, r, s, in, n, ec);
+    if (r.cap > kOneAboveCap) hipLaunchKernelGGL((k_shower_plain_flat<true, true>), g, b, lds, st, r, s, in, n, ec, pw);
+    else hipLaunchKernelGGL((k_shower_plain_flat<true, false>), g, b, lds, st, r, s, in, n, ec, pw);
   } else {
-    if (r.cap > kFourMaxCap) hipLaunchKernelGGL((k_shower_plain_flat<false, true>), g, b, lds, st, r, s, in, n, ec);
-    else hipLaunchKernelGGL((k_shower_plain_flat<false, true, true>), g, b, lds, st, r, s, in, n, ec);
+    if (r.cap > kFourMaxCap) hipLaunchKernelGGL((k_shower_plain_flat<false, true>), g, b, lds, st, r, s, in, n, ec, pw);
+    else hipLaunchKernelGGL((k_shower_plain_flat<false, true, true>), g, b, lds, st, r, s, in, n, ec, pw);
   }
 }
 
@@ -990,7 +1016,7 @@ __global__ void __launch_bounds__(64, kFour ? 4 : (kInPlace || (kCached && !kMas
   uint64_t slot = L;
   uint32_t since = 0;
   while (true) {
-    if (refill<(kInPlace ? 16u : 1u)>(A, busy, 64, lane, since, drained, req, ev)) {
+    if (refill<(kInPlace ? 16u : 1u)>(A, busy, A.per_wave, lane, since, drained, req, ev)) {
       slot = kInPlace ? ev : L;
       start_event<kInPlace>(s, A, A.reqs[req], ev, slot);
       if constexpr (!kOne) sh.climit[lane] = A.reqs[req].cycle_limit;
@@ -1144,10 +1170,21 @@ const void* persistent_kernel(uint32_t mapping, bool in_place, bool massive, boo
 
 uint32_t persistent_block(uint32_t mapping, uint32_t block) { return mapping == kMapFlat ? 64u : block; }
 
+uint32_t persistent_per_wave(uint64_t total, uint64_t lanes, uint32_t mapping, uint32_t cap, bool massive) {
+  if (mapping != kMapFlat) return 64;
+  return events_per_wave(total, std::min<uint64_t>(lanes / 64, flat_waves(cap, massive)));
+}
+
+// Blocks of a persistent launch: no more waves than the first claims serve.
+uint32_t persistent_grid(const PersistArgs& A, uint64_t lanes, uint32_t block, uint32_t mapping) {
+  const uint64_t all = lanes / block;
+  return (uint32_t)(mapping == kMapFlat ? std::min<uint64_t>(all, (A.total + A.per_wave - 1) / A.per_wave) : all);
+}
+
 void launch_persistent(const PersistArgs& A, uint64_t lanes, uint32_t block, uint32_t mapping, bool in_place,
                        bool massive, hipStream_t st) {
   block = persistent_block(mapping, block);
-  const dim3 grid((uint32_t)(lanes / block));
+  const dim3 grid(persistent_grid(A, lanes, block, mapping));
   const size_t lds = mapping == kMapFlat ? flat_lds_bytes(A.slots.cap) : 0;
   void* args[] = {const_cast<PersistArgs*>(&A)};
   (void)hipLaunchKernel(persistent_kernel(mapping, in_place, massive, A.cache.rec != nullptr, A.slots.cap), grid,
@@ -1220,8 +1257,7 @@ static vsh_status build_batch_graph(vsh_ctx* ctx, BatchGraph& g, const PersistAr
   GCHK(add_event(1));
   void* a_pers[] = {&g.args};
   const bool massive = g.in.massive != 0;
-  GCHK(add_kernel(persistent_kernel(g.mapping, true, massive, true, A.slots.cap), dim3((uint32_t)(lanes / block)),
-                  dim3(block),
+  GCHK(add_kernel(persistent_kernel(g.mapping, true, massive, true, A.slots.cap), dim3(persistent_grid(A, lanes, block, g.mapping)), dim3(block),
                   a_pers, g.mapping == kMapFlat ? (unsigned)flat_lds_bytes(A.slots.cap) : 0u));
   GCHK(add_event(2));
   g.nb = L.buf.out.cap + 1;
@@ -1318,7 +1354,7 @@ vsh_status run_batch(vsh_ctx* ctx, const vsh_request* req, uint64_t first_idx, u
   A.next = L.counter;
   A.threshold = ctx->tuned.refill_threshold;
   A.period = ctx->tuned.refill_period;
-  A.pad = 0;
+  A.per_wave = persistent_per_wave(n, lanes, mapping, cap, request_massive(*req) != 0);
   A.cache = L.cache;
   EventInputs in{};
   in.ecm = ecm_dev;
@@ -1477,7 +1513,7 @@ vsh_status generate_persistent(vsh_ctx* ctx, const vsh_request* req, vsh_result*
     A.next = L.counter;
     A.threshold = ctx->tuned.refill_threshold;
     A.period = ctx->tuned.refill_period;
-    A.pad = 0;
+    A.per_wave = persistent_per_wave(n, lanes, ctx->tuned.mapping, cap, in.massive != 0);
     A.cache = L.cache;
     (void)hipEventRecord(ctx->ev[1], st);
     launch_persistent(A, lanes, ctx->tuned.pers_block, ctx->tuned.mapping, true, in.massive != 0, st);

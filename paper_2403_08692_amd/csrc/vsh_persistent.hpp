@@ -54,7 +54,7 @@ struct PersistArgs {
   uint64_t total;                 // work indices 0 .. total-1
   unsigned long long* next;       // work counter, zeroed before the launch
   uint32_t period;                // veto cycles between refill checks
-  uint32_t pad;
+  uint32_t per_wave;              // flattened mapping: events a wave holds at once, 1..64
   EndCache cache;                 // flattened mapping: per-lane end coefficients, or none
 };
 
@@ -110,6 +110,8 @@ struct BatchGraph {
   uint32_t mapping = 0;
 };
 
+// events a wave of a persistent launch over `total` events holds at once
+uint32_t persistent_per_wave(uint64_t total, uint64_t lanes, uint32_t mapping, uint32_t cap, bool massive);
 uint64_t slots_bytes(uint64_t lanes, uint32_t cap);
 uint64_t request_out_bytes(uint64_t n, uint32_t cap, bool partners);
 uint64_t obs_scratch_bytes(uint64_t n, uint32_t cap);
