@@ -52,7 +52,7 @@ __device__ __forceinline__ uint32_t find_segment(const Segment* segs, uint32_t n
 template <uint32_t kGranule>
 __device__ __forceinline__ bool refill(const PersistArgs& A, bool busy, uint32_t wave_lanes, uint32_t lane,
                                       uint32_t& since, bool& drained, uint32_t& req, uint64_t& ev) {
-  const uint64_t idle = __ballot(!busy && lane < wave_lanes);
+  const uint64_t idle = __ballot(!busy) & (~0ull >> (64 - wave_lanes));
   const uint32_t n_idle = __popcll(idle);
   const uint32_t take = wave_lanes < 64 ? n_idle : n_idle / kGranule * kGranule;
   if (drained || take == 0 || (n_idle != wave_lanes && (since < A.period || n_idle < A.threshold)))
@@ -63,10 +63,10 @@ __device__ __forceinline__ bool refill(const PersistArgs& A, bool busy, uint32_t
   if (lane == leader) base = atomicAdd(A.next, (unsigned long long)take);
   base = __shfl(base, leader);
   if (base + take >= A.total) drained = true;
-  if (!(idle >> lane & 1ull)) return false;
+  if (busy) return false;
   const uint32_t rank = __popcll(idle & ((1ull << lane) - 1));
   const uint64_t w = base + rank;
-  if (rank >= take || w >= A.total) return false;
+  if (rank >= take || w >= A.total) return false;  // lanes past wave_lanes have rank n_idle
   const uint32_t sg = find_segment(A.segs, A.n_segs, w);
   req = A.segs[sg].req;
   ev = A.segs[sg].lo + (w - A.segs[sg].start);
