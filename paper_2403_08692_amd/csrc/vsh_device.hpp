@@ -47,10 +47,24 @@ extern "C" __device__ uint64_t __ockl_wfscan_add_u64(uint64_t, bool);
 extern "C" __device__ uint32_t __ockl_wfred_max_u32(uint32_t);
 __device__ __forceinline__ uint64_t wave_inclusive_sum(uint64_t x) { return __ockl_wfscan_add_u64(x, true); }
 __device__ __forceinline__ uint32_t wave_max(uint32_t x) { return __ockl_wfred_max_u32(x); }
+extern "C" __device__ uint32_t __ockl_wfred_min_u32(uint32_t);
+extern "C" __device__ uint64_t __ockl_wfred_max_u64(uint64_t);
+extern "C" __device__ double __ockl_wfred_min_f64(double);
+extern "C" __device__ double __ockl_wfred_max_f64(double);
+__device__ __forceinline__ uint32_t wave_min(uint32_t x) { return __ockl_wfred_min_u32(x); }
+__device__ __forceinline__ uint64_t wave_max_u64(uint64_t x) { return __ockl_wfred_max_u64(x); }
+__device__ __forceinline__ double wave_min_f64(double x) { return __ockl_wfred_min_f64(x); }
+__device__ __forceinline__ double wave_max_f64(double x) { return __ockl_wfred_max_f64(x); }
 __device__ __forceinline__ uint64_t lane63(uint64_t x) {
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, 63);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), 63);
   return ((uint64_t)hi << 32) | lo;
+}
+
+// x of lane `src` (the same in every lane of the wave)
+__device__ __forceinline__ double lane_value(double x, int src) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), src),
+                          __builtin_amdgcn_readlane(__double2loint(x), src));
 }
 
 // Quark masses by flavour (GeV), all zero for the massless shower.

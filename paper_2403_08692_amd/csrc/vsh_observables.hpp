@@ -10,8 +10,20 @@ namespace vsh {
 // ---------------------------------------------------------------------------
 // Observables, one thread per event (Sec. 3.1).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double len3(double x, double y, double z) {
-  return sqrt(x * x + y * y + z * z);
+// Sums of products with their fused operations written out, so that every
+// path that measures small events (one thread or one wave per event) rounds
+// alike: left to the compiler, the product it fuses depends on what else uses
+// it nearby.
+__device__ __forceinline__ double dot3(double ax, double ay, double az, double bx, double by, double bz) {
+#pragma clang fp contract(off)
+  return fma(az, bz, fma(ay, by, ax * bx));
+}
+__device__ __forceinline__ double sq3(double x, double y, double z) { return dot3(x, y, z, x, y, z); }
+__device__ __forceinline__ double len3(double x, double y, double z) { return sqrt(sq3(x, y, z)); }
+// a b - c d
+__device__ __forceinline__ double det2(double a, double b, double c, double d) {
+#pragma clang fp contract(off)
+  return fma(a, b, -(c * d));
 }
 
 __device__ __forceinline__ int bin_of(double x, double lo, double hi) {
@@ -175,12 +187,12 @@ __device__ __forceinline__ ObsOut scratch_observables(const Scratch& w, uint64_t
     const double l = len3(x, y, z);
     sum += l;
     const double il = 1.0 / l;
-    mxx += x * x * il;
-    myy += y * y * il;
-    mzz += z * z * il;
-    mxy += x * y * il;
-    mxz += x * z * il;
-    myz += y * z * il;
+    mxx = fma(x * x, il, mxx);
+    myy = fma(y * y, il, myy);
+    mzz = fma(z * z, il, mzz);
+    mxy = fma(x * y, il, mxy);
+    mxz = fma(x * z, il, mxz);
+    myz = fma(y * z, il, myz);
   }
   // thrust
   double best = -1.0, bx = 0.0, by = 0.0, bz = 1.0;
@@ -194,7 +206,7 @@ __device__ __forceinline__ ObsOut scratch_observables(const Scratch& w, uint64_t
         vy += sg * w.y[q];
         vz += sg * w.z[q];
       }
-      const double m2 = vx * vx + vy * vy + vz * vz;
+      const double m2 = sq3(vx, vy, vz);
       if (m2 > best) { best = m2; bx = vx; by = vy; bz = vz; }
     }
   } else {
@@ -204,13 +216,13 @@ __device__ __forceinline__ ObsOut scratch_observables(const Scratch& w, uint64_t
       for (int j = i + 1; j < np; ++j) {
         const uint64_t qj = (uint64_t)j * w.stride + t;
         const double xj = w.x[qj], yj = w.y[qj], zj = w.z[qj];
-        const double nx = yi * zj - zi * yj, ny = zi * xj - xi * zj, nz = xi * yj - yi * xj;
+        const double nx = det2(yi, zj, zi, yj), ny = det2(zi, xj, xi, zj), nz = det2(xi, yj, yi, xj);
         double vx = 0.0, vy = 0.0, vz = 0.0;
         for (int k = 0; k < np; ++k) {
           if (k == i || k == j) continue;
           const uint64_t qk = (uint64_t)k * w.stride + t;
           const double xk = w.x[qk], yk = w.y[qk], zk = w.z[qk];
-          const double d = xk * nx + yk * ny + zk * nz;
+          const double d = dot3(xk, yk, zk, nx, ny, nz);
           if (d > 0.0) { vx += xk; vy += yk; vz += zk; }
           else { vx -= xk; vy -= yk; vz -= zk; }
         }
@@ -218,7 +230,7 @@ __device__ __forceinline__ ObsOut scratch_observables(const Scratch& w, uint64_t
         for (int c = 0; c < 4; ++c) {
           const double si = (c < 2) ? 1.0 : -1.0, sj = (c & 1) ? -1.0 : 1.0;
           const double wx = vx + si * xi + sj * xj, wy = vy + si * yi + sj * yj, wz = vz + si * zi + sj * zj;
-          const double m2 = wx * wx + wy * wy + wz * wz;
+          const double m2 = sq3(wx, wy, wz);
           if (m2 > best) { best = m2; bx = wx; by = wy; bz = wz; }
         }
       }
@@ -238,8 +250,8 @@ __device__ __forceinline__ ObsOut scratch_observables(const Scratch& w, uint64_t
   for (int a = 0; a < np; ++a) {
     const uint64_t q = (uint64_t)a * w.stride + t;
     const P4 p{w.E[q], w.x[q], w.y[q], w.z[q]};
-    const double d = p.x * ax + p.y * ay + p.z * az;
-    const double kt = len3(p.y * az - p.z * ay, p.z * ax - p.x * az, p.x * ay - p.y * ax);
+    const double d = dot3(p.x, p.y, p.z, ax, ay, az);
+    const double kt = len3(det2(p.y, az, p.z, ay), det2(p.z, ax, p.x, az), det2(p.x, ay, p.y, ax));
     if (d >= 0.0) { hp.e += p.e; hp.x += p.x; hp.y += p.y; hp.z += p.z; bp += kt; }
     else { hm.e += p.e; hm.x += p.x; hm.y += p.y; hm.z += p.z; bm += kt; }
   }
@@ -313,12 +325,12 @@ __device__ __forceinline__ ObsOut reg_observables(const Records& r, uint64_t e, 
       const double l = len3(x, y, z);
       sum += l;
       const double il = 1.0 / l;
-      mxx += x * x * il;
-      myy += y * y * il;
-      mzz += z * z * il;
-      mxy += x * y * il;
-      mxz += x * z * il;
-      myz += y * z * il;
+      mxx = fma(x * x, il, mxx);
+      myy = fma(y * y, il, myy);
+      mzz = fma(z * z, il, mzz);
+      mxy = fma(x * y, il, mxy);
+      mxz = fma(x * z, il, mxz);
+      myz = fma(y * z, il, myz);
     }
   }
   // thrust
@@ -335,7 +347,7 @@ __device__ __forceinline__ ObsOut reg_observables(const Records& r, uint64_t e, 
           vz += sg * Z[a];
         }
       }
-      const double m2 = vx * vx + vy * vy + vz * vz;
+      const double m2 = sq3(vx, vy, vz);
       if (m2 > best) { best = m2; bx = vx; by = vy; bz = vz; }
     }
   } else {
@@ -351,13 +363,13 @@ __device__ __forceinline__ ObsOut reg_observables(const Records& r, uint64_t e, 
       for (int j = 1; j < M; ++j) {
         if (j >= wmax) break;
         if (j > i && j < np) {
-          const double nx = yi * Z[j] - zi * Y[j], ny = zi * X[j] - xi * Z[j], nz = xi * Y[j] - yi * X[j];
+          const double nx = det2(yi, Z[j], zi, Y[j]), ny = det2(zi, X[j], xi, Z[j]), nz = det2(xi, Y[j], yi, X[j]);
           double vx = 0.0, vy = 0.0, vz = 0.0;
 #pragma unroll
           for (int k = 0; k < M; ++k) {
             if (k >= wmax) break;
             if (k != i && k != j && k < np) {
-              const double d = X[k] * nx + Y[k] * ny + Z[k] * nz;
+              const double d = dot3(X[k], Y[k], Z[k], nx, ny, nz);
               if (d > 0.0) { vx += X[k]; vy += Y[k]; vz += Z[k]; }
               else { vx -= X[k]; vy -= Y[k]; vz -= Z[k]; }
             }
@@ -366,7 +378,7 @@ __device__ __forceinline__ ObsOut reg_observables(const Records& r, uint64_t e, 
           for (int c = 0; c < 4; ++c) {
             const double si = (c < 2) ? 1.0 : -1.0, sj = (c & 1) ? -1.0 : 1.0;
             const double wx = vx + si * xi + sj * X[j], wy = vy + si * yi + sj * Y[j], wz = vz + si * zi + sj * Z[j];
-            const double m2 = wx * wx + wy * wy + wz * wz;
+            const double m2 = sq3(wx, wy, wz);
             if (m2 > best) { best = m2; bx = wx; by = wy; bz = wz; }
           }
         }
@@ -388,8 +400,8 @@ __device__ __forceinline__ ObsOut reg_observables(const Records& r, uint64_t e, 
   for (int a = 0; a < M; ++a) {
     if (a < np) {
       const P4 p{E[a], X[a], Y[a], Z[a]};
-      const double d = p.x * ax + p.y * ay + p.z * az;
-      const double kt = len3(p.y * az - p.z * ay, p.z * ax - p.x * az, p.x * ay - p.y * ax);
+      const double d = dot3(p.x, p.y, p.z, ax, ay, az);
+      const double kt = len3(det2(p.y, az, p.z, ay), det2(p.z, ax, p.x, az), det2(p.x, ay, p.y, ax));
       if (d >= 0.0) { hp.e += p.e; hp.x += p.x; hp.y += p.y; hp.z += p.z; bp += kt; }
       else { hm.e += p.e; hm.x += p.x; hm.y += p.y; hm.z += p.z; bm += kt; }
     }
@@ -490,6 +502,26 @@ __device__ __forceinline__ FixScale fix_scale(const Scratch& sc) {
   return FixScale{62 - (int)sc.lbits - e, 62 - (int)sc.lbits - 2 * e};
 }
 
+// Add one event (weight w) to quantity h's row of a histogram set
+// [kNObs][kNHCol][3] in LDS or a global copy: FP64 sums, or (fx non-null) the
+// fixed-point sums of fix_scale in the same words.  The two jet rates are
+// binned in log10.
+__device__ __forceinline__ void hist_add(double* lh, int h, double x, double w, const FixScale* fx) {
+  if (h < 2) x = x > 0.0 ? log10(x) : -INFINITY;
+  const int b = bin_of(x, hist_lo(h), hist_hi(h));
+  double* cell = &lh[3 * (kNHCol * h + b)];
+  if (fx) {
+    unsigned long long* ic = reinterpret_cast<unsigned long long*>(cell);
+    atomicAdd(&ic[0], (unsigned long long)llrint(ldexp(w, fx->fw)));
+    atomicAdd(&ic[1], (unsigned long long)llrint(ldexp(w * w, fx->fw2)));
+    atomicAdd(&ic[2], 1ull);
+  } else {
+    atomicAdd(&cell[0], w);
+    atomicAdd(&cell[1], w * w);
+    atomicAdd(&cell[2], 1.0);
+  }
+}
+
 // Fill one event into a histogram set [kNObs][kNHCol][3], in LDS or a
 // global copy: FP64 sums, or (fx non-null) the fixed-point sums of
 // fix_scale in the same words.
@@ -523,19 +555,20 @@ __device__ __forceinline__ void hist_fill(double* lh, const ObsOut& o, double w,
 }
 
 // One LDS histogram set into this block's copy of the global one (block b:
-// copy b mod kHistCopies): FP64 atomics, or integer atomics into the
-// fixed-point cells.
+// copy b mod copies; with no copies FP64 sums go straight into hist): FP64
+// atomics, or integer atomics into the fixed-point cells.
 __device__ __forceinline__ void hist_flush(const double* lh, const Scratch& sc, bool fixed, uint32_t t0,
-                                           uint32_t step) {
+                                           uint32_t step, uint32_t copies, double* hist) {
   const unsigned long long* lq = reinterpret_cast<const unsigned long long*>(lh);
-  const uint32_t c0 = (blockIdx.x % kHistCopies) * (uint32_t)kHistDoubles;
+  const uint32_t c0 = copies ? (blockIdx.x % copies) * (uint32_t)kHistDoubles : 0u;
+  double* to = copies ? sc.hcopy + c0 : hist;
   for (uint32_t a = t0; a < (uint32_t)kHistDoubles; a += step) {
     if (fixed) {
       const unsigned long long q = lq[a];  // integer words: never read as doubles
       if (q) atomicAdd(&sc.ihist[c0 + a], q);
     } else {
       const double v = lh[a];
-      if (v != 0.0) unsafeAtomicAdd(&sc.hcopy[c0 + a], v);
+      if (v != 0.0) unsafeAtomicAdd(&to[a], v);
     }
   }
 }

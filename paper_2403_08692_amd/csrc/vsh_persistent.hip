@@ -1265,35 +1265,46 @@ static vsh_status build_batch_graph(vsh_ctx* ctx, BatchGraph& g, const PersistAr
   const bool fixed = g.in.fixed_hist != 0;
   g.ih = fixed ? g.sc.ihist : nullptr;
   g.wm = fixed ? g.sc.wmax : nullptr;
+  ObsFewLaunch few;
+  const bool is_few = obs_few_launch(n, g.cap, fixed, &few);
+  g.copies = is_few ? few.copies : kHistCopies;
   void* a_zero[] = {&g.sc.cnt, &g.nb, &g.sc.hcopy, &g.ih, &g.wm};
-  GCHK(add_kernel((const void*)k_obs_reset, dim3(obs_reset_blocks(g.nb)), dim3(256),
+  if (g.copies) GCHK(add_kernel((const void*)k_obs_reset, dim3(obs_reset_blocks(g.nb)), dim3(256),
                   a_zero));
-  const uint32_t eb = obs_sort_blocks(n);
-  void* a_count[] = {&g.sum, &g.n, &g.cap, &g.sc.cnt, &g.wm};
-  GCHK(add_kernel((const void*)k_obs_count, dim3(eb), dim3(256), a_count));
-  void* a_scan[] = {&g.sc.cnt, &g.nb};
-  GCHK(add_kernel((const void*)k_obs_scan, dim3(1), dim3(256), a_scan));
-  void* a_scatter[] = {&g.sum, &g.n, &g.cap, &g.sc.cnt, &g.sc.perm};
-  GCHK(add_kernel((const void*)k_obs_scatter, dim3(eb), dim3(256), a_scatter));
-  void* a_obs[] = {&g.rec, &g.sum, &g.in, &g.sc, &g.n, &g.hist};
-  const uint32_t ob = (uint32_t)(std::min<uint64_t>(g.sc.stride, (n + 255) / 256 * 256) / 256);
-  GCHK(add_kernel(obs_kernel(massive), dim3(ob), dim3(256), a_obs));
-  g.perm_c = g.sc.perm;
-  g.cnt_c = g.sc.cnt;
-  ObsGroupLaunch gl[3];
-  const uint32_t ng = obs_group_launches(g.cap, massive, gl);
-  for (uint32_t k = 0; k < ng; ++k) {
-    g.glo[k] = gl[k].lo;
-    g.ghi[k] = gl[k].hi;
-    g.gslots[k] = gl[k].slots;
-    void* a_grp[] = {&g.rec, &g.sum, &g.in, &g.perm_c, &g.cnt_c, &g.cap, &g.glo[k], &g.ghi[k], &g.gslots[k], &g.hist,
-                     &g.sc};
-    const uint32_t wb = (uint32_t)std::min<uint64_t>(n, kObsWaveBlocks);
-    GCHK(add_kernel(gl[k].fn, dim3(wb), dim3(64), a_grp, gl[k].lds));
+  if (is_few) {
+    g.fslots = few.slots;
+    void* a_wmax[] = {&g.sum, &g.n, &g.wm};
+    if (fixed) GCHK(add_kernel((const void*)k_obs_wmax, dim3(obs_wmax_blocks(n)), dim3(256), a_wmax));
+    void* a_few[] = {&g.rec, &g.sum, &g.in, &g.sc, &g.n, &g.fslots, &g.copies, &g.hist};
+    GCHK(add_kernel(obs_few_kernel(massive), dim3(few.blocks), dim3(few.threads), a_few, few.lds));
+  } else {
+    const uint32_t eb = obs_sort_blocks(n);
+    void* a_count[] = {&g.sum, &g.n, &g.cap, &g.sc.cnt, &g.wm};
+    GCHK(add_kernel((const void*)k_obs_count, dim3(eb), dim3(256), a_count));
+    void* a_scan[] = {&g.sc.cnt, &g.nb};
+    GCHK(add_kernel((const void*)k_obs_scan, dim3(1), dim3(256), a_scan));
+    void* a_scatter[] = {&g.sum, &g.n, &g.cap, &g.sc.cnt, &g.sc.perm};
+    GCHK(add_kernel((const void*)k_obs_scatter, dim3(eb), dim3(256), a_scatter));
+    void* a_obs[] = {&g.rec, &g.sum, &g.in, &g.sc, &g.n, &g.hist};
+    const uint32_t ob = (uint32_t)(std::min<uint64_t>(g.sc.stride, (n + 255) / 256 * 256) / 256);
+    GCHK(add_kernel(obs_kernel(massive), dim3(ob), dim3(256), a_obs));
+    g.perm_c = g.sc.perm;
+    g.cnt_c = g.sc.cnt;
+    ObsGroupLaunch gl[3];
+    const uint32_t ng = obs_group_launches(g.cap, massive, gl);
+    for (uint32_t k = 0; k < ng; ++k) {
+      g.glo[k] = gl[k].lo;
+      g.ghi[k] = gl[k].hi;
+      g.gslots[k] = gl[k].slots;
+      void* a_grp[] = {&g.rec, &g.sum, &g.in, &g.perm_c, &g.cnt_c, &g.cap, &g.glo[k], &g.ghi[k], &g.gslots[k], &g.hist,
+                       &g.sc};
+      const uint32_t wb = (uint32_t)std::min<uint64_t>(n, kObsWaveBlocks);
+      GCHK(add_kernel(gl[k].fn, dim3(wb), dim3(64), a_grp, gl[k].lds));
+    }
   }
   g.fixed = fixed ? 1u : 0u;
   void* a_fin[] = {&g.sc, &g.hist, &g.fixed};
-  GCHK(add_kernel((const void*)k_hist_finalize, dim3(1), dim3(256), a_fin));
+  if (g.copies) GCHK(add_kernel((const void*)k_hist_finalize, dim3(kHistBlocks), dim3(256), a_fin));
   GCHK(add_event(3));
   GCHK(hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0));
 #undef GCHK

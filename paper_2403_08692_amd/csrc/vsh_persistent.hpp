@@ -98,6 +98,8 @@ struct BatchGraph {
   Scratch sc{};
   uint32_t n = 0, nb = 0, cap = 0, thr = 0;
   uint32_t glo[3] = {0, 0, 0}, ghi[3] = {0, 0, 0}, gslots[3] = {0, 0, 0};
+  uint32_t fslots = 0;  // k_obs_few's LDS slots
+  uint32_t copies = 0;  // histogram copies (0: straight into hist)
   const uint32_t* perm_c = nullptr;
   const uint32_t* cnt_c = nullptr;
   double* hist = nullptr;
