@@ -400,6 +400,48 @@ struct ChunkTimes {
   float me = 0, shower = 0, obs = 0;
 };
 
+// Caller-supplied starts (checked offsets) into the chunk's records through
+// pinned staging and k_load_records; the device copy of the CSR arrays lies
+// where the end cache and the observables' scratch come to work afterwards.
+// VSH_E_INVALID (no message) when an event fails a check.
+static vsh_status load_records(vsh_ctx* ctx, const PlainLayout& L, const uint64_t* offsets, const double* p,
+                               const int8_t* pid, const uint16_t* col, const uint16_t* acol, uint64_t count,
+                               hipStream_t st) {
+  const uint64_t base = offsets[0], total = offsets[count] - base;
+  struct Part {
+    const void* from;
+    uint64_t bytes, at;
+  } parts[] = {{offsets, (count + 1) * 8, 0}, {p + 4 * base, total * 32, 0}, {pid + base, total, 0},
+               {col + base, total * 2, 0}, {acol + base, total * 2, 0}};
+  uint64_t bytes = 256;  // the first word: the first event that fails
+  for (Part& q : parts) {
+    q.at = bytes;
+    bytes += align_up(q.bytes, 256);
+  }
+  char* dev = reinterpret_cast<char*>(L.cache);
+  if (bytes > (uint64_t)(reinterpret_cast<char*>(L.sum.d) - dev)) {
+    set_error(ctx, "caller-supplied starts of %llu bytes exceed the workspace", (unsigned long long)bytes);
+    return VSH_E_INTERNAL;
+  }
+  vsh_status rc = ctx->stage.reserve(ctx, bytes);
+  if (rc) return rc;
+  char* host = static_cast<char*>(ctx->stage.ptr);
+  unsigned long long* bad = reinterpret_cast<unsigned long long*>(host);
+  *bad = ~0ull;
+  for (const Part& q : parts) std::memcpy(host + q.at, q.from, q.bytes);
+  hipError_t err = hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, st);
+  if (err != hipSuccess) return hip_fail(ctx, err, "starts copy");
+  const CsrStarts in{(const uint64_t*)(dev + parts[0].at), (const double*)(dev + parts[1].at),
+                     (const int8_t*)(dev + parts[2].at), (const uint16_t*)(dev + parts[3].at),
+                     (const uint16_t*)(dev + parts[4].at)};
+  launch_load_records(L.rec, L.sum, in, (uint32_t)count, L.ecm, (unsigned long long*)dev, st);
+  err = hipGetLastError();
+  if (err == hipSuccess) err = hipMemcpyAsync(bad, dev, 8, hipMemcpyDeviceToHost, st);
+  if (err == hipSuccess) err = hipStreamSynchronize(st);
+  if (err != hipSuccess) return hip_fail(ctx, err, "starts");
+  return *bad == ~0ull ? VSH_OK : VSH_E_INVALID;
+}
+
 static vsh_status run_plain_chunk(vsh_ctx* ctx, const vsh_request* req, uint64_t first_idx,
                                   uint64_t count, const uint64_t* caller_offsets,
                                   const double* cp, const int8_t* cpid, const uint16_t* ccol,
@@ -429,15 +471,7 @@ static vsh_status run_plain_chunk(vsh_ctx* ctx, const vsh_request* req, uint64_t
   in.ecm0 = req->ecm;
   in.tcut0 = req->t_cut;
   const bool from_records = caller_offsets != nullptr;
-  std::vector<double> ecm_host;
   if (from_records) {
-    ecm_host.resize(count);
-    for (uint64_t e = 0; e < count; ++e) {
-      double s = 0.0;
-      for (uint64_t a = caller_offsets[first_idx + e]; a < caller_offsets[first_idx + e + 1]; ++a) s += cp[4 * a];
-      ecm_host[e] = s;
-    }
-    HIPCHK(hipMemcpyAsync(L.ecm, ecm_host.data(), count * 8, hipMemcpyHostToDevice, st));
     in.ecm = L.ecm;
   } else if (req->ecm_per_event) {
     HIPCHK(hipMemcpyAsync(L.ecm, req->ecm_per_event + first_idx, count * 8, hipMemcpyHostToDevice, st));
@@ -449,38 +483,8 @@ static vsh_status run_plain_chunk(vsh_ctx* ctx, const vsh_request* req, uint64_t
   }
   HIPCHK(hipEventRecord(ctx->ev[0], st));
   if (from_records) {
-    // scatter the caller's partons into the slot-major records on the host
-    const uint64_t slots = (uint64_t)cap * stride;
-    std::vector<double> hE(slots, 0.0), hx(slots, 0.0), hy(slots, 0.0), hz(slots, 0.0);
-    std::vector<int8_t> hpid(slots, 0);
-    std::vector<uint16_t> hc(slots, 0), ha(slots, 0);
-    std::vector<int32_t> hn(count);
-    std::vector<double> hw(count, 1.0);
-    for (uint64_t e = 0; e < count; ++e) {
-      const uint64_t b0 = caller_offsets[first_idx + e], b1 = caller_offsets[first_idx + e + 1];
-      hn[e] = (int32_t)(b1 - b0);
-      for (uint64_t a = b0; a < b1; ++a) {
-        const uint64_t s = (a - b0) * stride + e;
-        hE[s] = cp[4 * a];
-        hx[s] = cp[4 * a + 1];
-        hy[s] = cp[4 * a + 2];
-        hz[s] = cp[4 * a + 3];
-        hpid[s] = cpid[a];
-        hc[s] = ccol[a];
-        ha[s] = cacol[a];
-      }
-    }
-    HIPCHK(hipMemcpy(L.rec.E, hE.data(), slots * 8, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(L.rec.x, hx.data(), slots * 8, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(L.rec.y, hy.data(), slots * 8, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(L.rec.z, hz.data(), slots * 8, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(L.rec.pid, hpid.data(), slots, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(L.rec.col, hc.data(), slots * 2, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(L.rec.acol, ha.data(), slots * 2, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(L.sum.i + kSiN * stride, hn.data(), count * 4, hipMemcpyHostToDevice));
-    HIPCHK(hipMemsetAsync(L.sum.d, 0, kNSumD * stride * 8, st));
-    HIPCHK(hipMemsetAsync(L.sum.i + kSiFlavour * stride, 0, stride * 4, st));
-    launch_shower_init_records(L.rec, L.sum, in, (uint32_t)count, st);
+    rc = load_records(ctx, L, caller_offsets + first_idx, cp, cpid, ccol, cacol, count, st);
+    if (rc) return rc;
   } else {
     launch_me(L.rec, L.sum, in, (uint32_t)count, st);
   }
@@ -630,6 +634,45 @@ vsh_status plain_into(vsh_ctx* ctx, const vsh_request* req, hipStream_t st, void
 }
 
 
+// The message for the first fault of caller-supplied starts.
+static vsh_status explain_starts(vsh_ctx* ctx, const vsh_request* req, const uint64_t* offsets, const double* p,
+                                 const int8_t* pid, const uint16_t* col, const uint16_t* acol) {
+  for (uint64_t e = 0; e < req->n_events; ++e) {
+    if (offsets[e + 1] < offsets[e] || offsets[e + 1] - offsets[e] > req->max_partons ||
+        offsets[e + 1] - offsets[e] < 2) {
+      set_error(ctx, "event %llu: parton count must be in 2..max_partons", (unsigned long long)e);
+      return VSH_E_INVALID;
+    }
+    // every colour line must have exactly one start and one end
+    std::vector<int> seen_c(kMaxCap * 2 + 2, 0), seen_a(kMaxCap * 2 + 2, 0);
+    double E = 0.0;
+    for (uint64_t a = offsets[e]; a < offsets[e + 1]; ++a) {
+      const int f = pid[a];
+      const bool q = f >= 1 && f <= 5, qb = f <= -1 && f >= -5, g = f == 21;
+      if (!(q || qb || g) || (q && (col[a] == 0 || acol[a] != 0)) || (qb && (col[a] != 0 || acol[a] == 0)) ||
+          (g && (col[a] == 0 || acol[a] == 0)) || col[a] > 2 * kMaxCap || acol[a] > 2 * kMaxCap) {
+        set_error(ctx, "event %llu parton %llu: bad flavour/colour", (unsigned long long)e,
+                  (unsigned long long)(a - offsets[e]));
+        return VSH_E_INVALID;
+      }
+      if (col[a]) seen_c[col[a]]++;
+      if (acol[a]) seen_a[acol[a]]++;
+      E += p[4 * a];
+    }
+    for (size_t c = 0; c < seen_c.size(); ++c)
+      if (seen_c[c] != seen_a[c] || seen_c[c] > 1) {
+        set_error(ctx, "event %llu: colour line %zu is not closed once", (unsigned long long)e, c);
+        return VSH_E_INVALID;
+      }
+    if (!(E > 0.0)) {
+      set_error(ctx, "event %llu: total energy must be > 0", (unsigned long long)e);
+      return VSH_E_INVALID;
+    }
+  }
+  set_error(ctx, "inconsistent initial states");  // not reached: the device makes the same checks
+  return VSH_E_INVALID;
+}
+
 }  // namespace vsh
 
 using namespace vsh;
@@ -764,40 +807,17 @@ vsh_status vsh_shower_records(vsh_ctx* ctx, const vsh_request* req, const uint64
     set_error(ctx, "vsh_shower_records runs the plain form with host inputs");
     return VSH_E_INVALID;
   }
-  for (uint64_t e = 0; e < req->n_events; ++e) {
-    if (offsets[e + 1] < offsets[e] || offsets[e + 1] - offsets[e] > req->max_partons ||
-        offsets[e + 1] - offsets[e] < 2) {
-      set_error(ctx, "event %llu: parton count must be in 2..max_partons", (unsigned long long)e);
-      return VSH_E_INVALID;
-    }
-    // every colour line must have exactly one start and one end
-    std::vector<int> seen_c(kMaxCap * 2 + 2, 0), seen_a(kMaxCap * 2 + 2, 0);
-    double E = 0.0;
-    for (uint64_t a = offsets[e]; a < offsets[e + 1]; ++a) {
-      const int f = pid[a];
-      const bool q = f >= 1 && f <= 5, qb = f <= -1 && f >= -5, g = f == 21;
-      if (!(q || qb || g) || (q && (col[a] == 0 || acol[a] != 0)) || (qb && (col[a] != 0 || acol[a] == 0)) ||
-          (g && (col[a] == 0 || acol[a] == 0)) || col[a] > 2 * kMaxCap || acol[a] > 2 * kMaxCap) {
-        set_error(ctx, "event %llu parton %llu: bad flavour/colour", (unsigned long long)e,
-                  (unsigned long long)(a - offsets[e]));
-        return VSH_E_INVALID;
-      }
-      if (col[a]) seen_c[col[a]]++;
-      if (acol[a]) seen_a[acol[a]]++;
-      E += p[4 * a];
-    }
-    for (size_t c = 0; c < seen_c.size(); ++c)
-      if (seen_c[c] != seen_a[c] || seen_c[c] > 1) {
-        set_error(ctx, "event %llu: colour line %zu is not closed once", (unsigned long long)e, c);
-        return VSH_E_INVALID;
-      }
-    if (!(E > 0.0)) {
-      set_error(ctx, "event %llu: total energy must be > 0", (unsigned long long)e);
-      return VSH_E_INVALID;
-    }
-  }
+  // the counts here, flavours and colours on the device as the events are
+  // loaded; a request that fails either is gone through again for its first
+  // fault
+  bool counts = true;
+  for (uint64_t e = 0; e < req->n_events; ++e)
+    counts = counts && offsets[e + 1] >= offsets[e] && offsets[e + 1] - offsets[e] <= req->max_partons &&
+             offsets[e + 1] - offsets[e] >= 2;
+  if (!counts) return explain_starts(ctx, req, offsets, p, pid, col, acol);
   (void)hipSetDevice(ctx->device);
-  return generate_plain(ctx, req, offsets, p, pid, col, acol, out);
+  rc = generate_plain(ctx, req, offsets, p, pid, col, acol, out);
+  return rc == VSH_E_INVALID ? explain_starts(ctx, req, offsets, p, pid, col, acol) : rc;
 }
 
 uint64_t vsh_workspace_size(const vsh_request* req) {

@@ -2,7 +2,7 @@
 // observables pass shared by both forms.
 //
 //   k_me             LO matrix element and event initialisation (App. B)
-//   k_init_records   colour-partner links for caller-supplied initial states
+//   k_load_records   caller-supplied initial states into records, checked
 //   k_shower_plain   thread per event, the whole veto loop in one launch
 //                    (App. A / C: select winner, cutoff, alpha_s, veto, split)
 //   k_obs            validation, Durham y23/y34, thrust, C, rho_H, B_T/B_W
@@ -32,24 +32,65 @@ __global__ void __launch_bounds__(256) k_me(Records r, Summary s, EventInputs in
   s.i[kSiFlavour * s.stride + e] = m.f;
 }
 
-// Caller-supplied starts: partner links from the colour labels.
-__global__ void __launch_bounds__(256) k_init_records(Records r, Summary s, uint32_t n) {
-  const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
+// Caller-supplied starts (CSR arrays, as the caller laid them out) into the
+// slot-major records, kLoadLanes lanes per event: flavours and colours
+// checked, partner links from the colour labels, the event's sqrt(s) as the
+// sum of its energies in order.  Done on the host this was a pass over
+// capacity x events of mostly empty slots, their upload, and two label tables
+// cleared per event: 23 of the 26 ms of a 20011-event call.  *bad: the first
+// event that fails a check (its record is not used then); offsets have been
+// checked by the host.
+__global__ void __launch_bounds__(256) k_load_records(Records r, Summary s, CsrStarts in, uint32_t n, double* ecm,
+                                                      unsigned long long* bad) {
+  const uint32_t e = (blockIdx.x * 256 + threadIdx.x) / kLoadLanes, lane = threadIdx.x % kLoadLanes;
   if (e >= n) return;
-  const int np = s.i[kSiN * s.stride + e];
-  for (int a = 0; a < np; ++a) {
-    const uint16_t ca = r.col[(uint64_t)a * r.stride + e];
-    const uint16_t aa = r.acol[(uint64_t)a * r.stride + e];
+  const uint64_t o = in.off[e] - in.off[0];
+  const int np = (int)(in.off[e + 1] - in.off[e]);
+  bool ok = true;
+  for (int a = (int)lane; a < np; a += (int)kLoadLanes) {
+    const int f = in.pid[o + a];
+    const uint32_t ca = in.col[o + a], aa = in.acol[o + a];
+    const bool q = f >= 1 && f <= 5, qb = f <= -1 && f >= -5, g = f == kGluon;
+    if (!(q || qb || g) || (q && (ca == 0 || aa != 0)) || (qb && (ca != 0 || aa == 0)) || (g && (ca == 0 || aa == 0)) ||
+        ca > 2 * kMaxCount || aa > 2 * kMaxCount)
+      ok = false;
+    // every colour line has exactly one start and one end
+    uint32_t starts_c = 0, ends_c = 0, starts_a = 0, ends_a = 0;
     uint16_t cp = kNoPartner, ap = kNoPartner;
     for (int b = 0; b < np; ++b) {
-      if (b == a) continue;
-      if (ca != 0 && r.acol[(uint64_t)b * r.stride + e] == ca && cp == kNoPartner) cp = (uint16_t)b;
-      if (aa != 0 && r.col[(uint64_t)b * r.stride + e] == aa && ap == kNoPartner) ap = (uint16_t)b;
+      const uint32_t cb = in.col[o + b], ab = in.acol[o + b];
+      starts_c += cb == ca;
+      ends_c += ab == ca;
+      starts_a += cb == aa;
+      ends_a += ab == aa;
+      if (b != a && ca != 0 && ab == ca && cp == kNoPartner) cp = (uint16_t)b;
+      if (b != a && aa != 0 && cb == aa && ap == kNoPartner) ap = (uint16_t)b;
     }
-    r.cpart[(uint64_t)a * r.stride + e] = cp;
-    r.apart[(uint64_t)a * r.stride + e] = ap;
+    if ((ca != 0 && (starts_c != 1 || ends_c != 1)) || (aa != 0 && (starts_a != 1 || ends_a != 1))) ok = false;
+    const double* p = in.p + 4 * (o + a);
+    const uint64_t to = (uint64_t)a * r.stride + e;
+    r.E[to] = p[0];
+    r.x[to] = p[1];
+    r.y[to] = p[2];
+    r.z[to] = p[3];
+    r.pid[to] = (int8_t)f;
+    r.col[to] = (uint16_t)ca;
+    r.acol[to] = (uint16_t)aa;
+    r.cpart[to] = cp;
+    r.apart[to] = ap;
   }
-  s.d[kSdW * s.stride + e] = 1.0;
+  if (lane == 0) {
+    double sum = 0.0;
+    for (int a = 0; a < np; ++a) sum += in.p[4 * (o + a)];
+    if (!(sum > 0.0)) ok = false;
+    ecm[e] = sum;
+    s.d[kSdW * s.stride + e] = 1.0;
+    s.d[kSdCos * s.stride + e] = 0.0;
+    s.d[kSdPhi * s.stride + e] = 0.0;
+    s.i[kSiN * s.stride + e] = np;
+    s.i[kSiFlavour * s.stride + e] = 0;
+  }
+  if (!ok) atomicMin(bad, (unsigned long long)e);
 }
 
 // Plain form: each thread evolves its event to the cutoff in one launch.
@@ -891,11 +932,11 @@ void launch_me(const Records& r, const Summary& s, const EventInputs& in, uint32
   hipLaunchKernelGGL(k_me, dim3(blocks_for(n, 256)), dim3(256), 0, st, r, s, in, n, zero_hist);
 }
 
-void launch_shower_init_records(const Records& r, const Summary& s, const EventInputs& in,
-                                uint32_t n, hipStream_t st) {
-  (void)in;
+void launch_load_records(const Records& r, const Summary& s, const CsrStarts& in, uint32_t n, double* ecm,
+                         unsigned long long* bad, hipStream_t st) {
   if (!n) return;
-  hipLaunchKernelGGL(k_init_records, dim3(blocks_for(n, 256)), dim3(256), 0, st, r, s, n);
+  hipLaunchKernelGGL(k_load_records, dim3(blocks_for((uint64_t)n * kLoadLanes, 256)), dim3(256), 0, st, r, s, in, n,
+                     ecm, bad);
 }
 
 void launch_shower_plain(const Records& r, const Summary& s, const EventInputs& in, uint32_t n,

@@ -73,6 +73,16 @@ struct EventInputs {
   __device__ __forceinline__ double tcut_of(uint64_t e) const { return tcut ? tcut[e] : tcut0; }
 };
 
+// caller-supplied starts of a chunk of events on the device: parton a of
+// event e at index off[e] - off[0] + a of the others
+struct CsrStarts {
+  const uint64_t* off;  // [n + 1]
+  const double* p;      // [total][4]
+  const int8_t* pid;
+  const uint16_t *col, *acol;
+};
+constexpr uint32_t kLoadLanes = 16;  // lanes per event of k_load_records
+
 struct HistRanges {
   double lo[kNObs], hi[kNObs];
 };
@@ -161,6 +171,6 @@ void launch_shower_plain(const Records& r, const Summary& s, const EventInputs& 
                          uint32_t block, uint32_t waves, hipStream_t st);
 void launch_obs(const Records& r, const Summary& s, const EventInputs& in, const Scratch& sc,
                 uint32_t n, double* hist, hipStream_t st);
-void launch_shower_init_records(const Records& r, const Summary& s, const EventInputs& in,
-                                uint32_t n, hipStream_t st);
+void launch_load_records(const Records& r, const Summary& s, const CsrStarts& in, uint32_t n, double* ecm,
+                         unsigned long long* bad, hipStream_t st);
 }  // namespace vsh
