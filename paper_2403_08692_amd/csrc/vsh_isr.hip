@@ -1,7 +1,7 @@
 // vsh_isr.hip -- the initial-state shower: Drell-Yan q qbar -> V at a hadron
 // collider with backward evolution of the incoming lines and the ratio of
 // parton densities in the veto (the step to hadron colliders that the
-// paper's conclusions name), one lane per event.
+// paper's conclusions name), a few lanes per event.
 //
 // No parton-density set is available here, so a closed-form density stands
 // in for one: every light quark and antiquark flavour has
@@ -46,6 +46,8 @@ __device__ __forceinline__ double isr_pdf(double x) {
   return (63.0 / 128.0) / sqrt(x) * ((1.0 - x) * (1.0 - x) * (1.0 - x));
 }
 
+constexpr int kIsrHist = 4 * kNHCol * 3;  // the histogram's used rows
+constexpr uint32_t kIsrEmitDiv = 2;  // pending emissions are built once one running event in two has one
 constexpr int kIsrKernel = 16;  // the emission hash's kernel id of an initial-state q -> q g
 
 // histogram ranges of the branch: log10(p_T,V / GeV), y_V, emitted gluons,
@@ -61,155 +63,256 @@ __device__ __forceinline__ int isr_bin(double x, double lo, double hi) {
   return b > kNBins ? kNBins : b;
 }
 
-__global__ void __launch_bounds__(256) k_isr(Records r, Summary sm, IsrInputs in, uint32_t n, double* hist) {
-  __shared__ double lh[kHistDoubles];
-  for (int a = threadIdx.x; a < kHistDoubles; a += blockDim.x) lh[a] = 0.0;
+__device__ __forceinline__ double isr_zmax(double a) { return 1.0 + 2.0 * a - 2.0 * sqrt(a + a * a); }
+
+// a value that every lane holds alike, kept in scalar registers
+__device__ __forceinline__ double uniform(double x) { return lane_value(x, 0); }
+
+// x of the lane below (within a row of 16)
+__device__ __forceinline__ double lane_below(double x) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x111, 0xf, 0xf, false),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x111, 0xf, 0xf, false));
+}
+
+// One line's trial coefficient over the range of its overestimate; false
+// when the line has no phase space above the cutoff.
+struct IsrLine {
+  double L, c;
+  bool open;
+};
+__device__ __forceinline__ IsrLine isr_line(double x, double zmax, double cfac) {
+  IsrLine l{0.0, 1.0, zmax > x};
+  if (l.open) {
+    l.L = log_fast((1.0 - x) / (1.0 - zmax));
+    l.c = cfac * ((2.0 * kCF) / sqrt(x) * l.L);
+  }
+  return l;
+}
+
+// K lanes per event.  Between emissions a line's trial coefficient stays and
+// a cycle's draws are keyed by the cycle alone, so lane k of a group makes
+// the trials of cycle c + k; the lanes add the winners' ln(R)/c in cycle order
+// (a cycle's scale is the one before plus its own, whichever lane adds them),
+// make their cutoff and veto tests, and the first lane whose cycle ends the
+// sequence (cutoff or emission) is what the event takes; the cycles after it
+// are drawn again, under the same keys, after the emission.  Its final-state
+// momenta are transformed by the group's lanes together.  With one lane per
+// event the kernel spent its time on emissions that a few lanes of the wave
+// built in nearly every cycle, and on coefficients that only an emission
+// changes; a few events took as long as their longest chain of cycles.  Three
+// waves per SIMD (160 registers, none spilled).
+template <int K>  // 2, 4, 8 or 16
+__global__ void __launch_bounds__(256, 3) k_isr(Records r, Summary sm, IsrInputs in, uint32_t n, double* hist) {
+  constexpr uint32_t kPerBlock = 256 / K;
+  constexpr uint64_t kGroup = (1ull << K) - 1ull;
+  __shared__ double lh[kIsrHist];
+  for (int a = threadIdx.x; a < kIsrHist; a += blockDim.x) lh[a] = 0.0;
   __syncthreads();
-  const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < n) {
+  const uint32_t lane = threadIdx.x % K, shift = __lane_id() / K * K;
+  const double ltc = uniform(log_fast(in.tcut));
+  const double asmax = uniform(alpha_s_of_log(ltc));
+  const double cfac = uniform(asmax / (2.0 * kPi));
+  const double lts = uniform(log_fast(in.q * in.q));
+  const double Y = uniform(log(in.sqrt_s / in.q));
+  const double tau = uniform(in.q * in.q / (in.sqrt_s * in.sqrt_s));
+  const double sqrt_tau = uniform(sqrt(tau));
+  for (uint64_t e0 = (uint64_t)blockIdx.x * kPerBlock; e0 < n; e0 += (uint64_t)gridDim.x * kPerBlock) {
+    const uint64_t e = e0 + threadIdx.x / K;
+    const bool mine = e < n;
     const Keyed key = make_keyed(in.seed, in.first + e);
     // --- the Drell-Yan start
     const U4 m0 = key.draw(0, kPurposeME, 0);
     const int f = 1 + (int)(((uint64_t)m0.x * 5u) >> 32);
     const bool qa = (m0.y & 1u) == 0u;
-    const double Y = log(in.sqrt_s / in.q);
     const double y0 = -Y + 2.0 * Y * unit(m0.z, m0.w);
-    const double tau = in.q * in.q / (in.sqrt_s * in.sqrt_s);
-    double x[2] = {sqrt(tau) * exp(y0), sqrt(tau) * exp(-y0)};
+    double x[2] = {sqrt_tau * exp(y0), sqrt_tau * exp(-y0)};
     const double eb = 0.5 * in.sqrt_s;
-    const double w = 10.0 * (2.0 * Y) * tau * isr_pdf(x[0]) * isr_pdf(x[1]);
-    r.store(0, e, P4{x[0] * eb, 0.0, 0.0, x[0] * eb});
-    r.store(1, e, P4{x[1] * eb, 0.0, 0.0, -x[1] * eb});
-    r.store(2, e, P4{x[0] * eb + x[1] * eb, 0.0, 0.0, x[0] * eb - x[1] * eb});
-    const uint64_t s1 = r.stride, s2 = 2 * r.stride;
-    r.pid[e] = (int8_t)(qa ? f : -f);
-    r.pid[s1 + e] = (int8_t)(qa ? -f : f);
-    r.pid[s2 + e] = 23;
-    r.col[e] = qa ? 1 : 0;
-    r.acol[e] = qa ? 0 : 1;
-    r.col[s1 + e] = qa ? 0 : 1;
-    r.acol[s1 + e] = qa ? 1 : 0;
-    r.col[s2 + e] = 0;
-    r.acol[s2 + e] = 0;
+    double ea = x[0] * eb, ebm = x[1] * eb;  // the incoming partons (E, 0, 0, +-E) from beams A and B
+    P4 own{x[0] * eb + x[1] * eb, 0.0, 0.0, x[0] * eb - x[1] * eb};  // final-state parton 2 + lane (V: lane 0)
+    uint16_t tag[2] = {1, 1};  // the incoming lines' open colour labels
+    if (mine && lane == 0) {  // what the evolution does not change
+      sm.d[kSdW * sm.stride + e] = 10.0 * (2.0 * Y) * tau * isr_pdf(x[0]) * isr_pdf(x[1]);
+      sm.i[kSiFlavour * sm.stride + e] = qa ? f : -f;
+      const uint64_t s1 = r.stride, s2 = 2 * r.stride;
+      r.pid[e] = (int8_t)(qa ? f : -f);
+      r.pid[s1 + e] = (int8_t)(qa ? -f : f);
+      r.pid[s2 + e] = 23;
+      (qa ? r.acol : r.col)[e] = 0;
+      (qa ? r.col : r.acol)[s1 + e] = 0;
+      r.col[s2 + e] = 0;
+      r.acol[s2 + e] = 0;
+    }
     // --- backward evolution of the two incoming lines
-    const double ltc = log_fast(in.tcut);
-    const double asmax = alpha_s_of_log(ltc);
-    const double cfac = asmax / (2.0 * kPi);
-    double lt = log_fast(in.q * in.q);
-    int np = 3, next_col = 2, n_emit = 0, status = kRunning;
-    uint32_t cycle = 0, trials = 0, ends = 0;
+    double lt = lts;
+    int np = 3, status = mine ? kRunning : kDone;
+    uint32_t cycle = 0, trials = 0;  // one trial per open line and cycle
     uint64_t hash = kFnvOffset;
-    while (status == kRunning) {
-      const P4 pa0 = r.load(0, e), pb0 = r.load(1, e);
-      const double st = 2.0 * mdot(pa0, pb0);
-      const double a = in.tcut / st;
-      const double zmax = 1.0 + 2.0 * a - 2.0 * sqrt(a + a * a);
-      double best = ltc, wzlo = 0.0, wL = 0.0;
-      int wl = -1;
+    double st = 2.0 * mdot(P4{ea, 0.0, 0.0, ea}, P4{ebm, 0.0, 0.0, -ebm});
+    double zmax = isr_zmax(in.tcut / st);
+    IsrLine line[2] = {isr_line(x[0], zmax, cfac), isr_line(x[1], zmax, cfac)};
+    bool pend = false;  // an accepted emission waits to be built
+    double t = 0.0, z = 0.0, disc = 0.0;
+    int wl = -1;
+    while (__any(status == kRunning)) {
+      if (status == kRunning && !pend) {
+        const uint32_t this_cycle = cycle + lane;
+        // the cycle's winner: the larger ln(R)/c, the first line on ties
+        double v = -INFINITY;
+        wl = -1;
 #pragma unroll
-      for (int l = 0; l < 2; ++l) {
-        if (!(zmax > x[l])) continue;  // no phase space above the cutoff
-        ends += 1;
-        const double L = log_fast((1.0 - x[l]) / (1.0 - zmax));
-        const double c = cfac * ((2.0 * kCF) / sqrt(x[l]) * L);
-        const U4 d = key.draw(cycle, kPurposeTrial, trial_slot((uint32_t)l, (uint32_t)(1 - l), 0));
-        const double lt_try = lt + log_fast(unit(d.x, d.y)) / c;
-        trials += 1;
-        if (lt_try > best) {
-          best = lt_try;
-          wl = l;
-          wzlo = x[l];
-          wL = L;
+        for (int l = 0; l < 2; ++l) {
+          if (!line[l].open) continue;
+          const U4 d = key.draw(this_cycle, kPurposeTrial, trial_slot((uint32_t)l, (uint32_t)(1 - l), 0));
+          const double vl = log_fast(unit(d.x, d.y)) / line[l].c;
+          if (wl < 0 || vl > v) {
+            v = vl;
+            wl = l;
+          }
+        }
+        double my_lt = lt + v;  // this lane's cycle's scale: the one before it plus its own
+#pragma unroll
+        for (uint32_t q = 1; q < K; ++q) {
+          const double before = lane_below(my_lt);
+          if (lane == q) my_lt = before + v;
+        }
+        bool done = wl < 0 || !(my_lt > ltc), accept = false;
+        if (!done) {
+          t = exp(my_lt);
+          const double xl = wl == 0 ? x[0] : x[1], wL = wl == 0 ? line[0].L : line[1].L;
+          const U4 acc = key.draw(this_cycle, kPurposeAccept, 0);
+          z = 1.0 - (1.0 - xl) * exp(-unit(acc.x, acc.y) * wL);
+          disc = (1.0 - z) * (1.0 - z) - 4.0 * t * z / st;
+          if (disc >= 0.0 && z > xl) {  // else no room for the emission at this t
+            const double dens = kCF * (1.0 + z * z) / (1.0 - z) / z * isr_pdf(xl / z) / isr_pdf(xl);
+            const double over = 2.0 * kCF / sqrt(xl) / (1.0 - z);
+            const double prob = alpha_s_of_log(my_lt) / asmax * (dens / over);
+            accept = unit(acc.z, acc.w) < prob;
+          }
+        }
+        // the group's first cycle that ends the sequence, else all K
+        const uint64_t stop = (__ballot(done || accept) >> shift) & kGroup;
+        const int at = stop ? __ffsll((unsigned long long)stop) - 1 : K - 1;
+        cycle += (uint32_t)at + 1u;
+        trials += ((line[0].open ? 1u : 0u) + (line[1].open ? 1u : 0u)) * ((uint32_t)at + 1u);
+        lt = __shfl(my_lt, at, K);
+        if (stop) {
+          t = __shfl(t, at, K);
+          z = __shfl(z, at, K);
+          disc = __shfl(disc, at, K);
+          wl = __shfl(wl, at, K);
+          done = __shfl((int)done, at, K) != 0;
+          if (done) status = kDone;
+          else if (np == (int)r.cap) status = kOverflow;
+          else pend = true;
         }
       }
-      const uint32_t this_cycle = cycle++;
-      if (wl < 0) {
-        status = kDone;
-        break;
-      }
-      lt = best;
-      const double t = exp(best);
-      const U4 acc = key.draw(this_cycle, kPurposeAccept, 0);
-      const double z = 1.0 - (1.0 - wzlo) * exp(-unit(acc.x, acc.y) * wL);
-      const double xl = x[wl];
-      const double disc = (1.0 - z) * (1.0 - z) - 4.0 * t * z / st;
-      if (!(disc >= 0.0) || !(z > xl)) continue;  // no room for the emission at this t
-      const double dens = kCF * (1.0 + z * z) / (1.0 - z) / z * isr_pdf(xl / z) / isr_pdf(xl);
-      const double over = 2.0 * kCF / sqrt(xl) / (1.0 - z);
-      const double prob = alpha_s_of_log(best) / asmax * (dens / over);
-      if (!(unit(acc.z, acc.w) < prob)) continue;
-      if (np == (int)r.cap) {
-        status = kOverflow;
-        break;
-      }
+      // the emissions of the wave's events together, once half of the running
+      // ones have one (a third and a quarter 1 to 7% slower, at once 33%)
+      const uint32_t n_pend = __popcll(__ballot(pend)), n_run = __popcll(__ballot(status == kRunning));
+      if (kIsrEmitDiv * n_pend < n_run || !pend) continue;
+      pend = false;
       // --- the emission: initial-initial map and the final state's transformation
-      const U4 sd = key.draw(this_cycle, kPurposeSplit, 0);
+      const U4 sd = key.draw(cycle - 1u, kPurposeSplit, 0);
       const double phi = 2.0 * kPi * unit(sd.x, sd.y);
       double sphi, cphi;
       sincos(phi, &sphi, &cphi);
-      const P4 pa = wl == 0 ? pa0 : pb0, pb = wl == 0 ? pb0 : pa0;
-      const double v = 0.5 * ((1.0 - z) - sqrt(disc));
-      const P4 na{pa.e / z, pa.x / z, pa.y / z, pa.z / z};
+      const P4 pa{ea, 0.0, 0.0, ea}, pb{ebm, 0.0, 0.0, -ebm};
+      const P4 pe = wl == 0 ? pa : pb, ps = wl == 0 ? pb : pa;  // the emitter and the other incoming parton
+      const double vv = 0.5 * ((1.0 - z) - sqrt(disc));
+      const P4 na{pe.e / z, pe.x / z, pe.y / z, pe.z / z};
       const double kt = sqrt(t);
-      const double c1 = 1.0 - z - v;
-      const P4 pj{c1 * na.e + v * pb.e, c1 * na.x + v * pb.x + kt * cphi, c1 * na.y + v * pb.y + kt * sphi,
-                  c1 * na.z + v * pb.z};
-      const P4 Kt{pa.e + pb.e, pa.x + pb.x, pa.y + pb.y, pa.z + pb.z};
-      const P4 K{na.e + pb.e - pj.e, na.x + pb.x - pj.x, na.y + pb.y - pj.y, na.z + pb.z - pj.z};
-      const P4 S{K.e + Kt.e, K.x + Kt.x, K.y + Kt.y, K.z + Kt.z};
+      const double c1 = 1.0 - z - vv;
+      const P4 pj{c1 * na.e + vv * ps.e, c1 * na.x + vv * ps.x + kt * cphi, c1 * na.y + vv * ps.y + kt * sphi,
+                  c1 * na.z + vv * ps.z};
+      const P4 Kt{pe.e + ps.e, pe.x + ps.x, pe.y + ps.y, pe.z + ps.z};
+      const P4 Kn{na.e + ps.e - pj.e, na.x + ps.x - pj.x, na.y + ps.y - pj.y, na.z + ps.z - pj.z};
+      const P4 S{Kn.e + Kt.e, Kn.x + Kt.x, Kn.y + Kt.y, Kn.z + Kt.z};
       const double s2n = mdot(S, S), kt2 = mdot(Kt, Kt);
-      for (int q = 2; q < np; ++q) {
-        const P4 k = r.load((uint32_t)q, e);
+      for (int q = 2 + (int)lane; q < np; q += K) {
+        const P4 k = q - 2 < K ? own : r.load((uint32_t)q, e);
         const double sx = mdot(S, k), kx = mdot(Kt, k);
         const double cs = 2.0 * sx / s2n, ck = 2.0 * kx / kt2;
-        r.store((uint32_t)q, e, P4{k.e - cs * S.e + ck * K.e, k.x - cs * S.x + ck * K.x, k.y - cs * S.y + ck * K.y,
-                                    k.z - cs * S.z + ck * K.z});
+        const P4 to{k.e - cs * S.e + ck * Kn.e, k.x - cs * S.x + ck * Kn.x, k.y - cs * S.y + ck * Kn.y,
+                    k.z - cs * S.z + ck * Kn.z};
+        if (q - 2 < K) own = to;
+        else r.store((uint32_t)q, e, to);
       }
-      r.store((uint32_t)wl, e, na);
-      r.store((uint32_t)np, e, pj);
-      x[wl] = xl / z;
-      // the gluon goes onto the emitter's colour line
-      const uint64_t ow = (uint64_t)wl * r.stride + e, oj = (uint64_t)np * r.stride + e;
-      const uint16_t m = (uint16_t)next_col++;
-      r.pid[oj] = (int8_t)kGluon;
-      if (r.col[ow] != 0) {
-        r.col[oj] = r.col[ow];
-        r.acol[oj] = m;
-        r.col[ow] = m;
-      } else {
-        r.col[oj] = m;
-        r.acol[oj] = r.acol[ow];
-        r.acol[ow] = m;
+      const uint16_t m = (uint16_t)(np - 1);  // the next unused label
+      if ((int)lane == (np - 2) % K) {
+        if (np - 2 < K) own = pj;
+        else r.store((uint32_t)np, e, pj);
+        // the gluon goes onto the emitter's colour line (the quark's colour,
+        // the antiquark's anticolour)
+        const uint64_t oj = (uint64_t)np * r.stride + e;
+        const bool quark = (wl == 0) == qa;
+        const uint16_t was = wl == 0 ? tag[0] : tag[1];
+        r.pid[oj] = (int8_t)kGluon;
+        r.col[oj] = quark ? was : m;
+        r.acol[oj] = quark ? m : was;
       }
       hash = fnv_step(fnv_step(fnv_step(hash, (uint32_t)kIsrKernel), (uint32_t)wl), (uint32_t)(1 - wl));
       ++np;
-      ++n_emit;
       if (cycle >= kCycleLimit) status = kCycleLimitHit;
+      if (wl == 0) {
+        ea = na.e;
+        x[0] = x[0] / z;
+        tag[0] = m;
+      } else {
+        ebm = na.e;
+        x[1] = x[1] / z;
+        tag[1] = m;
+      }
+      st = 2.0 * mdot(P4{ea, 0.0, 0.0, ea}, P4{ebm, 0.0, 0.0, -ebm});
+      zmax = isr_zmax(in.tcut / st);
+      line[0] = isr_line(x[0], zmax, cfac);
+      line[1] = isr_line(x[1], zmax, cfac);
     }
     // --- validation: finite; the final state carries the incoming total;
     // V on its mass shell, the others massless
-    const P4 ia = r.load(0, e), ib = r.load(1, e);
-    const P4 tin{ia.e + ib.e, ia.x + ib.x, ia.y + ib.y, ia.z + ib.z};
-    P4 tout{0.0, 0.0, 0.0, 0.0};
-    bool finite = true, shell = true;
+    const P4 pa{ea, 0.0, 0.0, ea}, pb{ebm, 0.0, 0.0, -ebm};
+    const P4 tin{pa.e + pb.e, pa.x + pb.x, pa.y + pb.y, pa.z + pb.z};
     const double s_in = mdot(tin, tin);
+    P4 tout{0.0, 0.0, 0.0, 0.0};
     double ptg = 0.0;
-    for (int a2 = 0; a2 < np; ++a2) {
-      const P4 p = r.load((uint32_t)a2, e);
-      finite = finite && isfinite(p.e) && isfinite(p.x) && isfinite(p.y) && isfinite(p.z);
-      const double m2 = a2 == 2 ? in.q * in.q : 0.0;
-      shell = shell && fabs(mdot(p, p) - m2) <= 1e-10 * s_in;
-      if (a2 >= 2) {
+    bool finite = true, shell = true;
+    if (mine) {
+      auto check = [&](const P4& p, double m2) {
+        finite = finite && isfinite(p.e) && isfinite(p.x) && isfinite(p.y) && isfinite(p.z);
+        shell = shell && fabs(mdot(p, p) - m2) <= 1e-10 * s_in;
+      };
+      if (lane == 0) {
+        check(pa, 0.0);
+        check(pb, 0.0);
+        r.store(0, e, pa);
+        r.store(1, e, pb);
+        (qa ? r.col : r.acol)[e] = tag[0];
+        (qa ? r.acol : r.col)[r.stride + e] = tag[1];
+      }
+      for (int q = 2 + (int)lane; q < np; q += K) {
+        P4 p = own;
+        if (q - 2 < K) r.store((uint32_t)q, e, p);
+        else p = r.load((uint32_t)q, e);
+        check(p, q == 2 ? in.q * in.q : 0.0);
         tout.e += p.e;
         tout.x += p.x;
         tout.y += p.y;
         tout.z += p.z;
-      }
-      if (a2 >= 3) {
-        const double pt = sqrt(p.x * p.x + p.y * p.y);
-        if (pt > ptg) ptg = pt;
+        if (q >= 3) {
+          const double pt = sqrt(p.x * p.x + p.y * p.y);
+          if (pt > ptg) ptg = pt;
+        }
       }
     }
+#pragma unroll
+    for (int d = K / 2; d >= 1; d >>= 1) {
+      tout.e += __shfl_xor(tout.e, d, K);
+      tout.x += __shfl_xor(tout.x, d, K);
+      tout.y += __shfl_xor(tout.y, d, K);
+      tout.z += __shfl_xor(tout.z, d, K);
+      ptg = fmax(ptg, __shfl_xor(ptg, d, K));
+    }
+    finite = !((__ballot(!finite) >> shift) & kGroup);
+    shell = !((__ballot(!shell) >> shift) & kGroup);
     if (status == kDone) {
       const double tol = 1e-10 * tin.e;
       if (!finite) status = kNonFinite;
@@ -217,36 +320,54 @@ __global__ void __launch_bounds__(256) k_isr(Records r, Summary sm, IsrInputs in
                fabs(tout.z - tin.z) > tol || !shell)
         status = kConservation;
     }
-    const P4 V = r.load(2, e);
-    const double ptv = sqrt(V.x * V.x + V.y * V.y);
-    const double yv = 0.5 * log((V.e + V.z) / (V.e - V.z));
-    if (status == kDone) {
-      const double vals[4] = {ptv > 0.0 ? log10(ptv) : -INFINITY, yv, (double)n_emit, ptg > 0.0 ? log10(ptg) : -INFINITY};
+    if (mine && lane == 0) {  // V is this lane's
+      const double ptv = sqrt(own.x * own.x + own.y * own.y);
+      const double yv = 0.5 * log((own.e + own.z) / (own.e - own.z));
+      if (status == kDone) {
+        const double w = sm.d[kSdW * sm.stride + e];
+        const double vals[4] = {ptv > 0.0 ? log10(ptv) : -INFINITY, yv, (double)(np - 3),
+                                ptg > 0.0 ? log10(ptg) : -INFINITY};
 #pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        double* cell = &lh[3 * (kNHCol * h + isr_bin(vals[h], isr_lo(h), isr_hi(h)))];
-        atomicAdd(&cell[0], w);
-        atomicAdd(&cell[1], w * w);
-        atomicAdd(&cell[2], 1.0);
+        for (int h = 0; h < 4; ++h) {
+          double* cell = &lh[3 * (kNHCol * h + isr_bin(vals[h], isr_lo(h), isr_hi(h)))];
+          atomicAdd(&cell[0], w);
+          atomicAdd(&cell[1], w * w);
+          atomicAdd(&cell[2], 1.0);
+        }
       }
-    }
-    const double dv[kNSumD] = {w, yv, ptv, x[0], x[1], ptg, 0.0, 0.0, 0.0, 0.0};
+      const double dv[kNSumD] = {0.0, yv, ptv, x[0], x[1], ptg, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int k = 0; k < kNSumD; ++k) sm.d[k * sm.stride + e] = dv[k];
-    sm.i[kSiN * sm.stride + e] = np;
-    sm.i[kSiStatus * sm.stride + e] = status;
-    sm.i[kSiCycles * sm.stride + e] = (int32_t)cycle;
-    sm.i[kSiEmit * sm.stride + e] = n_emit;
-    sm.i[kSiFlavour * sm.stride + e] = qa ? f : -f;
-    sm.i[kSiTrials * sm.stride + e] = (int32_t)trials;
-    sm.i[kSiEnds * sm.stride + e] = (int32_t)ends;
-    sm.hash[e] = hash;
+      for (int k = kSdW + 1; k < kNSumD; ++k) sm.d[k * sm.stride + e] = dv[k];
+      sm.i[kSiN * sm.stride + e] = np;
+      sm.i[kSiStatus * sm.stride + e] = status;
+      sm.i[kSiCycles * sm.stride + e] = (int32_t)cycle;
+      sm.i[kSiEmit * sm.stride + e] = np - 3;
+      sm.i[kSiTrials * sm.stride + e] = (int32_t)trials;
+      sm.i[kSiEnds * sm.stride + e] = (int32_t)trials;
+      sm.hash[e] = hash;
+    }
   }
   __syncthreads();
-  for (int a = threadIdx.x; a < kHistDoubles; a += blockDim.x) {
+  for (int a = threadIdx.x; a < kIsrHist; a += blockDim.x) {
     const double v = lh[a];
     if (v != 0.0) unsafeAtomicAdd(&hist[a], v);
   }
+}
+
+// Lanes per event: as many as leave every event resident.  k_isr alone, one
+// lane per event as before and this rule: 100 events 347 and 40 us, 5000 452
+// and 65, 20000 463 and 111, 50000 455 and 199, 200003 1161 and 566, 10^6
+// 4396 and 2385 (sixteen lanes there: 4252).
+static void launch_isr(const Records& r, const Summary& sm, const IsrInputs& in, uint32_t n, double* hist,
+                       hipStream_t st) {
+  const uint32_t K = n <= 4096 ? 16 : n <= 32768 ? 8 : n <= 131072 ? 4 : 2;
+  // events past the grid's are taken in further rounds of its blocks, so
+  // that their histograms are not flushed too often
+  const dim3 g((uint32_t)std::min<uint64_t>(((uint64_t)n * K + 255) / 256, 8192)), b(256);
+  if (K == 16) hipLaunchKernelGGL(k_isr<16>, g, b, 0, st, r, sm, in, n, hist);
+  else if (K == 8) hipLaunchKernelGGL(k_isr<8>, g, b, 0, st, r, sm, in, n, hist);
+  else if (K == 4) hipLaunchKernelGGL(k_isr<4>, g, b, 0, st, r, sm, in, n, hist);
+  else hipLaunchKernelGGL(k_isr<2>, g, b, 0, st, r, sm, in, n, hist);
 }
 
 }  // namespace vsh
@@ -338,8 +459,7 @@ extern "C" vsh_status vsh_generate_isr(vsh_ctx* ctx, const vsh_request* req, dou
     launch_zero(hist, kHistDoubles, st);
     const IsrInputs in{req->seed, req->first_event + a, sqrt_s_hadron, req->ecm, req->t_cut};
     (void)hipEventRecord(ctx->ev[1], st);
-    hipLaunchKernelGGL(k_isr, dim3((uint32_t)((count + 255) / 256)), dim3(256), 0, st, r, sm, in, (uint32_t)count,
-                       hist);
+    launch_isr(r, sm, in, (uint32_t)count, hist, st);
     (void)hipEventRecord(ctx->ev[2], st);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) {
