@@ -285,7 +285,7 @@ uint64_t vsh_workspace_size(const vsh_request *req);
    vsh_workspace_size(req) must not exceed it); every device that runs the
    library holds its own copy until the process ends.  The call allocates
    nothing (no hipMalloc, no pinned memory, no library allocation), only
-   enqueues kernels and device-to-device copies on `stream`, and returns.
+   enqueues kernels on `stream`, and returns.
    Arguments, outputs and per-event inputs as for vsh_generate_into.
    All calls on one device share that device's array and nothing in it needs
    to start at zero, but calls whose work overlaps on one device (two host

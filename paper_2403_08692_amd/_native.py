@@ -154,35 +154,68 @@ def _check(code, ctx_ptr=None):
         raise VshError(code, msg.decode() if msg else "")
 
 
-def _arr(ptr, count, dtype):
-    if not ptr or count == 0:
-        return None
-    return np.ctypeslib.as_array(ptr, shape=(count,)).astype(dtype, copy=True)
+class _Result:
+    """Owns a library result; frees it when the last array that views it goes."""
+
+    def __init__(self, ptr):
+        self._ptr, self._free = ptr, load().vsh_result_free
+
+    def __del__(self):
+        if self._ptr:
+            self._free(self._ptr)
+            self._ptr = None
 
 
-def result_to_dict(res: vsh_result) -> dict:
+class _Span:
+    """One array inside a result, for numpy.asarray: the array keeps this
+    object, and through it the result, alive."""
+
+    __slots__ = ("__array_interface__", "_owner")
+
+    def __init__(self, addr, shape, typestr, owner):
+        self.__array_interface__ = {"data": (addr, False), "shape": shape, "typestr": typestr, "version": 3}
+        self._owner = owner
+
+
+# Arrays of at least this many bytes view the result's memory instead of
+# copying it (a copy's first touch of fresh pages costs more than the transfer
+# from the device); smaller results are copied, so that little memory is held.
+_VIEW_BYTES = 1 << 18
+
+
+def result_to_dict(ptr) -> dict:
+    """The result at ptr (taken over: freed here, or with the arrays that view
+    it) as a dict of numbers and numpy arrays."""
+    owner, res = _Result(ptr), ptr.contents
     n = res.n_events
+
+    def arr(p, shape, typestr, nbytes):
+        if nbytes == 0:
+            return np.zeros(shape, typestr)
+        span = _Span(C.addressof(p.contents), shape, typestr, owner)
+        return np.asarray(span) if nbytes >= _VIEW_BYTES else np.array(span)
+
     out = dict(n_events=n, n_done=res.n_done, n_overflow=res.n_overflow, n_nonfinite=res.n_nonfinite,
                n_conservation=res.n_conservation, n_cycle_limit=res.n_cycle_limit, sum_w=res.sum_w, sum_w2=res.sum_w2,
                total_cycles=res.total_cycles, total_trials=res.total_trials, total_ends=res.total_ends,
                total_emissions=res.total_emissions, max_cycles=res.max_cycles,
                t_me_ms=res.t_me_ms, t_shower_ms=res.t_shower_ms, t_obs_ms=res.t_obs_ms,
                t_total_ms=res.t_total_ms, queue_ahead=res.queue_ahead, t_queue_ms=res.t_queue_ms)
-    out["hist"] = _arr(res.hist, HIST_DOUBLES, np.float64).reshape(NOBS, NHCOL, 3)
-    out["hist_lo"] = _arr(res.hist_lo, NOBS, np.float64)
-    out["hist_hi"] = _arr(res.hist_hi, NOBS, np.float64)
+    out["hist"] = arr(res.hist, (NOBS, NHCOL, 3), "<f8", 8 * HIST_DOUBLES)
+    out["hist_lo"] = arr(res.hist_lo, (NOBS,), "<f8", 8 * NOBS)
+    out["hist_hi"] = arr(res.hist_hi, (NOBS,), "<f8", 8 * NOBS)
     if res.sum_d:
-        out["sum_d"] = _arr(res.sum_d, NSUM_D * n, np.float64).reshape(NSUM_D, n)
-        out["sum_i"] = _arr(res.sum_i, NSUM_I * n, np.int32).reshape(NSUM_I, n)
-        out["hash"] = _arr(res.sum_hash, n, np.uint64)
+        out["sum_d"] = arr(res.sum_d, (NSUM_D, n), "<f8", 8 * NSUM_D * n)
+        out["sum_i"] = arr(res.sum_i, (NSUM_I, n), "<i4", 4 * NSUM_I * n)
+        out["hash"] = arr(res.sum_hash, (n,), "<u8", 8 * n)
     if res.rec_offsets:
-        off = _arr(res.rec_offsets, n + 1, np.uint64)
+        off = arr(res.rec_offsets, (n + 1,), "<u8", 8 * (n + 1))
         tot = int(off[-1])
         out["rec_offsets"] = off
-        out["rec_p"] = _arr(res.rec_p, 4 * tot, np.float64).reshape(tot, 4) if tot else np.zeros((0, 4))
-        out["rec_pid"] = _arr(res.rec_pid, tot, np.int8) if tot else np.zeros(0, np.int8)
-        out["rec_col"] = _arr(res.rec_col, tot, np.uint16) if tot else np.zeros(0, np.uint16)
-        out["rec_acol"] = _arr(res.rec_acol, tot, np.uint16) if tot else np.zeros(0, np.uint16)
+        out["rec_p"] = arr(res.rec_p, (tot, 4), "<f8", 32 * tot)
+        out["rec_pid"] = arr(res.rec_pid, (tot,), "|i1", tot)
+        out["rec_col"] = arr(res.rec_col, (tot,), "<u2", 2 * tot)
+        out["rec_acol"] = arr(res.rec_acol, (tot,), "<u2", 2 * tot)
     return out
 
 
@@ -254,10 +287,7 @@ class Context:
                                  ecm_per_event, tcut_per_event, cycle_limit, t_over, mass_c, mass_b)
         res = C.POINTER(vsh_result)()
         _check(load().vsh_generate(self._ptr, C.byref(req), C.byref(res)), self._ptr)
-        try:
-            return result_to_dict(res.contents)
-        finally:
-            load().vsh_result_free(res)
+        return result_to_dict(res)
 
     def generate_isr(self, n_events, sqrt_s_hadron=1960.0, q=91.2, t_cut=1.0, seed=1, first_event=0, max_partons=64,
                      summary=True, records=False):
@@ -267,10 +297,7 @@ class Context:
         req, keep = make_request(n_events, seed, first_event, q, t_cut, max_partons, flags)
         res = C.POINTER(vsh_result)()
         _check(load().vsh_generate_isr(self._ptr, C.byref(req), float(sqrt_s_hadron), C.byref(res)), self._ptr)
-        try:
-            return result_to_dict(res.contents)
-        finally:
-            load().vsh_result_free(res)
+        return result_to_dict(res)
 
     def shower_records(self, offsets, p, pid, col, acol, seed=1, first_event=0, t_cut=1.0, max_partons=64,
                        summary=True, records=True, mass_c=0.0, mass_b=0.0):
@@ -286,10 +313,7 @@ class Context:
         _check(load().vsh_shower_records(self._ptr, C.byref(req), offsets.ctypes.data, p.ctypes.data,
                                          pid.ctypes.data, col.ctypes.data, acol.ctypes.data, C.byref(res)),
                self._ptr)
-        try:
-            return result_to_dict(res.contents)
-        finally:
-            load().vsh_result_free(res)
+        return result_to_dict(res)
 
     def workspace_size(self, req):
         return int(load().vsh_workspace_size(C.byref(req)))
@@ -356,10 +380,7 @@ class Context:
     def wait(self, ticket):
         res = C.POINTER(vsh_result)()
         _check(load().vsh_wait(self._ptr, ticket, C.byref(res)), self._ptr)
-        try:
-            return result_to_dict(res.contents)
-        finally:
-            load().vsh_result_free(res)
+        return result_to_dict(res)
 
     def cancel(self, ticket):
         _check(load().vsh_cancel(self._ptr, ticket), self._ptr)

@@ -94,8 +94,9 @@ vsh_status validate_request(vsh_ctx* ctx, const vsh_request* req, bool need_ener
 }
 
 // ---------------------------------------------------------------------------
-// Plain-form device layout of a chunk of `stride` events with capacity cap:
-// records, Durham scratch, summaries, per-event inputs, histogram.
+// Plain-form device layout of a chunk of n events with capacity cap: records
+// (columns of n rounded up to 64), Durham scratch, the results' span, per-event
+// inputs.
 // ---------------------------------------------------------------------------
 uint64_t plain_bytes_per_event(uint32_t cap, bool massive) {
   return (uint64_t)cap * (4 * 8 + 1 + 4 * 2 + cache_words(massive) * 8) + kNSumD * 8 + kNSumI * 4 + 8 + 2 * 8;
@@ -106,8 +107,9 @@ uint64_t plain_layout_bytes(uint64_t stride, uint32_t cap, bool massive) {
                       kHistDoubles * 8, 256);
 }
 
-PlainLayout carve_plain(void* base, uint64_t stride, uint32_t cap, bool massive) {
+PlainLayout carve_plain(void* base, uint64_t n, uint32_t cap, bool massive) {
   PlainLayout L;
+  const uint64_t stride = align_up(n, 64);
   char* p = static_cast<char*>(base);
   auto take = [&](uint64_t bytes) {
     char* q = p;
@@ -132,13 +134,13 @@ PlainLayout carve_plain(void* base, uint64_t stride, uint32_t cap, bool massive)
     L.sc = carve_obs_scratch(q, stride, cap);
     p = q;
   }
-  L.sum.d = (double*)take(kNSumD * stride * 8);
-  L.sum.i = (int32_t*)take(kNSumI * stride * 4);
-  L.sum.hash = (uint64_t*)take(stride * 8);
-  L.sum.stride = stride;
-  L.ecm = (double*)take(stride * 8);
-  L.tcut = (double*)take(stride * 8);
   L.hist = (double*)take(kHistDoubles * 8);
+  L.sum.i = (int32_t*)take(kNSumI * n * 4);
+  L.sum.d = (double*)take(kNSumD * n * 8);
+  L.sum.hash = (uint64_t*)take(n * 8);
+  L.sum.stride = n;
+  L.ecm = (double*)take(n * 8);
+  L.tcut = (double*)take(n * 8);
   L.end = p;
   return L;
 }
@@ -187,12 +189,69 @@ void HostStage::release() {
   size = 0;
 }
 
+PinnedBlock PinnedPool::acquire(uint64_t bytes) {
+  std::lock_guard<std::mutex> lk(mu);
+  size_t best = idle.size();
+  for (size_t k = 0; k < idle.size(); ++k)
+    if (idle[k].size >= bytes && idle[k].size <= 2 * bytes + (1u << 20) &&
+        (best == idle.size() || idle[k].size < idle[best].size))
+      best = k;
+  if (best < idle.size()) {
+    const PinnedBlock b = idle[best];
+    idle.erase(idle.begin() + (long)best);
+    return b;
+  }
+  const uint64_t size = align_up(bytes, 65536);
+  while (held + size > kMost && !idle.empty()) {  // make room: the oldest first
+    (void)hipHostFree(idle.front().ptr);
+    held -= idle.front().size;
+    idle.erase(idle.begin());
+  }
+  PinnedBlock b;
+  if (held + size > kMost) return b;
+  idle.reserve(idle.size() + 64);  // release() never allocates
+  if (hipHostMalloc(&b.ptr, size, 0) != hipSuccess) {
+    (void)hipGetLastError();
+    b.ptr = nullptr;
+    return b;
+  }
+  b.size = size;
+  held += size;
+  return b;
+}
+
+void PinnedPool::release(PinnedBlock b) {
+  if (!b.ptr) return;
+  std::lock_guard<std::mutex> lk(mu);
+  if (closed || idle.size() == idle.capacity()) {
+    (void)hipHostFree(b.ptr);
+    held -= b.size;
+  } else {
+    idle.push_back(b);
+  }
+}
+
+void PinnedPool::close() {
+  std::lock_guard<std::mutex> lk(mu);
+  closed = true;
+  for (const PinnedBlock& b : idle) {
+    (void)hipHostFree(b.ptr);
+    held -= b.size;
+  }
+  idle.clear();
+}
+
+ResultBox::~ResultBox() {
+  if (!pool) return;
+  pool->release(sum_block);
+  pool->release(rec_block);
+}
+
 // ---------------------------------------------------------------------------
 // result assembly
 // ---------------------------------------------------------------------------
-ResultBox* new_result(uint64_t n_events, bool summary) {
-  ResultBox* b = new (std::nothrow) ResultBox();
-  if (!b) return nullptr;
+ResultBox* new_result(uint64_t n_events, bool summary) try {
+  std::unique_ptr<ResultBox> b(new ResultBox());
   b->hist.assign(kHistDoubles, 0.0);
   b->lo.assign(kNObs, 0.0);
   b->hi.assign(kNObs, 0.0);
@@ -211,8 +270,33 @@ ResultBox* new_result(uint64_t n_events, bool summary) {
   b->pub.n_events = n_events;
   b->pub.n_obs = kNObs;
   b->pub.n_bins = kNBins;
-  return b;
+  return b.release();
+} catch (const std::bad_alloc&) {
+  return nullptr;
 }
+
+ResultBox* new_call_result(vsh_ctx* ctx, const vsh_request* req, bool whole) {
+  const bool summary = req->flags & VSH_SUMMARY;
+  PinnedBlock block;
+  if (whole && summary) block = ctx->pool->acquire(ResultSpan(req->n_events).bytes);
+  ResultBox* box = new_result(req->n_events, summary && !block.ptr);
+  if (!box) {
+    ctx->pool->release(block);
+    set_error(ctx, "host allocation failed");
+    return nullptr;
+  }
+  box->pool = ctx->pool;
+  box->sum_block = block;
+  return box;
+}
+
+// CSR records in one span: offsets, momenta, flavours, colours, anticolours.
+struct RecordSpan {
+  uint64_t p, pid, col, acol, bytes;
+  RecordSpan(uint64_t n, uint64_t total)
+      : p(align_up((n + 1) * 8, 256)), pid(p + align_up(total * 32, 256)), col(pid + align_up(total, 256)),
+        acol(col + align_up(total * 2, 256)), bytes(acol + align_up(total * 2, 256)) {}
+};
 
 void finish_result(ResultBox* b) {
   vsh_result& r = b->pub;
@@ -222,37 +306,28 @@ void finish_result(ResultBox* b) {
   r.sum_d = b->sum_d.empty() ? nullptr : b->sum_d.data();
   r.sum_i = b->sum_i.empty() ? nullptr : b->sum_i.data();
   r.sum_hash = b->hash.empty() ? nullptr : b->hash.data();
-  if (!b->rec_offsets.empty()) {
+  if (b->sum_block.ptr) {
+    const ResultSpan sp(r.n_events);
+    const char* p = static_cast<const char*>(b->sum_block.ptr);
+    r.sum_i = reinterpret_cast<const int32_t*>(p + sp.i);
+    r.sum_d = reinterpret_cast<const double*>(p + sp.d);
+    r.sum_hash = reinterpret_cast<const uint64_t*>(p + sp.hash);
+  }
+  if (b->rec_block.ptr) {
+    const uint64_t* off = static_cast<const uint64_t*>(b->rec_block.ptr);
+    const RecordSpan sp(r.n_events, off[r.n_events]);
+    const char* p = static_cast<const char*>(b->rec_block.ptr);
+    r.rec_offsets = off;
+    r.rec_p = reinterpret_cast<const double*>(p + sp.p);
+    r.rec_pid = reinterpret_cast<const int8_t*>(p + sp.pid);
+    r.rec_col = reinterpret_cast<const uint16_t*>(p + sp.col);
+    r.rec_acol = reinterpret_cast<const uint16_t*>(p + sp.acol);
+  } else if (!b->rec_offsets.empty()) {
     r.rec_offsets = b->rec_offsets.data();
     r.rec_p = b->rec_p.data();
     r.rec_pid = b->rec_pid.data();
     r.rec_col = b->rec_col.data();
     r.rec_acol = b->rec_acol.data();
-  }
-}
-
-// Fold one chunk's per-event ints/doubles into the result counters.
-// The result's counts and sums over count events, from the summary fields
-// [field][stride] (only status, cycles, emissions, trials, active ends and
-// the weight are read).
-void tally_chunk(ResultBox* b, const int32_t* si, const double* sd, uint64_t stride, uint64_t count) {
-  vsh_result& r = b->pub;
-  for (uint64_t e = 0; e < count; ++e) {
-    const int st = si[kSiStatus * stride + e];
-    r.n_done += st == kDone;
-    r.n_overflow += st == kOverflow;
-    r.n_nonfinite += st == kNonFinite;
-    r.n_conservation += st == kConservation;
-    r.n_cycle_limit += st == kCycleLimitHit;
-    const double w = sd[kSdW * stride + e];
-    r.sum_w += w;
-    r.sum_w2 += w * w;
-    const uint32_t cyc = (uint32_t)si[kSiCycles * stride + e];
-    r.total_cycles += cyc;
-    r.max_cycles = std::max(r.max_cycles, cyc);
-    r.total_trials += (uint32_t)si[kSiTrials * stride + e];
-    r.total_ends += (uint32_t)si[kSiEnds * stride + e];
-    r.total_emissions += (uint32_t)si[kSiEmit * stride + e];
   }
 }
 
@@ -279,50 +354,56 @@ void tally_fields(ResultBox* b, const int32_t* si0, uint64_t stride, const doubl
   }
 }
 
-// Copy a chunk's results back through the pinned staging buffer: the
-// histogram, and either every summary field (requested summaries or records)
-// or only the fields the counts read (the weight, then the integer fields
-// from status to active ends); tally them, add the histogram and, with
-// summaries, place the fields in the result.  *n_host (optional) points at
-// the staged parton counts when all fields were copied.
+// Copy a chunk's results (one device span from dev_hist on, ResultSpan) back,
+// add up the counts and the histogram, and with summaries place the fields in
+// the result: in its own pinned block, the counts made from the span's head
+// while the rest arrives, or through the staging buffer.  *n_host (optional)
+// points at the parton counts.
 vsh_status copy_back_chunk(vsh_ctx* ctx, hipStream_t st, const double* dev_hist, const Summary& dev_sum,
-                           uint64_t stride, uint64_t count, bool all_fields, ResultBox* box, uint64_t first_idx,
+                           uint64_t count, uint32_t flags, ResultBox* box, uint64_t first_idx,
                            const int32_t** n_host) {
-  static_assert(kSiStatus == 1 && kSiEnds == kNSumI - 1, "the counted integer fields are the last ones");
-  const uint64_t hist_b = align_up(kHistDoubles * 8, 256);
-  const uint64_t d_fields = all_fields ? kNSumD : 1, i_fields = all_fields ? kNSumI : kNSumI - kSiStatus;
-  const uint64_t d_b = align_up(d_fields * stride * 8, 256), i_b = align_up(i_fields * stride * 4, 256);
-  const uint64_t h_b = all_fields ? align_up(stride * 8, 256) : 0;
-  vsh_status rc = ctx->stage.reserve(ctx, hist_b + d_b + i_b + h_b);
-  if (rc) return rc;
-  char* base = static_cast<char*>(ctx->stage.ptr);
-  double* hh = reinterpret_cast<double*>(base);
-  double* sd = reinterpret_cast<double*>(base + hist_b);
-  int32_t* si = reinterpret_cast<int32_t*>(base + hist_b + d_b);
-  uint64_t* hs = reinterpret_cast<uint64_t*>(base + hist_b + d_b + i_b);
-  hipError_t err = hipMemcpyAsync(hh, dev_hist, kHistDoubles * 8, hipMemcpyDeviceToHost, st);
-  if (all_fields) {
-    if (err == hipSuccess) err = hipMemcpyAsync(sd, dev_sum.d, kNSumD * stride * 8, hipMemcpyDeviceToHost, st);
-    if (err == hipSuccess) err = hipMemcpyAsync(si, dev_sum.i, kNSumI * stride * 4, hipMemcpyDeviceToHost, st);
-    if (err == hipSuccess) err = hipMemcpyAsync(hs, dev_sum.hash, stride * 8, hipMemcpyDeviceToHost, st);
-  } else {
-    if (err == hipSuccess)
-      err = hipMemcpyAsync(sd, dev_sum.d + kSdW * stride, stride * 8, hipMemcpyDeviceToHost, st);
-    if (err == hipSuccess)
-      err = hipMemcpyAsync(si, dev_sum.i + kSiStatus * stride, i_fields * stride * 4, hipMemcpyDeviceToHost, st);
+  static_assert(kSiStatus == 1 && kSiEnds == kNSumI - 1 && kSdW == 0, "the counts read the span's head");
+  const ResultSpan sp(count);
+  const char* dev = reinterpret_cast<const char*>(dev_hist);
+  if (reinterpret_cast<const char*>(dev_sum.i) != dev + sp.i || reinterpret_cast<const char*>(dev_sum.d) != dev + sp.d ||
+      reinterpret_cast<const char*>(dev_sum.hash) != dev + sp.hash || dev_sum.stride != count) {
+    set_error(ctx, "results are not in one span (internal error)");
+    return VSH_E_INTERNAL;
   }
-  if (err == hipSuccess) err = hipStreamSynchronize(st);
+  const uint64_t bytes = (flags & VSH_SUMMARY) ? sp.bytes : sp.head;
+  char* host = static_cast<char*>(box->sum_block.ptr);
+  if (!host) {
+    vsh_status rc = ctx->stage.reserve(ctx, bytes);
+    if (rc) return rc;
+    host = static_cast<char*>(ctx->stage.ptr);
+  }
+  // small results in one copy
+  const uint64_t first = bytes <= (1u << 18) ? bytes : sp.head;
+  hipError_t err = hipMemcpyAsync(host, dev, first, hipMemcpyDeviceToHost, st);
+  if (err == hipSuccess && first < bytes) {
+    err = hipEventRecord(ctx->head_ev, st);
+    if (err == hipSuccess) err = hipMemcpyAsync(host + first, dev + first, bytes - first, hipMemcpyDeviceToHost, st);
+    if (err == hipSuccess) err = hipEventSynchronize(ctx->head_ev);
+  } else if (err == hipSuccess) {
+    err = hipStreamSynchronize(st);
+  }
   if (err != hipSuccess) return hip_fail(ctx, err, "result copy");
+  const double* hh = reinterpret_cast<const double*>(host);
+  const int32_t* si = reinterpret_cast<const int32_t*>(host + sp.i);
+  const double* sd = reinterpret_cast<const double*>(host + sp.d);
   for (int a = 0; a < kHistDoubles; ++a) box->hist[a] += hh[a];
-  const int32_t* si0 = all_fields ? si + kSiStatus * stride : si;  // field kSiStatus onwards
-  tally_fields(box, si0, stride, all_fields ? sd + kSdW * stride : sd, count);
-  if (all_fields && !box->sum_d.empty()) {
-    const uint64_t N = box->pub.n_events;
-    for (int f = 0; f < kNSumD; ++f) std::memcpy(&box->sum_d[f * N + first_idx], &sd[f * stride], count * 8);
-    for (int f = 0; f < kNSumI; ++f) std::memcpy(&box->sum_i[f * N + first_idx], &si[f * stride], count * 4);
-    std::memcpy(&box->hash[first_idx], hs, count * 8);
+  tally_fields(box, si + kSiStatus * count, count, sd + kSdW * count, count);
+  if (first < bytes) {
+    err = hipStreamSynchronize(st);
+    if (err != hipSuccess) return hip_fail(ctx, err, "result copy");
   }
-  if (n_host) *n_host = all_fields ? si + kSiN * stride : nullptr;
+  if ((flags & VSH_SUMMARY) && !box->sum_block.ptr) {
+    const uint64_t N = box->pub.n_events;
+    for (int f = 0; f < kNSumD; ++f) std::memcpy(&box->sum_d[f * N + first_idx], &sd[f * count], count * 8);
+    for (int f = 0; f < kNSumI; ++f) std::memcpy(&box->sum_i[f * N + first_idx], &si[f * count], count * 4);
+    std::memcpy(&box->hash[first_idx], host + sp.hash, count * 8);
+  }
+  if (n_host) *n_host = si + kSiN * count;
   return VSH_OK;
 }
 
@@ -346,47 +427,57 @@ __global__ void k_gather_records(Records r, const int32_t* __restrict__ n_of, co
   }
 }
 
-// Append the final partons of `count` events held slot-major in r (parton
-// counts n_dev on the device, n_host on the host) to box's CSR records.
+// The final partons of `count` events held slot-major in r (parton counts
+// n_dev on the device, n_host on the host) as CSR records: the whole result's
+// (first_idx 0, all its events) in a pinned block of its own, a chunk's
+// appended to box's vectors.
 vsh_status gather_records(vsh_ctx* ctx, const Records& r, const int32_t* n_dev, const int32_t* n_host,
                           uint64_t count, ResultBox* box) {
   hipStream_t st = ctx->stream;
-  std::vector<uint64_t> off(count + 1, 0);
-  for (uint64_t e = 0; e < count; ++e) off[e + 1] = off[e] + (uint64_t)n_host[e];
-  const uint64_t total = off[count];
-  const uint64_t need = align_up((count + 1) * 8, 256) + align_up(total * 32, 256) + align_up(total, 256) +
-                        2 * align_up(total * 2, 256) + 256;
-  vsh_status rc = ctx->arena2.reserve(ctx, need);
+  uint64_t total = 0;
+  for (uint64_t e = 0; e < count; ++e) total += (uint64_t)n_host[e];
+  const RecordSpan sp(count, total);
+  vsh_status rc = ctx->arena2.reserve(ctx, sp.bytes + 256);
   if (rc) return rc;
+  PinnedBlock block;
+  if (count == box->pub.n_events) block = ctx->pool->acquire(sp.bytes);
+  box->rec_block = block;  // released with the result
+  std::vector<uint64_t> own;
+  if (!block.ptr) own.resize(count + 1);
+  uint64_t* off = block.ptr ? static_cast<uint64_t*>(block.ptr) : own.data();
+  off[0] = 0;
+  for (uint64_t e = 0; e < count; ++e) off[e + 1] = off[e] + (uint64_t)n_host[e];
   char* q = (char*)ctx->arena2.ptr;
   uint64_t* d_off = (uint64_t*)q;
-  q += align_up((count + 1) * 8, 256);
-  double* d_p = (double*)q;
-  q += align_up(total * 32, 256);
-  int8_t* d_pid = (int8_t*)q;
-  q += align_up(total, 256);
-  uint16_t* d_col = (uint16_t*)q;
-  q += align_up(total * 2, 256);
-  uint16_t* d_acol = (uint16_t*)q;
-  hipError_t err = hipMemcpyAsync(d_off, off.data(), (count + 1) * 8, hipMemcpyHostToDevice, st);
+  double* d_p = (double*)(q + sp.p);
+  int8_t* d_pid = (int8_t*)(q + sp.pid);
+  uint16_t* d_col = (uint16_t*)(q + sp.col);
+  uint16_t* d_acol = (uint16_t*)(q + sp.acol);
+  hipError_t err = hipMemcpyAsync(d_off, off, (count + 1) * 8, hipMemcpyHostToDevice, st);
   if (err != hipSuccess) return hip_fail(ctx, err, "offset copy");
   hipLaunchKernelGGL(k_gather_records, dim3((uint32_t)((count + 255) / 256)), dim3(256), 0, st, r, n_dev,
                      (const uint64_t*)d_off, (uint32_t)count, d_p, d_pid, d_col, d_acol);
   err = hipGetLastError();
   if (err != hipSuccess) return hip_fail(ctx, err, "k_gather_records");
-  const uint64_t base = box->rec_offsets.empty() ? 0 : box->rec_offsets.back();
-  if (box->rec_offsets.empty()) box->rec_offsets.push_back(0);
-  for (uint64_t e = 0; e < count; ++e) box->rec_offsets.push_back(base + off[e + 1]);
-  box->rec_p.resize((base + total) * 4);
-  box->rec_pid.resize(base + total);
-  box->rec_col.resize(base + total);
-  box->rec_acol.resize(base + total);
-  if (total) {
-    err = hipMemcpyAsync(&box->rec_p[base * 4], d_p, total * 32, hipMemcpyDeviceToHost, st);
-    if (err == hipSuccess) err = hipMemcpyAsync(&box->rec_pid[base], d_pid, total, hipMemcpyDeviceToHost, st);
-    if (err == hipSuccess) err = hipMemcpyAsync(&box->rec_col[base], d_col, total * 2, hipMemcpyDeviceToHost, st);
-    if (err == hipSuccess) err = hipMemcpyAsync(&box->rec_acol[base], d_acol, total * 2, hipMemcpyDeviceToHost, st);
+  if (block.ptr) {
+    if (total)
+      err = hipMemcpyAsync(static_cast<char*>(block.ptr) + sp.p, q + sp.p, sp.bytes - sp.p, hipMemcpyDeviceToHost, st);
     if (err != hipSuccess) return hip_fail(ctx, err, "record copy");
+  } else {
+    const uint64_t base = box->rec_offsets.empty() ? 0 : box->rec_offsets.back();
+    if (box->rec_offsets.empty()) box->rec_offsets.push_back(0);
+    for (uint64_t e = 0; e < count; ++e) box->rec_offsets.push_back(base + off[e + 1]);
+    box->rec_p.resize((base + total) * 4);
+    box->rec_pid.resize(base + total);
+    box->rec_col.resize(base + total);
+    box->rec_acol.resize(base + total);
+    if (total) {
+      err = hipMemcpyAsync(&box->rec_p[base * 4], d_p, total * 32, hipMemcpyDeviceToHost, st);
+      if (err == hipSuccess) err = hipMemcpyAsync(&box->rec_pid[base], d_pid, total, hipMemcpyDeviceToHost, st);
+      if (err == hipSuccess) err = hipMemcpyAsync(&box->rec_col[base], d_col, total * 2, hipMemcpyDeviceToHost, st);
+      if (err == hipSuccess) err = hipMemcpyAsync(&box->rec_acol[base], d_acol, total * 2, hipMemcpyDeviceToHost, st);
+      if (err != hipSuccess) return hip_fail(ctx, err, "record copy");
+    }
   }
   err = hipStreamSynchronize(st);
   if (err != hipSuccess) return hip_fail(ctx, err, "hipStreamSynchronize");
@@ -419,7 +510,7 @@ static vsh_status load_records(vsh_ctx* ctx, const PlainLayout& L, const uint64_
     bytes += align_up(q.bytes, 256);
   }
   char* dev = reinterpret_cast<char*>(L.cache);
-  if (bytes > (uint64_t)(reinterpret_cast<char*>(L.sum.d) - dev)) {
+  if (bytes > (uint64_t)(reinterpret_cast<char*>(L.hist) - dev)) {
     set_error(ctx, "caller-supplied starts of %llu bytes exceed the workspace", (unsigned long long)bytes);
     return VSH_E_INTERNAL;
   }
@@ -434,7 +525,7 @@ static vsh_status load_records(vsh_ctx* ctx, const PlainLayout& L, const uint64_
   const CsrStarts in{(const uint64_t*)(dev + parts[0].at), (const double*)(dev + parts[1].at),
                      (const int8_t*)(dev + parts[2].at), (const uint16_t*)(dev + parts[3].at),
                      (const uint16_t*)(dev + parts[4].at)};
-  launch_load_records(L.rec, L.sum, in, (uint32_t)count, L.ecm, (unsigned long long*)dev, st);
+  launch_load_records(L.rec, L.sum, in, (uint32_t)count, L.ecm, (unsigned long long*)dev, L.hist, st);
   err = hipGetLastError();
   if (err == hipSuccess) err = hipMemcpyAsync(bad, dev, 8, hipMemcpyDeviceToHost, st);
   if (err == hipSuccess) err = hipStreamSynchronize(st);
@@ -448,18 +539,16 @@ static vsh_status run_plain_chunk(vsh_ctx* ctx, const vsh_request* req, uint64_t
                                   const uint16_t* cacol, ResultBox* box, ChunkTimes& tm) {
   hipStream_t st = ctx->stream;
   const uint32_t cap = req->max_partons;
-  const uint64_t stride = align_up(count, 64);
   const bool massive = request_massive(*req) != 0;
-  vsh_status rc = ctx->arena.reserve(ctx, plain_layout_bytes(stride, cap, massive));
+  vsh_status rc = ctx->arena.reserve(ctx, plain_layout_bytes(align_up(count, 64), cap, massive));
   if (rc) return rc;
-  PlainLayout L = carve_plain(ctx->arena.ptr, stride, cap, massive);
+  PlainLayout L = carve_plain(ctx->arena.ptr, count, cap, massive);
   hipError_t err;
 #define HIPCHK(x)                                 \
   do {                                            \
     err = (x);                                    \
     if (err != hipSuccess) return hip_fail(ctx, err, #x); \
   } while (0)
-  HIPCHK(hipMemsetAsync(L.hist, 0, kHistDoubles * 8, st));
   EventInputs in{};
   in.seed = req->seed;
   in.first = req->first_event + first_idx;
@@ -486,7 +575,7 @@ static vsh_status run_plain_chunk(vsh_ctx* ctx, const vsh_request* req, uint64_t
     rc = load_records(ctx, L, caller_offsets + first_idx, cp, cpid, ccol, cacol, count, st);
     if (rc) return rc;
   } else {
-    launch_me(L.rec, L.sum, in, (uint32_t)count, st);
+    launch_me(L.rec, L.sum, in, (uint32_t)count, st, L.hist);
   }
   HIPCHK(hipGetLastError());
   HIPCHK(hipEventRecord(ctx->ev[1], st));
@@ -497,11 +586,8 @@ static vsh_status run_plain_chunk(vsh_ctx* ctx, const vsh_request* req, uint64_t
   launch_obs(L.rec, L.sum, in, L.sc, (uint32_t)count, L.hist, st);
   HIPCHK(hipGetLastError());
   HIPCHK(hipEventRecord(ctx->ev[3], st));
-  // copy back: the histogram and the summary fields the counts need (all of
-  // them for summaries or records)
-  const bool all_fields = !box->sum_d.empty() || (req->flags & VSH_RECORDS);
   const int32_t* n_host = nullptr;
-  rc = copy_back_chunk(ctx, st, L.hist, L.sum, stride, count, all_fields, box, first_idx, &n_host);
+  rc = copy_back_chunk(ctx, st, L.hist, L.sum, count, req->flags, box, first_idx, &n_host);
   if (rc) return rc;
   float ms;
   HIPCHK(hipEventElapsedTime(&ms, ctx->ev[0], ctx->ev[1]));
@@ -511,7 +597,7 @@ static vsh_status run_plain_chunk(vsh_ctx* ctx, const vsh_request* req, uint64_t
   HIPCHK(hipEventElapsedTime(&ms, ctx->ev[2], ctx->ev[3]));
   tm.obs += ms;
   if (req->flags & VSH_RECORDS) {
-    rc = gather_records(ctx, L.rec, L.sum.i + kSiN * stride, n_host, count, box);
+    rc = gather_records(ctx, L.rec, L.sum.i + kSiN * count, n_host, count, box);
     if (rc) return rc;
   }
 #undef HIPCHK
@@ -539,11 +625,8 @@ vsh_status generate_plain(vsh_ctx* ctx, const vsh_request* req, const uint64_t* 
               (unsigned long long)ctx->budget, req->max_partons);
     return VSH_E_NOMEM;
   }
-  ResultBox* box = new_result(req->n_events, req->flags & VSH_SUMMARY);
-  if (!box) {
-    set_error(ctx, "host allocation failed");
-    return VSH_E_NOMEM;
-  }
+  ResultBox* box = new_call_result(ctx, req, chunk >= req->n_events);
+  if (!box) return VSH_E_NOMEM;
   ChunkTimes tm;
   for (uint64_t a = 0; a < req->n_events; a += chunk) {
     const uint64_t count = std::min(chunk, req->n_events - a);
@@ -578,16 +661,14 @@ hipEvent_t* timing_slot(vsh_ctx* ctx) {
 // The plain-form launch sequence of vsh_generate_into on stream st with the
 // workspace at `ws` (at least vsh_workspace_size bytes; nothing in it needs
 // to start at zero): matrix element, shower, observables and histogram
-// accumulated into dev_hist, then the summaries copied out in the caller's
-// [field][n_events] layout; when n is a multiple of 64 that layout is the
-// kernels' own, so they work in the caller's summary buffers directly and
-// nothing is copied.  `timed`: record the stage events of vsh_timing_start.
-// Launches and device-to-device copies only.
+// accumulated into dev_hist, the kernels working in the caller's [field][n]
+// summary buffers directly (in the workspace's where the caller gave none).
+// `timed`: record the stage events of vsh_timing_start.
+// Launches only.
 vsh_status plain_into(vsh_ctx* ctx, const vsh_request* req, hipStream_t st, void* ws, double* dev_hist,
                       double* dev_sum_d, int32_t* dev_sum_i, uint64_t* dev_hash, bool timed) {
   const uint64_t n = req->n_events;
-  const uint64_t stride = align_up(n, 64);
-  PlainLayout L = carve_plain(ws, stride, req->max_partons, request_massive(*req) != 0);
+  PlainLayout L = carve_plain(ws, n, req->max_partons, request_massive(*req) != 0);
   EventInputs in{};
   in.seed = req->seed;
   in.first = req->first_event;
@@ -601,10 +682,9 @@ vsh_status plain_into(vsh_ctx* ctx, const vsh_request* req, hipStream_t st, void
   in.ecm = req->ecm_per_event;
   in.tcut = req->tcut_per_event;
   Summary sum = L.sum;
-  const bool direct = stride == n;  // the caller's [field][n] arrays have the kernels' stride
-  if (direct && dev_sum_d) sum.d = dev_sum_d;
-  if (direct && dev_sum_i) sum.i = dev_sum_i;
-  if (direct && dev_hash) sum.hash = dev_hash;
+  if (dev_sum_d) sum.d = dev_sum_d;
+  if (dev_sum_i) sum.i = dev_sum_i;
+  if (dev_hash) sum.hash = dev_hash;
   hipEvent_t* tev = timed ? timing_slot(ctx) : nullptr;
   if (tev) (void)hipEventRecord(tev[0], st);
   launch_me(L.rec, sum, in, (uint32_t)n, st);
@@ -616,23 +696,8 @@ vsh_status plain_into(vsh_ctx* ctx, const vsh_request* req, hipStream_t st, void
   if (tev) (void)hipEventRecord(tev[3], st);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return hip_fail(ctx, err, "kernel launch");
-  // summaries out, in the caller's [field][n_events] layout
-  if (direct) return VSH_OK;
-  if (dev_sum_d) {
-    err = hipMemcpy2DAsync(dev_sum_d, n * 8, sum.d, stride * 8, n * 8, kNSumD, hipMemcpyDeviceToDevice, st);
-    if (err != hipSuccess) return hip_fail(ctx, err, "summary copy");
-  }
-  if (dev_sum_i) {
-    err = hipMemcpy2DAsync(dev_sum_i, n * 4, sum.i, stride * 4, n * 4, kNSumI, hipMemcpyDeviceToDevice, st);
-    if (err != hipSuccess) return hip_fail(ctx, err, "summary copy");
-  }
-  if (dev_hash) {
-    err = hipMemcpyAsync(dev_hash, sum.hash, n * 8, hipMemcpyDeviceToDevice, st);
-    if (err != hipSuccess) return hip_fail(ctx, err, "summary copy");
-  }
   return VSH_OK;
 }
-
 
 // The message for the first fault of caller-supplied starts.
 static vsh_status explain_starts(vsh_ctx* ctx, const vsh_request* req, const uint64_t* offsets, const double* p,
@@ -713,6 +778,13 @@ vsh_status vsh_create(const vsh_ctx_opts* opts, vsh_ctx** out) {
   }
   ctx->device = dev;
   ctx->n_cu = prop.multiProcessorCount;
+  try {
+    ctx->pool = std::make_shared<PinnedPool>();
+  } catch (const std::bad_alloc&) {
+    delete ctx;
+    set_error(nullptr, "host allocation failed");
+    return VSH_E_NOMEM;
+  }
   size_t free_b = 0, total_b = 0;
   err = hipMemGetInfo(&free_b, &total_b);
   if (err != hipSuccess) {
@@ -740,6 +812,11 @@ vsh_status vsh_create(const vsh_ctx_opts* opts, vsh_ctx** out) {
       return hip_fail(nullptr, err, "hipEventCreate");
     }
   }
+  err = hipEventCreateWithFlags(&ctx->head_ev, hipEventDisableTiming);
+  if (err != hipSuccess) {
+    delete ctx;
+    return hip_fail(nullptr, err, "hipEventCreate");
+  }
   // the static workspace's address on this device (vsh_generate_into_static
   // looks it up itself if this fails; nothing else depends on it)
   (void)static_scratch_init(ctx);
@@ -756,6 +833,8 @@ void vsh_destroy(vsh_ctx* ctx) {
   ctx->arena.release();
   ctx->arena2.release();
   ctx->stage.release();
+  ctx->pool->close();  // results still held free their blocks themselves
+  if (ctx->head_ev) (void)hipEventDestroy(ctx->head_ev);
   for (auto& e : ctx->timing_ev) (void)hipEventDestroy(e);
   destroy_graph(ctx->graph);
   for (auto& e : ctx->idle_ev)

@@ -44,13 +44,43 @@ struct HostStage {
   void release();
 };
 
+// Pinned host memory that results live in, so that they come from the device
+// by DMA and nothing is cleared, faulted in page by page or copied again on
+// the host.  A context's blocks are kept for its later results, kMost bytes
+// of them at most, in use and idle together (acquire returns none beyond);
+// idle ones are freed with the context, one in use when its result is.
+struct PinnedBlock {
+  void* ptr = nullptr;
+  uint64_t size = 0;
+};
+struct PinnedPool {
+  static constexpr uint64_t kMost = 1ull << 30;
+  std::mutex mu;
+  std::vector<PinnedBlock> idle;
+  uint64_t held = 0;  // bytes of every block, in use and idle
+  bool closed = false;
+  PinnedBlock acquire(uint64_t bytes);
+  void release(PinnedBlock b);
+  void close();
+};
+
 struct PlainLayout {
   Records rec;
   uint64_t* cache;  // end cache of the flattened kernel, [event][cap] entries of kCacheWords words
   Scratch sc;
-  Summary sum;
+  Summary sum;      // [field][n]; with hist one span in the order of ResultSpan
   double *ecm, *tcut, *hist;
   char* end;
+};
+
+// A request's results in one span, on the device and in host memory alike:
+// histogram, integer fields, doubles (weight first), hash.  The first `head`
+// bytes hold what the counts read.
+struct ResultSpan {
+  uint64_t i, d, hash, head, bytes;  // offsets, from the histogram at 0
+  explicit ResultSpan(uint64_t n)
+      : i(align_up(kHistDoubles * 8, 256)), d(i + align_up(kNSumI * n * 4, 256)),
+        hash(d + align_up(kNSumD * n * 8, 256)), head(d + n * 8), bytes(hash + n * 8) {}
 };
 
 // launch parameters picked by the autotuner (defaults until it has run)
@@ -79,6 +109,8 @@ struct vsh_ctx {
   vsh::BatchGraph graph;
   vsh::Arena arena, arena2;
   vsh::HostStage stage;
+  std::shared_ptr<vsh::PinnedPool> pool;
+  hipEvent_t head_ev = nullptr;  // after the part of a result that the counts read
   vsh::Tuned tuned;
   float tuned_ms = 0.0f;  // shower-kernel time of the autotuner's choice on its sample
   std::string tuner_cache_path;  // file of earlier tunings (empty: none)
@@ -102,20 +134,26 @@ struct ResultBox {
   std::vector<double> rec_p;
   std::vector<int8_t> rec_pid;
   std::vector<uint16_t> rec_col, rec_acol;
+  // a request processed in one piece keeps its summaries and records in
+  // pinned blocks instead of the vectors above
+  std::shared_ptr<PinnedPool> pool;
+  PinnedBlock sum_block, rec_block;
+  ~ResultBox();
 };
 
 void set_error(vsh_ctx* ctx, const char* fmt, ...);
 vsh_status hip_fail(vsh_ctx* ctx, hipError_t err, const char* what);
 vsh_status validate_request(vsh_ctx* ctx, const vsh_request* req, bool need_energy);
-ResultBox* new_result(uint64_t n_events, bool summary);
+ResultBox* new_result(uint64_t n_events, bool summary);  // null when out of memory
 void finish_result(ResultBox* b);
-void tally_chunk(ResultBox* b, const int32_t* si, const double* sd, uint64_t stride, uint64_t count);
 void tally_fields(ResultBox* b, const int32_t* si0, uint64_t stride, const double* w, uint64_t count);
+// A generating call's result; `whole`: the request is processed in one piece.
+ResultBox* new_call_result(vsh_ctx* ctx, const vsh_request* req, bool whole);
 vsh_status copy_back_chunk(vsh_ctx* ctx, hipStream_t st, const double* dev_hist, const Summary& dev_sum,
-                           uint64_t stride, uint64_t count, bool all_fields, ResultBox* box, uint64_t first_idx,
+                           uint64_t count, uint32_t flags, ResultBox* box, uint64_t first_idx,
                            const int32_t** n_host);
 uint64_t plain_layout_bytes(uint64_t stride, uint32_t cap, bool massive);
-PlainLayout carve_plain(void* base, uint64_t stride, uint32_t cap, bool massive);
+PlainLayout carve_plain(void* base, uint64_t n, uint32_t cap, bool massive);
 
 vsh_status gather_records(vsh_ctx* ctx, const Records& r, const int32_t* n_dev, const int32_t* n_host,
                           uint64_t count, ResultBox* box);

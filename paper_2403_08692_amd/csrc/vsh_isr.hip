@@ -414,11 +414,8 @@ extern "C" vsh_status vsh_generate_isr(vsh_ctx* ctx, const vsh_request* req, dou
     set_error(ctx, "memory budget cannot hold one event of %u partons", cap);
     return VSH_E_NOMEM;
   }
-  ResultBox* box = new_result(req->n_events, req->flags & VSH_SUMMARY);
-  if (!box) {
-    set_error(ctx, "host allocation failed");
-    return VSH_E_NOMEM;
-  }
+  ResultBox* box = new_call_result(ctx, req, chunk >= req->n_events);
+  if (!box) return VSH_E_NOMEM;
   static const double L[kNObs] = {-1.0, -5.0, 0.0, -1.0, 0.0, 0.0, 0.0, 0.0};
   static const double H[kNObs] = {3.0, 5.0, 50.0, 3.0, 1.0, 1.0, 1.0, 1.0};
   for (int h = 0; h < kNObs; ++h) {
@@ -451,11 +448,11 @@ extern "C" vsh_status vsh_generate_isr(vsh_ctx* ctx, const vsh_request* req, dou
     r.stride = stride;
     r.cap = cap;
     Summary sm{};
-    sm.d = (double*)c.take(kNSumD * stride * 8);
-    sm.i = (int32_t*)c.take(kNSumI * stride * 4);
-    sm.hash = (uint64_t*)c.take(stride * 8);
-    sm.stride = stride;
     double* hist = (double*)c.take(kHistDoubles * 8);
+    sm.i = (int32_t*)c.take(kNSumI * count * 4);
+    sm.d = (double*)c.take(kNSumD * count * 8);
+    sm.hash = (uint64_t*)c.take(count * 8);
+    sm.stride = count;
     launch_zero(hist, kHistDoubles, st);
     const IsrInputs in{req->seed, req->first_event + a, sqrt_s_hadron, req->ecm, req->t_cut};
     (void)hipEventRecord(ctx->ev[1], st);
@@ -466,9 +463,8 @@ extern "C" vsh_status vsh_generate_isr(vsh_ctx* ctx, const vsh_request* req, dou
       delete box;
       return hip_fail(ctx, err, "k_isr launch");
     }
-    const bool all_fields = !box->sum_d.empty() || (req->flags & VSH_RECORDS);
     const int32_t* n_host = nullptr;
-    rc = copy_back_chunk(ctx, st, hist, sm, stride, count, all_fields, box, a, &n_host);
+    rc = copy_back_chunk(ctx, st, hist, sm, count, req->flags, box, a, &n_host);
     if (rc) {
       delete box;
       return rc;
@@ -476,7 +472,7 @@ extern "C" vsh_status vsh_generate_isr(vsh_ctx* ctx, const vsh_request* req, dou
     float ms = 0.0f;
     if (hipEventElapsedTime(&ms, ctx->ev[1], ctx->ev[2]) == hipSuccess) t_sh += ms;
     if (req->flags & VSH_RECORDS) {
-      rc = gather_records(ctx, r, sm.i + kSiN * stride, n_host, count, box);
+      rc = gather_records(ctx, r, sm.i + kSiN * count, n_host, count, box);
       if (rc) {
         delete box;
         return rc;

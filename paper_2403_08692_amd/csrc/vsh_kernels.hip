@@ -15,14 +15,12 @@
 
 namespace vsh {
 
-// zero_hist (optional): a histogram set to clear on the way (the first
-// min(n, 256) threads clear it), saving its own launch.
+// zero_hist (optional): a histogram set to clear on the way (the first block
+// clears it), saving its own launch.
 __global__ void __launch_bounds__(256) k_me(Records r, Summary s, EventInputs in, uint32_t n, double* zero_hist) {
   const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (zero_hist && e < 256u) {
-    const uint32_t step = n < 256u ? n : 256u;
-    for (uint32_t a = e; a < (uint32_t)kHistDoubles; a += step) zero_hist[a] = 0.0;
-  }
+  if (zero_hist && blockIdx.x == 0)
+    for (uint32_t a = threadIdx.x; a < (uint32_t)kHistDoubles; a += blockDim.x) zero_hist[a] = 0.0;
   if (e >= n) return;
   const MEOut m = me_event(r, e, make_keyed(in.seed, in.first + e), in.ecm_of(e), in.qm, in.massive != 0);
   s.d[kSdW * s.stride + e] = m.w;
@@ -41,7 +39,8 @@ __global__ void __launch_bounds__(256) k_me(Records r, Summary s, EventInputs in
 // event that fails a check (its record is not used then); offsets have been
 // checked by the host.
 __global__ void __launch_bounds__(256) k_load_records(Records r, Summary s, CsrStarts in, uint32_t n, double* ecm,
-                                                      unsigned long long* bad) {
+                                                      unsigned long long* bad, double* zero_hist) {
+  for (uint32_t a = blockIdx.x * 256 + threadIdx.x; a < (uint32_t)kHistDoubles; a += gridDim.x * 256) zero_hist[a] = 0.0;
   const uint32_t e = (blockIdx.x * 256 + threadIdx.x) / kLoadLanes, lane = threadIdx.x % kLoadLanes;
   if (e >= n) return;
   const uint64_t o = in.off[e] - in.off[0];
@@ -933,10 +932,10 @@ void launch_me(const Records& r, const Summary& s, const EventInputs& in, uint32
 }
 
 void launch_load_records(const Records& r, const Summary& s, const CsrStarts& in, uint32_t n, double* ecm,
-                         unsigned long long* bad, hipStream_t st) {
+                         unsigned long long* bad, double* zero_hist, hipStream_t st) {
   if (!n) return;
   hipLaunchKernelGGL(k_load_records, dim3(blocks_for((uint64_t)n * kLoadLanes, 256)), dim3(256), 0, st, r, s, in, n,
-                     ecm, bad);
+                     ecm, bad, zero_hist);
 }
 
 void launch_shower_plain(const Records& r, const Summary& s, const EventInputs& in, uint32_t n,

@@ -172,5 +172,5 @@ void launch_shower_plain(const Records& r, const Summary& s, const EventInputs& 
 void launch_obs(const Records& r, const Summary& s, const EventInputs& in, const Scratch& sc,
                 uint32_t n, double* hist, hipStream_t st);
 void launch_load_records(const Records& r, const Summary& s, const CsrStarts& in, uint32_t n, double* ecm,
-                         unsigned long long* bad, hipStream_t st);
+                         unsigned long long* bad, double* zero_hist, hipStream_t st);
 }  // namespace vsh

@@ -1468,11 +1468,8 @@ vsh_status generate_persistent(vsh_ctx* ctx, const vsh_request* req, vsh_result*
   const uint64_t per_event = request_out_bytes(1, cap, true) + 64 + (uint64_t)cap * 32;
   uint64_t chunk = std::min<uint64_t>(req->n_events, (budget - fixed) / per_event);
   chunk = std::min<uint64_t>(chunk, 1ull << 27);
-  ResultBox* box = new_result(req->n_events, req->flags & VSH_SUMMARY);
-  if (!box) {
-    set_error(ctx, "host allocation failed");
-    return VSH_E_NOMEM;
-  }
+  ResultBox* box = new_call_result(ctx, req, chunk >= req->n_events);
+  if (!box) return VSH_E_NOMEM;
   hipStream_t st = ctx->stream;
   float t_me = 0, t_sh = 0, t_obs = 0;
   for (uint64_t a = 0; a < req->n_events; a += chunk) {
@@ -1496,7 +1493,6 @@ vsh_status generate_persistent(vsh_ctx* ctx, const vsh_request* req, vsh_result*
       if (err != hipSuccess) { delete box; return hip_fail(ctx, err, "input copy"); }
       tcut_dev = L.buf.tcut;
     }
-    launch_zero(L.buf.hist, kHistDoubles, st);
     (void)hipEventRecord(ctx->ev[0], st);
     PersistArgs A;
     ReqDev d;
@@ -1515,7 +1511,7 @@ vsh_status generate_persistent(vsh_ctx* ctx, const vsh_request* req, vsh_result*
     in.qm = request_masses(*req);
     in.massive = request_massive(*req);
     in.fixed_hist = (req->flags & VSH_HIST_FIXEDPOINT) ? 1u : 0u;
-    launch_me(L.buf.out, L.buf.sum, in, (uint32_t)n, st);
+    launch_me(L.buf.out, L.buf.sum, in, (uint32_t)n, st, L.buf.hist);
     A.slots = L.buf.out;  // in place
     A.reqs = L.reqs;
     A.segs = L.segs;
@@ -1533,9 +1529,8 @@ vsh_status generate_persistent(vsh_ctx* ctx, const vsh_request* req, vsh_result*
     (void)hipEventRecord(ctx->ev[3], st);
     err = hipGetLastError();
     if (err != hipSuccess) { delete box; return hip_fail(ctx, err, "kernel launch"); }
-    const bool all_fields = !box->sum_d.empty() || (req->flags & VSH_RECORDS);
     const int32_t* n_host = nullptr;
-    rc = copy_back_chunk(ctx, st, L.buf.hist, L.buf.sum, n, n, all_fields, box, a, &n_host);
+    rc = copy_back_chunk(ctx, st, L.buf.hist, L.buf.sum, n, req->flags, box, a, &n_host);
     if (rc) {
       delete box;
       return rc;
