@@ -798,13 +798,6 @@ vsh_status vsh_create(const vsh_ctx_opts* opts, vsh_ctx** out) {
     delete ctx;
     return hip_fail(nullptr, err, "hipStreamCreate");
   }
-  for (auto& e : ctx->idle_ev) {
-    err = hipEventCreate(&e);
-    if (err != hipSuccess) {
-      delete ctx;
-      return hip_fail(nullptr, err, "hipEventCreate");
-    }
-  }
   for (auto& e : ctx->ev) {
     err = hipEventCreate(&e);
     if (err != hipSuccess) {
@@ -836,9 +829,6 @@ void vsh_destroy(vsh_ctx* ctx) {
   ctx->pool->close();  // results still held free their blocks themselves
   if (ctx->head_ev) (void)hipEventDestroy(ctx->head_ev);
   for (auto& e : ctx->timing_ev) (void)hipEventDestroy(e);
-  destroy_graph(ctx->graph);
-  for (auto& e : ctx->idle_ev)
-    if (e) (void)hipEventDestroy(e);
   for (auto& e : ctx->ev)
     if (e) (void)hipEventDestroy(e);
   if (ctx->stream) (void)hipStreamDestroy(ctx->stream);

@@ -105,8 +105,6 @@ struct vsh_ctx {
   uint64_t budget = 0;
   hipStream_t stream = nullptr;
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
-  hipEvent_t idle_ev[4] = {nullptr, nullptr, nullptr, nullptr};  // graph event nodes when not timing
-  vsh::BatchGraph graph;
   vsh::Arena arena, arena2;
   vsh::HostStage stage;
   std::shared_ptr<vsh::PinnedPool> pool;
@@ -166,7 +164,7 @@ uint32_t persistent_lanes(const vsh_ctx* ctx);
 uint64_t batch_bytes(uint64_t n, uint32_t cap, bool massive);
 BatchLayout carve_batch(void* base, uint64_t n, uint32_t cap, bool massive);
 vsh_status run_batch(vsh_ctx* ctx, const vsh_request* req, uint64_t first_idx, uint64_t n, hipStream_t st,
-                     void* base, const double* ecm_dev, const double* tcut_dev, double* hist, bool use_graph,
+                     void* base, const double* ecm_dev, const double* tcut_dev, double* hist, const Summary* out,
                      BatchLayout* out_layout);
 vsh_status generate_persistent(vsh_ctx* ctx, const vsh_request* req, vsh_result** out);
 uint64_t persistent_workspace_bytes(const vsh_request* req);

@@ -119,11 +119,6 @@ __global__ void __launch_bounds__(256, kWaves) k_shower_plain(Records r, Summary
 // later pass), computes the observables and fills an LDS histogram that is
 // added to the global one once per block.
 // ---------------------------------------------------------------------------
-__global__ void k_zero_u32(uint32_t* p, uint32_t n) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0u;
-}
-
 // Zero the counting sort's counters, the histogram copies and, for fixed-point histograms, the
 // integer cells and the largest-weight word (a kernel, not a memset, so the
 // sequence can be captured in a graph).
@@ -138,7 +133,7 @@ __global__ void k_obs_reset(uint32_t* cnt, uint32_t nb, double* hcopy, unsigned 
   if (wmax && i == 0) *wmax = 0ull;
 }
 
-uint32_t obs_reset_blocks(uint32_t nb) { return (std::max<uint32_t>(nb, kHistCopies * kHistDoubles) + 255) / 256; }
+static uint32_t obs_reset_blocks(uint32_t nb) { return (std::max<uint32_t>(nb, kHistCopies * kHistDoubles) + 255) / 256; }
 
 // The largest |w| of the launch's events (the bits of non-negative doubles
 // order like the integers), one atomic per wave.
@@ -869,16 +864,25 @@ __global__ void __launch_bounds__(256, 4) k_obs_few(Records r, Summary sm, Event
 
 static inline uint32_t blocks_for(uint64_t n, uint32_t b) { return (uint32_t)((n + b - 1) / b); }
 
+// one launch of the group observables kernel: function, parton-count range
+// [lo, hi), LDS parton slots per group, dynamic LDS bytes
+struct ObsGroupLaunch {
+  const void* fn;
+  uint32_t lo, hi, slots, lds;
+};
+// the one-wave-per-event launch of small requests
+struct ObsFewLaunch {
+  uint32_t blocks, threads, slots, lds, copies;
+};
+
+static size_t obs_group_lds(uint32_t g, uint32_t slots) {
+  return (size_t)(64 / g) * slots * (7 * 8 + 2) + 64;
+}
+
 // The group launches for records of capacity cap: 16 lanes from
 // kObsWaveThreshold to 31 partons, 64 lanes from 32 (smaller events go to
 // k_obs).
-const void* obs_few_kernel(bool massive) {
-  return massive ? (const void*)k_obs_few<true> : (const void*)k_obs_few<false>;
-}
-
-const void* obs_kernel(bool massive) { return massive ? (const void*)k_obs<true> : (const void*)k_obs<false>; }
-
-uint32_t obs_group_launches(uint32_t cap, bool massive, ObsGroupLaunch out[3]) {
+static uint32_t obs_group_launches(uint32_t cap, bool massive, ObsGroupLaunch out[3]) {
   uint32_t k = 0;
   if (cap > kObsWaveMaxCap || kObsWaveThreshold > cap) return 0;
   const uint32_t t = kObsWaveThreshold;
@@ -903,7 +907,7 @@ uint32_t obs_group_launches(uint32_t cap, bool massive, ObsGroupLaunch out[3]) {
 // 10000 events 598 and 340, 100000 644 and 1831.  FP64 sums go straight into
 // the caller's histogram: copies would add two launches, and the additions of
 // up to 2048 blocks do not queue up.
-bool obs_few_launch(uint64_t n, uint32_t cap, bool fixed, ObsFewLaunch* out) {
+static bool obs_few_launch(uint64_t n, uint32_t cap, bool fixed, ObsFewLaunch* out) {
   if (cap > kObsWaveMaxCap || n > (cap > 128 ? kObsFewBig : kObsFew)) return false;
   const uint32_t waves = cap <= 128 ? 4 : cap <= 256 ? 2 : 1;  // at most 30 KB of LDS
   out->threads = 64 * waves;
@@ -914,16 +918,12 @@ bool obs_few_launch(uint64_t n, uint32_t cap, bool fixed, ObsFewLaunch* out) {
   return true;
 }
 
-uint32_t obs_wmax_blocks(uint64_t n) { return (uint32_t)std::min<uint64_t>(blocks_for(n, 256), 256); }
-
-size_t obs_group_lds(uint32_t g, uint32_t slots) {
-  return (size_t)(64 / g) * slots * (7 * 8 + 2) + 64;
-}
+static uint32_t obs_wmax_blocks(uint64_t n) { return (uint32_t)std::min<uint64_t>(blocks_for(n, 256), 256); }
 
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-uint32_t obs_sort_blocks(uint64_t n) { return blocks_for(n, 256u * kObsSortPer); }
+static uint32_t obs_sort_blocks(uint64_t n) { return blocks_for(n, 256u * kObsSortPer); }
 
 void launch_me(const Records& r, const Summary& s, const EventInputs& in, uint32_t n,
                hipStream_t st, double* zero_hist) {

@@ -119,8 +119,6 @@ constexpr uint32_t kObsWaveMaxCap = 512;
 constexpr uint32_t kObsSortPer = 16;  // events per thread of the counting sort by parton count
 constexpr uint32_t kHistCopies = 16;  // copies of the histogram set that the blocks' atomics spread over
 constexpr uint32_t kHistBlocks = (kHistDoubles + 255) / 256;  // blocks of k_hist_finalize
-uint32_t obs_sort_blocks(uint64_t n);
-uint32_t obs_wmax_blocks(uint64_t n);
 constexpr uint32_t kObsGroup64 = 32;     // events from this many partons: 64 lanes each
 constexpr uint32_t kObsFew = 32768, kObsFewBig = 16384;  // most events of k_obs_few (obs_few_launch)
 constexpr uint32_t kObsFewBlocks = 2048;
@@ -139,32 +137,6 @@ namespace vsh {
 uint64_t obs_threads(uint64_t n, uint32_t cap);
 uint64_t obs_scratch_bytes(uint64_t n, uint32_t cap);
 Scratch carve_obs_scratch(char*& p, uint64_t n, uint32_t cap);
-// k_obs for requests without (false) or with (true) quark masses
-const void* obs_kernel(bool massive);
-__global__ void k_obs_count(Summary sm, uint32_t n, uint32_t cap, uint32_t* cnt, unsigned long long* wmax);
-__global__ void k_obs_reset(uint32_t* cnt, uint32_t nb, double* hcopy, unsigned long long* ihist,
-                            unsigned long long* wmax);
-__global__ void k_obs_wmax(Summary sm, uint32_t n, unsigned long long* wmax);
-__global__ void k_hist_finalize(Scratch sc, double* hist, uint32_t fixed);
-uint32_t obs_reset_blocks(uint32_t nb);
-__global__ void k_obs_scan(uint32_t* cnt, uint32_t nb);
-__global__ void k_obs_scatter(Summary sm, uint32_t n, uint32_t cap, uint32_t* cnt, uint32_t* perm);
-__global__ void k_zero_u32(uint32_t* p, uint32_t n);
-__global__ void k_me(Records r, Summary s, EventInputs in, uint32_t n, double* zero_hist);
-// one launch of the group observables kernel: function, parton-count range
-// [lo, hi), LDS parton slots per group, dynamic LDS bytes
-struct ObsGroupLaunch {
-  const void* fn;
-  uint32_t lo, hi, slots, lds;
-};
-// the one-wave-per-event launch of small requests, when they take it
-struct ObsFewLaunch {
-  uint32_t blocks, threads, slots, lds, copies;
-};
-bool obs_few_launch(uint64_t n, uint32_t cap, bool fixed, ObsFewLaunch* out);
-const void* obs_few_kernel(bool massive);
-uint32_t obs_group_launches(uint32_t cap, bool massive, ObsGroupLaunch out[3]);
-size_t obs_group_lds(uint32_t g, uint32_t slots);
 void launch_me(const Records& r, const Summary& s, const EventInputs& in, uint32_t n,
                hipStream_t st, double* zero_hist = nullptr);
 void launch_shower_plain(const Records& r, const Summary& s, const EventInputs& in, uint32_t n,

@@ -1200,123 +1200,6 @@ void launch_zero(double* p, uint32_t n, hipStream_t st) {
   hipLaunchKernelGGL(k_zero, dim3((n + 255) / 256), dim3(256), 0, st, p, n);
 }
 
-// Host-side graph of one batch: [ev0] reset [ev1] persistent [ev2] obs [ev3].
-// The event nodes are pointed at the call's timing events (or at the
-// context's idle set) before each launch.
-static vsh_status build_batch_graph(vsh_ctx* ctx, BatchGraph& g, const PersistArgs& A, const ReqDev& d,
-                                    const Segment& sg, uint64_t lanes, uint32_t block, const BatchLayout& L,
-                                    const EventInputs& in, uint64_t n, double* hist) {
-  hipError_t err;
-#define GCHK(x)                                          \
-  do {                                                   \
-    err = (x);                                           \
-    if (err != hipSuccess) return hip_fail(ctx, err, #x); \
-  } while (0)
-  GCHK(hipGraphCreate(&g.graph, 0));
-  hipGraphNode_t prev = nullptr;
-  auto add_event = [&](int k) -> hipError_t {
-    hipGraphNode_t node;
-    hipError_t e = hipGraphAddEventRecordNode(&node, g.graph, prev ? &prev : nullptr, prev ? 1 : 0,
-                                              ctx->idle_ev[k]);
-    if (e == hipSuccess) {
-      g.ev_nodes[k] = node;
-      prev = node;
-    }
-    return e;
-  };
-  auto add_kernel = [&](const void* fn, dim3 grid, dim3 blk, void** args, unsigned lds = 0) -> hipError_t {
-    hipKernelNodeParams p{};
-    p.func = const_cast<void*>(fn);
-    p.gridDim = grid;
-    p.blockDim = blk;
-    p.sharedMemBytes = lds;
-    p.kernelParams = args;
-    p.extra = nullptr;
-    hipGraphNode_t node;
-    hipError_t e = hipGraphAddKernelNode(&node, g.graph, prev ? &prev : nullptr, prev ? 1 : 0, &p);
-    if (e == hipSuccess) prev = node;
-    return e;
-  };
-  g.args = A;
-  g.d = d;
-  g.s = sg;
-  g.rd = L.reqs;
-  g.sd = L.segs;
-  g.counter = L.counter;
-  g.rec = L.buf.out;
-  g.sum = L.buf.sum;
-  g.in = in;
-  g.sc = L.sc;
-  g.n = (uint32_t)n;
-  g.hist = hist;
-  GCHK(add_event(0));
-  void* a_setup[] = {&g.rd, &g.d, &g.sd, &g.s, &g.counter};
-  GCHK(add_kernel((const void*)k_setup, dim3(1), dim3(64), a_setup));
-  void* a_me[] = {&g.rec, &g.sum, &g.in, &g.n, &g.no_hist};
-  GCHK(add_kernel((const void*)k_me, dim3((uint32_t)((n + 255) / 256)), dim3(256), a_me));
-  GCHK(add_event(1));
-  void* a_pers[] = {&g.args};
-  const bool massive = g.in.massive != 0;
-  GCHK(add_kernel(persistent_kernel(g.mapping, true, massive, true, A.slots.cap), dim3(persistent_grid(A, lanes, block, g.mapping)), dim3(block),
-                  a_pers, g.mapping == kMapFlat ? (unsigned)flat_lds_bytes(A.slots.cap) : 0u));
-  GCHK(add_event(2));
-  g.nb = L.buf.out.cap + 1;
-  g.cap = L.buf.out.cap;
-  const bool fixed = g.in.fixed_hist != 0;
-  g.ih = fixed ? g.sc.ihist : nullptr;
-  g.wm = fixed ? g.sc.wmax : nullptr;
-  ObsFewLaunch few;
-  const bool is_few = obs_few_launch(n, g.cap, fixed, &few);
-  g.copies = is_few ? few.copies : kHistCopies;
-  void* a_zero[] = {&g.sc.cnt, &g.nb, &g.sc.hcopy, &g.ih, &g.wm};
-  if (g.copies) GCHK(add_kernel((const void*)k_obs_reset, dim3(obs_reset_blocks(g.nb)), dim3(256),
-                  a_zero));
-  if (is_few) {
-    g.fslots = few.slots;
-    void* a_wmax[] = {&g.sum, &g.n, &g.wm};
-    if (fixed) GCHK(add_kernel((const void*)k_obs_wmax, dim3(obs_wmax_blocks(n)), dim3(256), a_wmax));
-    void* a_few[] = {&g.rec, &g.sum, &g.in, &g.sc, &g.n, &g.fslots, &g.copies, &g.hist};
-    GCHK(add_kernel(obs_few_kernel(massive), dim3(few.blocks), dim3(few.threads), a_few, few.lds));
-  } else {
-    const uint32_t eb = obs_sort_blocks(n);
-    void* a_count[] = {&g.sum, &g.n, &g.cap, &g.sc.cnt, &g.wm};
-    GCHK(add_kernel((const void*)k_obs_count, dim3(eb), dim3(256), a_count));
-    void* a_scan[] = {&g.sc.cnt, &g.nb};
-    GCHK(add_kernel((const void*)k_obs_scan, dim3(1), dim3(256), a_scan));
-    void* a_scatter[] = {&g.sum, &g.n, &g.cap, &g.sc.cnt, &g.sc.perm};
-    GCHK(add_kernel((const void*)k_obs_scatter, dim3(eb), dim3(256), a_scatter));
-    void* a_obs[] = {&g.rec, &g.sum, &g.in, &g.sc, &g.n, &g.hist};
-    const uint32_t ob = (uint32_t)(std::min<uint64_t>(g.sc.stride, (n + 255) / 256 * 256) / 256);
-    GCHK(add_kernel(obs_kernel(massive), dim3(ob), dim3(256), a_obs));
-    g.perm_c = g.sc.perm;
-    g.cnt_c = g.sc.cnt;
-    ObsGroupLaunch gl[3];
-    const uint32_t ng = obs_group_launches(g.cap, massive, gl);
-    for (uint32_t k = 0; k < ng; ++k) {
-      g.glo[k] = gl[k].lo;
-      g.ghi[k] = gl[k].hi;
-      g.gslots[k] = gl[k].slots;
-      void* a_grp[] = {&g.rec, &g.sum, &g.in, &g.perm_c, &g.cnt_c, &g.cap, &g.glo[k], &g.ghi[k], &g.gslots[k], &g.hist,
-                       &g.sc};
-      const uint32_t wb = (uint32_t)std::min<uint64_t>(n, kObsWaveBlocks);
-      GCHK(add_kernel(gl[k].fn, dim3(wb), dim3(64), a_grp, gl[k].lds));
-    }
-  }
-  g.fixed = fixed ? 1u : 0u;
-  void* a_fin[] = {&g.sc, &g.hist, &g.fixed};
-  if (g.copies) GCHK(add_kernel((const void*)k_hist_finalize, dim3(kHistBlocks), dim3(256), a_fin));
-  GCHK(add_event(3));
-  GCHK(hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0));
-#undef GCHK
-  return VSH_OK;
-}
-
-void destroy_graph(BatchGraph& g) {
-  if (g.exec) (void)hipGraphExecDestroy(g.exec);
-  if (g.graph) (void)hipGraphDestroy(g.graph);
-  g = BatchGraph{};
-}
-
 static void fill_request_desc(ReqDev& d, const ReqBuffers& b, const vsh_request* req, uint64_t first_idx,
                               const double* ecm_dev, const double* tcut_dev) {
   d.out = b.out;
@@ -1337,10 +1220,14 @@ static void fill_request_desc(ReqDev& d, const ReqBuffers& b, const vsh_request*
 // One batch of `n` events of req (starting at request index first_idx)
 // through the persistent form on stream st, with the batch's buffers in the
 // workspace at `base`.  Inputs: per-event arrays already on the device (or
-// null).  Writes the histogram into hist (accumulates).
+// null).  Writes the histogram into hist (accumulates), the summary fields
+// into the arrays that `out` names, [field][n], and the workspace's for others.
+// The kernels are launched one by one: the same sequence as an instantiated
+// graph took 25 us longer a call (its event nodes set anew each time), and 60
+// where a caller's buffers change from call to call.
 vsh_status run_batch(vsh_ctx* ctx, const vsh_request* req, uint64_t first_idx, uint64_t n,
                             hipStream_t st, void* base, const double* ecm_dev, const double* tcut_dev,
-                            double* hist, bool use_graph, BatchLayout* out_layout) {
+                            double* hist, const Summary* out, BatchLayout* out_layout) {
   const uint32_t cap = req->max_partons;
   const uint64_t lanes = persistent_lanes(ctx);
   const uint32_t mapping = ctx->tuned.mapping;
@@ -1351,6 +1238,9 @@ vsh_status run_batch(vsh_ctx* ctx, const vsh_request* req, uint64_t first_idx, u
     return VSH_E_INTERNAL;
   }
   BatchLayout L = carve_batch(base, n, cap, request_massive(*req) != 0);
+  if (out && out->d) L.buf.sum.d = out->d;
+  if (out && out->i) L.buf.sum.i = out->i;
+  if (out && out->hash) L.buf.sum.hash = out->hash;
   if (out_layout) *out_layout = L;
   ReqDev d;
   fill_request_desc(d, L.buf, req, first_idx, ecm_dev, tcut_dev);
@@ -1380,41 +1270,16 @@ vsh_status run_batch(vsh_ctx* ctx, const vsh_request* req, uint64_t first_idx, u
   in.massive = request_massive(*req);
   in.fixed_hist = (req->flags & VSH_HIST_FIXEDPOINT) ? 1u : 0u;
   hipEvent_t* tev = timing_slot(ctx);
-  if (use_graph) {
-    BatchGraph& g = ctx->graph;
-    const bool same = g.exec && std::memcmp(&g.args, &A, sizeof A) == 0 && g.hist == hist && g.n == n &&
-                      std::memcmp(&g.in, &in, sizeof in) == 0 && std::memcmp(&g.d, &d, sizeof d) == 0 &&
-                      std::memcmp(&g.s, &sg, sizeof sg) == 0 && g.lanes == lanes && g.block == block &&
-                      g.mapping == mapping;
-    if (!same) {
-      destroy_graph(g);
-      g.mapping = mapping;
-      vsh_status rc = build_batch_graph(ctx, g, A, d, sg, lanes, block, L, in, n, hist);
-      if (rc) {
-        destroy_graph(g);
-        return rc;
-      }
-      g.lanes = lanes;
-      g.block = block;
-    }
-    for (int k = 0; k < 4; ++k) {
-      err = hipGraphExecEventRecordNodeSetEvent(g.exec, g.ev_nodes[k], tev ? tev[k] : ctx->idle_ev[k]);
-      if (err != hipSuccess) return hip_fail(ctx, err, "hipGraphExecEventRecordNodeSetEvent");
-    }
-    err = hipGraphLaunch(g.exec, st);
-    if (err != hipSuccess) return hip_fail(ctx, err, "hipGraphLaunch");
-  } else {
-    if (tev) (void)hipEventRecord(tev[0], st);
-    launch_setup(L.reqs, d, L.segs, sg, L.counter, st);
-    launch_me(L.buf.out, L.buf.sum, in, (uint32_t)n, st);
-    if (tev) (void)hipEventRecord(tev[1], st);
-    launch_persistent(A, lanes, block, mapping, true, in.massive != 0, st);
-    if (tev) (void)hipEventRecord(tev[2], st);
-    launch_obs(L.buf.out, L.buf.sum, in, L.sc, (uint32_t)n, hist, st);
-    if (tev) (void)hipEventRecord(tev[3], st);
-    err = hipGetLastError();
-    if (err != hipSuccess) return hip_fail(ctx, err, "kernel launch");
-  }
+  if (tev) (void)hipEventRecord(tev[0], st);
+  launch_setup(L.reqs, d, L.segs, sg, L.counter, st);
+  launch_me(L.buf.out, L.buf.sum, in, (uint32_t)n, st);
+  if (tev) (void)hipEventRecord(tev[1], st);
+  launch_persistent(A, lanes, block, mapping, true, in.massive != 0, st);
+  if (tev) (void)hipEventRecord(tev[2], st);
+  launch_obs(L.buf.out, L.buf.sum, in, L.sc, (uint32_t)n, hist, st);
+  if (tev) (void)hipEventRecord(tev[3], st);
+  err = hipGetLastError();
+  if (err != hipSuccess) return hip_fail(ctx, err, "kernel launch");
   return VSH_OK;
 }
 
@@ -1428,24 +1293,9 @@ uint64_t persistent_workspace_bytes(const vsh_request* req) {
 
 vsh_status persistent_into(vsh_ctx* ctx, const vsh_request* req, hipStream_t st, void* ws, double* dev_hist,
                            double* dev_sum_d, int32_t* dev_sum_i, uint64_t* dev_hash) {
-  const uint64_t n = req->n_events;
-  BatchLayout L;
-  vsh_status rc = run_batch(ctx, req, 0, n, st, ws, req->ecm_per_event, req->tcut_per_event, dev_hist, true, &L);
-  if (rc) return rc;
-  hipError_t err;
-  if (dev_sum_d) {
-    err = hipMemcpyAsync(dev_sum_d, L.buf.sum.d, kNSumD * n * 8, hipMemcpyDeviceToDevice, st);
-    if (err != hipSuccess) return hip_fail(ctx, err, "summary copy");
-  }
-  if (dev_sum_i) {
-    err = hipMemcpyAsync(dev_sum_i, L.buf.sum.i, kNSumI * n * 4, hipMemcpyDeviceToDevice, st);
-    if (err != hipSuccess) return hip_fail(ctx, err, "summary copy");
-  }
-  if (dev_hash) {
-    err = hipMemcpyAsync(dev_hash, L.buf.sum.hash, n * 8, hipMemcpyDeviceToDevice, st);
-    if (err != hipSuccess) return hip_fail(ctx, err, "summary copy");
-  }
-  return VSH_OK;
+  const Summary out{dev_sum_d, dev_sum_i, dev_hash, req->n_events};
+  return run_batch(ctx, req, 0, req->n_events, st, ws, req->ecm_per_event, req->tcut_per_event, dev_hist, &out,
+                   nullptr);
 }
 
 vsh_status generate_persistent(vsh_ctx* ctx, const vsh_request* req, vsh_result** out) {

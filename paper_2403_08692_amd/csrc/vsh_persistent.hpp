@@ -80,38 +80,6 @@ struct BatchLayout {
   char* end;
 };
 
-// the launch sequence of one batch as an instantiated hipGraph; the kernel
-// arguments live here so the graph's parameter pointers stay valid
-struct BatchGraph {
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
-  hipGraphNode_t ev_nodes[4] = {nullptr, nullptr, nullptr, nullptr};
-  ReqDev* rd = nullptr;
-  ReqDev d{};
-  Segment* sd = nullptr;
-  Segment s{};
-  unsigned long long* counter = nullptr;
-  PersistArgs args{};
-  Records rec{};
-  Summary sum{};
-  EventInputs in{};
-  Scratch sc{};
-  uint32_t n = 0, nb = 0, cap = 0, thr = 0;
-  uint32_t glo[3] = {0, 0, 0}, ghi[3] = {0, 0, 0}, gslots[3] = {0, 0, 0};
-  uint32_t fslots = 0;  // k_obs_few's LDS slots
-  uint32_t copies = 0;  // histogram copies (0: straight into hist)
-  const uint32_t* perm_c = nullptr;
-  const uint32_t* cnt_c = nullptr;
-  double* hist = nullptr;
-  double* no_hist = nullptr;  // k_me's histogram to clear: none in a batch
-  unsigned long long* ih = nullptr;  // fixed-point cells and largest weight (null: FP64 sums)
-  unsigned long long* wm = nullptr;
-  uint32_t fixed = 0;  // k_hist_finalize's fixed-point flag
-  uint64_t lanes = 0;
-  uint32_t block = 0;
-  uint32_t mapping = 0;
-};
-
 // events a wave of a persistent launch over `total` events holds at once
 uint32_t persistent_per_wave(uint64_t total, uint64_t lanes, uint32_t mapping, uint32_t cap, bool massive);
 uint64_t slots_bytes(uint64_t lanes, uint32_t cap);
@@ -128,6 +96,5 @@ void launch_setup(ReqDev* rd, const ReqDev& d, Segment* sd, const Segment& s, un
 void launch_zero(double* p, uint32_t n, hipStream_t st);
 void launch_shower_plain_flat(const Records& r, const Summary& s, const EventInputs& in, uint32_t n,
                               uint64_t* cache, hipStream_t st);
-void destroy_graph(BatchGraph& g);
 
 }  // namespace vsh

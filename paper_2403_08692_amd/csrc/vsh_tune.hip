@@ -60,7 +60,7 @@ static vsh_status time_persistent(vsh_ctx* ctx, const vsh_request* req, uint64_t
   ctx->timing = true;
   ctx->timing_calls = 0;
   BatchLayout L;
-  vsh_status rc = run_batch(ctx, req, 0, m, ctx->stream, base, ecm_dev, tcut_dev, hist, false, &L);
+  vsh_status rc = run_batch(ctx, req, 0, m, ctx->stream, base, ecm_dev, tcut_dev, hist, nullptr, &L);
   hipError_t err = hipSuccess;
   if (!rc) err = hipStreamSynchronize(ctx->stream);
   if (!rc && err == hipSuccess) err = hipEventElapsedTime(ms, ctx->timing_ev[1], ctx->timing_ev[2]);
@@ -147,7 +147,6 @@ static vsh_status autotune_persistent(vsh_ctx* ctx, const vsh_request* req) {
   }
   ctx->tuned = best;
   ctx->tuned_ms = best_ms;
-  destroy_graph(ctx->graph);
   return VSH_OK;
 }
 
@@ -281,7 +280,6 @@ vsh_status vsh_set_tuning(vsh_ctx* ctx, const vsh_tuning* t) {
   if (!ctx || !t) return VSH_E_INVALID;
   std::lock_guard<std::mutex> lk(ctx->mu);
   ctx->tuned = from_pub(*t);
-  destroy_graph(ctx->graph);
   return VSH_OK;
 }
 
@@ -306,8 +304,7 @@ vsh_status vsh_autotune(vsh_ctx* ctx, const vsh_request* sample, vsh_tuning* cho
       ctx->tuned.pers_block = t.pers_block;
       ctx->tuned.refill_threshold = t.refill_threshold;
       ctx->tuned.refill_period = t.refill_period;
-      destroy_graph(ctx->graph);
-    } else {
+        } else {
       ctx->tuned.plain_block = t.plain_block;
       ctx->tuned.plain_waves = t.plain_waves;
       ctx->tuned.plain_mapping = t.plain_mapping;
