@@ -61,6 +61,17 @@ __device__ __forceinline__ uint64_t lane63(uint64_t x) {
   return ((uint64_t)hi << 32) | lo;
 }
 
+// x of the lane R places below within the row of 16 lanes, wrapping round
+// (DPP row_ror; the lanes of a row run together)
+template <int R>
+__device__ __forceinline__ uint32_t row_ror(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x120 + R, 0xf, 0xf, false);
+}
+template <int R>
+__device__ __forceinline__ double row_ror(double x) {
+  return __hiloint2double((int)row_ror<R>((uint32_t)__double2hiint(x)), (int)row_ror<R>((uint32_t)__double2loint(x)));
+}
+
 // x of lane `src` (the same in every lane of the wave)
 __device__ __forceinline__ double lane_value(double x, int src) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), src),

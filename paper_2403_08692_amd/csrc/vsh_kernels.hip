@@ -332,10 +332,22 @@ __global__ void __launch_bounds__(256) k_obs(Records r, Summary sm, EventInputs 
 // wave, whose LDS operations take effect in program order, so the groups
 // (which may run different numbers of steps) need no barrier between them.
 // ---------------------------------------------------------------------------
+// Reductions over G = 16 or 64 lanes.  Within a row of 16 lanes as DPP
+// rotations (by 8, 4, 2, 1: after each the values repeat with that period, so
+// a rotation meets the same pairs as a butterfly) instead of shuffles through
+// the LDS pipe, whose latency bound the groups: k_obs_group<16> on the
+// 10^6-event stress batch 4.54 -> 4.47 ms.
 template <int G>
 __device__ __forceinline__ double group_sum(double v) {
-#pragma unroll
-  for (int d = G / 2; d >= 1; d >>= 1) v += __shfl_xor(v, d, G);
+  static_assert(G == 16 || G == 64, "a row of lanes or a wave");
+  if constexpr (G == 64) {
+    v += __shfl_xor(v, 32);
+    v += __shfl_xor(v, 16);
+  }
+  v += row_ror<8>(v);
+  v += row_ror<4>(v);
+  v += row_ror<2>(v);
+  v += row_ror<1>(v);
   return v;
 }
 
@@ -347,15 +359,16 @@ __device__ __forceinline__ void group_argmax(double& v, uint32_t& idx) {
     idx = wave_min(v == m ? idx : 0xFFFFFFFFu);
     v = m;
   } else {
-#pragma unroll
-    for (int d = G / 2; d >= 1; d >>= 1) {
-      const double ov = __shfl_xor(v, d, G);
-      const uint32_t oi = __shfl_xor(idx, d, G);
+    auto take = [&](double ov, uint32_t oi) {
       if (ov > v || (ov == v && oi < idx)) {
         v = ov;
         idx = oi;
       }
-    }
+    };
+    take(row_ror<8>(v), row_ror<8>(idx));
+    take(row_ror<4>(v), row_ror<4>(idx));
+    take(row_ror<2>(v), row_ror<2>(idx));
+    take(row_ror<1>(v), row_ror<1>(idx));
   }
 }
 
@@ -366,15 +379,16 @@ __device__ __forceinline__ void group_argmin(double& v, uint32_t& idx) {
     idx = wave_min(v == m ? idx : 0xFFFFFFFFu);
     v = m;
   } else {
-#pragma unroll
-    for (int d = G / 2; d >= 1; d >>= 1) {
-      const double ov = __shfl_xor(v, d, G);
-      const uint32_t oi = __shfl_xor(idx, d, G);
+    auto take = [&](double ov, uint32_t oi) {
       if (ov < v || (ov == v && oi < idx)) {
         v = ov;
         idx = oi;
       }
-    }
+    };
+    take(row_ror<8>(v), row_ror<8>(idx));
+    take(row_ror<4>(v), row_ror<4>(idx));
+    take(row_ror<2>(v), row_ror<2>(idx));
+    take(row_ror<1>(v), row_ror<1>(idx));
   }
 }
 
@@ -438,15 +452,15 @@ __device__ __forceinline__ int group_observables(const Records& r, const EventIn
     tx += p.x;
     ty += p.y;
     tz += p.z;
-    const double l = sqrt(p.x * p.x + p.y * p.y + p.z * p.z);
+    const double l = len3(p.x, p.y, p.z);
     sum += l;
     const double il = 1.0 / l;
-    mxx += p.x * p.x * il;
-    myy += p.y * p.y * il;
-    mzz += p.z * p.z * il;
-    mxy += p.x * p.y * il;
-    mxz += p.x * p.z * il;
-    myz += p.y * p.z * il;
+    mxx = fma(p.x * p.x, il, mxx);
+    myy = fma(p.y * p.y, il, myy);
+    mzz = fma(p.z * p.z, il, mzz);
+    mxy = fma(p.x * p.y, il, mxy);
+    mxz = fma(p.x * p.z, il, mxz);
+    myz = fma(p.y * p.z, il, myz);
   }
   tE = group_sum<S>(tE);
   tx = group_sum<S>(tx);
@@ -477,20 +491,20 @@ __device__ __forceinline__ int group_observables(const Records& r, const EventIn
     for (uint32_t pidx = lane; pidx < npairs; pidx += P, pw.advance(P)) {
       const uint32_t i = pw.i, j = pw.j();
       const double xi = px[i], yi = py[i], zi = pz[i], xj = px[j], yj = py[j], zj = pz[j];
-      const double nx = yi * zj - zi * yj, ny = zi * xj - xi * zj, nz = xi * yj - yi * xj;
+      const double nx = det2(yi, zj, zi, yj), ny = det2(zi, xj, xi, zj), nz = det2(xi, yj, yi, xj);
       double vx = 0.0, vy = 0.0, vz = 0.0;
       for (int k = 0; k < np; ++k) {
-        if (k == (int)i || k == (int)j) continue;
         const double xk = px[k], yk = py[k], zk = pz[k];
-        const double d = xk * nx + yk * ny + zk * nz;
-        if (d > 0.0) { vx += xk; vy += yk; vz += zk; }
-        else { vx -= xk; vy -= yk; vz -= zk; }
+        const double sk = side(dot3(xk, yk, zk, nx, ny, nz), k == (int)i || k == (int)j);
+        vx = fma(sk, xk, vx);
+        vy = fma(sk, yk, vy);
+        vz = fma(sk, zk, vz);
       }
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         const double si = (c < 2) ? 1.0 : -1.0, sj = (c & 1) ? -1.0 : 1.0;
         const double wx = vx + si * xi + sj * xj, wy = vy + si * yi + sj * yj, wz = vz + si * zi + sj * zj;
-        const double m2 = wx * wx + wy * wy + wz * wz;
+        const double m2 = sq3(wx, wy, wz);
         if (m2 > best) { best = m2; bidx = 4 * pidx + c; bx = wx; by = wy; bz = wz; }
       }
     }
@@ -509,24 +523,20 @@ __device__ __forceinline__ int group_observables(const Records& r, const EventIn
     const double T = sum > 0.0 ? lb / sum : 0.0;
     const double tau = 1.0 - T;
     v[2] = tau > 0.0 ? tau : 0.0;
-    const double m2s = mxx * mxx + myy * myy + mzz * mzz + 2.0 * (mxy * mxy + mxz * mxz + myz * myz);
-    const double cpar = 1.5 * (sum * sum - m2s) / (sum * sum);
-    v[3] = cpar > 0.0 ? cpar : 0.0;
+    v[3] = c_parameter(sum, mxx, myy, mzz, mxy, mxz, myz);
     // hemispheres
     double hpE = 0, hpx = 0, hpy = 0, hpz = 0, hmE = 0, hmx = 0, hmy = 0, hmz = 0, bp = 0, bm = 0;
     for (int a = sub; a < np; a += S) {
       const double x = px[a], y = py[a], z = pz[a], en = pE[a];
-      const double d = x * ax + y * ay + z * az;
-      const double cx = y * az - z * ay, cy = z * ax - x * az, cz = x * ay - y * ax;
-      const double kt = sqrt(cx * cx + cy * cy + cz * cz);
+      const double d = dot3(x, y, z, ax, ay, az);
+      const double kt = len3(det2(y, az, z, ay), det2(z, ax, x, az), det2(x, ay, y, ax));
       if (d >= 0.0) { hpE += en; hpx += x; hpy += y; hpz += z; bp += kt; }
       else { hmE += en; hmx += x; hmy += y; hmz += z; bm += kt; }
     }
     hpE = group_sum<S>(hpE); hpx = group_sum<S>(hpx); hpy = group_sum<S>(hpy); hpz = group_sum<S>(hpz);
     hmE = group_sum<S>(hmE); hmx = group_sum<S>(hmx); hmy = group_sum<S>(hmy); hmz = group_sum<S>(hmz);
     bp = group_sum<S>(bp); bm = group_sum<S>(bm);
-    const double mp = hpE * hpE - hpx * hpx - hpy * hpy - hpz * hpz;
-    const double mm = hmE * hmE - hmx * hmx - hmy * hmy - hmz * hmz;
+    const double mp = mass2(hpE, hpx, hpy, hpz), mm = mass2(hmE, hmx, hmy, hmz);
     const double rho = (mp > mm ? mp : mm) / sh;
     v[4] = rho > 0.0 ? rho : 0.0;
     bp /= 2.0 * sum;
@@ -537,7 +547,7 @@ __device__ __forceinline__ int group_observables(const Records& r, const EventIn
     const double inv_s = 1.0 / sh;
     for (int a = lane; a < np; a += P) {
       list[a] = (uint16_t)a;
-      const double l = sqrt(px[a] * px[a] + py[a] * py[a] + pz[a] * pz[a]);
+      const double l = len3(px[a], py[a], pz[a]);
       ux[a] = px[a] / l;
       uy[a] = py[a] / l;
       uz[a] = pz[a] / l;
@@ -551,26 +561,25 @@ __device__ __forceinline__ int group_observables(const Records& r, const EventIn
       for (uint32_t pidx = lane; pidx < mp2; pidx += P, dw.advance(P)) {
         const int ja = list[dw.i], jb = list[dw.j()];
         const double dx = ux[ja] - ux[jb], dy = uy[ja] - uy[jb], dz = uz[ja] - uz[jb];
-        const double d2 = (dx * dx + dy * dy) + dz * dz;
-        const double em = pE[ja] < pE[jb] ? pE[ja] : pE[jb];
-        const double y = em * em * d2 * inv_s;
-        if (y < ymin) { ymin = y; yidx = pidx; }
+        const double y = jet_y(pE[ja] < pE[jb] ? pE[ja] : pE[jb], dx, dy, dz, inv_s);
+        if (y < ymin) { ymin = y; yidx = (dw.i << 16) | dw.j(); }  // ordered like pidx
       }
       group_argmin<P>(ymin, yidx);
-      const PairWalk win(yidx, (uint32_t)m);
-      const uint32_t ia = win.i, ib = win.j();
+      const uint32_t ia = yidx >> 16, ib = yidx & 0xFFFFu;
       if (m == 4) v[1] = ymin;
-      if (m == 3) v[0] = ymin;
+      if (m == 3) {  // two jets are left
+        v[0] = ymin;
+        break;
+      }
       const int ja = list[ia], jb = list[ib];
-      if (lane == 0) {
-        pE[ja] += pE[jb];
-        px[ja] += px[jb];
-        py[ja] += py[jb];
-        pz[ja] += pz[jb];
-        const double l = sqrt(px[ja] * px[ja] + py[ja] * py[ja] + pz[ja] * pz[ja]);
-        ux[ja] = px[ja] / l;
-        uy[ja] = py[ja] / l;
-        uz[ja] = pz[ja] / l;
+      const double en = pE[ja] + pE[jb], x = px[ja] + px[jb], y = py[ja] + py[jb], z = pz[ja] + pz[jb];
+      const double l = len3(x, y, z);
+      // one of E and the components per lane: one division instead of three in
+      // the step's serial chain (stress batch 4.15 -> 4.06 ms)
+      if (lane < 4) {
+        const double c = lane == 0 ? x : lane == 1 ? y : z;
+        (lane == 3 ? pE : lane == 0 ? px : lane == 1 ? py : pz)[ja] = lane == 3 ? en : c;
+        if (lane < 3) (lane == 0 ? ux : lane == 1 ? uy : uz)[ja] = c / l;
       }
       // drop jet ib from the list: read the entries after it, then write them back one place down
       uint16_t mv[MV];
@@ -709,11 +718,11 @@ __device__ __forceinline__ int small_observables(const Records& r, const EventIn
       const double nx = det2(yi, zj, zi, yj), ny = det2(zi, xj, xi, zj), nz = det2(xi, yj, yi, xj);
       double vx = 0.0, vy = 0.0, vz = 0.0;
       for (int k = 0; k < np; ++k) {
-        if (k == i || k == j) continue;
         const double xk = X[k], yk = Y[k], zk = Z[k];
-        const double d = dot3(xk, yk, zk, nx, ny, nz);
-        if (d > 0.0) { vx += xk; vy += yk; vz += zk; }
-        else { vx -= xk; vy -= yk; vz -= zk; }
+        const double sk = side(dot3(xk, yk, zk, nx, ny, nz), k == i || k == j);
+        vx = fma(sk, xk, vx);
+        vy = fma(sk, yk, vy);
+        vz = fma(sk, zk, vz);
       }
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
@@ -736,9 +745,7 @@ __device__ __forceinline__ int small_observables(const Records& r, const EventIn
   const double T = sum > 0.0 ? lb / sum : 0.0;
   const double tau = 1.0 - T;
   v[2] = tau > 0.0 ? tau : 0.0;
-  const double m2s = mxx * mxx + myy * myy + mzz * mzz + 2.0 * (mxy * mxy + mxz * mxz + myz * myz);
-  const double cpar = 1.5 * (sum * sum - m2s) / (sum * sum);
-  v[3] = cpar > 0.0 ? cpar : 0.0;
+  v[3] = c_parameter(sum, mxx, myy, mzz, mxy, mxz, myz);
   // hemispheres
   bool plus = false;
   if (lane < (uint32_t)np) {
@@ -755,7 +762,7 @@ __device__ __forceinline__ int small_observables(const Records& r, const EventIn
     if (in_plus >> a & 1ull) { hp.e += p.e; hp.x += p.x; hp.y += p.y; hp.z += p.z; bp += kt; }
     else { hm.e += p.e; hm.x += p.x; hm.y += p.y; hm.z += p.z; bm += kt; }
   }
-  const double mp = mdot(hp, hp), mm = mdot(hm, hm);
+  const double mp = mass2(hp.e, hp.x, hp.y, hp.z), mm = mass2(hm.e, hm.x, hm.y, hm.z);
   const double rho = (mp > mm ? mp : mm) / sh;
   v[4] = rho > 0.0 ? rho : 0.0;
   bp /= 2.0 * sum;
@@ -778,10 +785,8 @@ __device__ __forceinline__ int small_observables(const Records& r, const EventIn
     const bool live = lane < npairs && (alive >> i & 1u) && (alive >> j & 1u);
     if (live && stale) {
       const double dx = L.ux[i] - L.ux[j], dy = L.uy[i] - L.uy[j], dz = L.uz[i] - L.uz[j];
-      const double d2 = (dx * dx + dy * dy) + dz * dz;
       const double ei = E[i], ej = E[j];
-      const double em = ei < ej ? ei : ej;
-      y = em * em * d2 * inv_s;
+      y = jet_y(ei < ej ? ei : ej, dx, dy, dz, inv_s);
     }
     // the serial scan takes the first pair and then any smaller one: a NaN
     // stays only if it comes first

@@ -10,16 +10,23 @@ namespace vsh {
 // ---------------------------------------------------------------------------
 // Observables, one thread per event (Sec. 3.1).
 // ---------------------------------------------------------------------------
-// Sums of products with their fused operations written out, so that every
-// path that measures small events (one thread or one wave per event) rounds
-// alike: left to the compiler, the product it fuses depends on what else uses
-// it nearby.
+// Sums of products with their fused operations written out, so that the
+// kernels that measure an event of some size (one thread, a lane group or a
+// wave) round alike: left to the compiler, the product it fuses depends on
+// what else uses it nearby.
 __device__ __forceinline__ double dot3(double ax, double ay, double az, double bx, double by, double bz) {
 #pragma clang fp contract(off)
   return fma(az, bz, fma(ay, by, ax * bx));
 }
 __device__ __forceinline__ double sq3(double x, double y, double z) { return dot3(x, y, z, x, y, z); }
 __device__ __forceinline__ double len3(double x, double y, double z) { return sqrt(sq3(x, y, z)); }
+// +1 for d > 0, else -1, and 0 where `out`: a parton's sign in a plane's sum.
+// v + sign x by one fused operation is v + x, v - x or v, exactly. (The
+// two branches of a comparison instead: k_obs 447 against 427 us on 10^6 LEP
+// events, k_obs_group<16> 4.47 against 4.15 ms on the stress batch.)
+__device__ __forceinline__ double side(double d, bool out) {
+  return __hiloint2double(out ? 0 : (d > 0.0 ? 0x3FF00000 : (int)0xBFF00000u), 0);
+}
 // a b - c d
 __device__ __forceinline__ double det2(double a, double b, double c, double d) {
 #pragma clang fp contract(off)
@@ -32,6 +39,25 @@ __device__ __forceinline__ int bin_of(double x, double lo, double hi) {
   if (x >= hi) return kNBins + 1;
   int b = 1 + (int)((x - lo) / (hi - lo) * kNBins);
   return b > kNBins ? kNBins : b;
+}
+
+// squared mass of a momentum sum
+__device__ __forceinline__ double mass2(double e, double x, double y, double z) {
+#pragma clang fp contract(off)
+  return fma(-z, z, fma(-y, y, fma(-x, x, e * e)));
+}
+// C from sum |p| and the momentum tensor
+__device__ __forceinline__ double c_parameter(double sum, double mxx, double myy, double mzz, double mxy, double mxz,
+                                              double myz) {
+#pragma clang fp contract(off)
+  const double m2s = fma(2.0, sq3(mxy, mxz, myz), sq3(mxx, myy, mzz));
+  const double c = 1.5 * fma(sum, sum, -m2s) / (sum * sum);
+  return c > 0.0 ? c : 0.0;
+}
+// Durham y of two jets: smaller energy, difference of the unit vectors
+__device__ __forceinline__ double jet_y(double em, double dx, double dy, double dz, double inv_s) {
+#pragma clang fp contract(off)
+  return em * em * sq3(dx, dy, dz) * inv_s;
 }
 
 struct ObsOut {
@@ -56,10 +82,8 @@ struct ObsOut {
 
 __device__ __forceinline__ double durham_y(const Scratch& w, uint64_t qa, uint64_t qb, double inv_s) {
   const double dx = w.ux[qa] - w.ux[qb], dy = w.uy[qa] - w.uy[qb], dz = w.uz[qa] - w.uz[qb];
-  const double d2 = (dx * dx + dy * dy) + dz * dz;
   const double ea = w.E[qa], eb = w.E[qb];
-  const double em = ea < eb ? ea : eb;
-  return em * em * d2 * inv_s;
+  return jet_y(ea < eb ? ea : eb, dx, dy, dz, inv_s);
 }
 
 __device__ __forceinline__ void set_unit(const Scratch& w, uint64_t q) {
@@ -242,9 +266,7 @@ __device__ __forceinline__ ObsOut scratch_observables(const Scratch& w, uint64_t
   const double T = sum > 0.0 ? lb / sum : 0.0;
   const double tau = 1.0 - T;
   o.v[2] = tau > 0.0 ? tau : 0.0;
-  const double m2s = mxx * mxx + myy * myy + mzz * mzz + 2.0 * (mxy * mxy + mxz * mxz + myz * myz);
-  const double cpar = 1.5 * (sum * sum - m2s) / (sum * sum);
-  o.v[3] = cpar > 0.0 ? cpar : 0.0;
+  o.v[3] = c_parameter(sum, mxx, myy, mzz, mxy, mxz, myz);
   P4 hp{0, 0, 0, 0}, hm{0, 0, 0, 0};
   double bp = 0.0, bm = 0.0;
   for (int a = 0; a < np; ++a) {
@@ -255,7 +277,7 @@ __device__ __forceinline__ ObsOut scratch_observables(const Scratch& w, uint64_t
     if (d >= 0.0) { hp.e += p.e; hp.x += p.x; hp.y += p.y; hp.z += p.z; bp += kt; }
     else { hm.e += p.e; hm.x += p.x; hm.y += p.y; hm.z += p.z; bm += kt; }
   }
-  const double mp = mdot(hp, hp), mm = mdot(hm, hm);
+  const double mp = mass2(hp.e, hp.x, hp.y, hp.z), mm = mass2(hm.e, hm.x, hm.y, hm.z);
   const double rho = (mp > mm ? mp : mm) / sh;
   o.v[4] = rho > 0.0 ? rho : 0.0;
   bp /= 2.0 * sum;
@@ -368,10 +390,11 @@ __device__ __forceinline__ ObsOut reg_observables(const Records& r, uint64_t e, 
 #pragma unroll
           for (int k = 0; k < M; ++k) {
             if (k >= wmax) break;
-            if (k != i && k != j && k < np) {
-              const double d = dot3(X[k], Y[k], Z[k], nx, ny, nz);
-              if (d > 0.0) { vx += X[k]; vy += Y[k]; vz += Z[k]; }
-              else { vx -= X[k]; vy -= Y[k]; vz -= Z[k]; }
+            if (k != i && k != j) {  // slots past np hold zeros
+              const double s = side(dot3(X[k], Y[k], Z[k], nx, ny, nz), false);
+              vx = fma(s, X[k], vx);
+              vy = fma(s, Y[k], vy);
+              vz = fma(s, Z[k], vz);
             }
           }
 #pragma unroll
@@ -391,9 +414,7 @@ __device__ __forceinline__ ObsOut reg_observables(const Records& r, uint64_t e, 
   const double T = sum > 0.0 ? lb / sum : 0.0;
   const double tau = 1.0 - T;
   o.v[2] = tau > 0.0 ? tau : 0.0;
-  const double m2s = mxx * mxx + myy * myy + mzz * mzz + 2.0 * (mxy * mxy + mxz * mxz + myz * myz);
-  const double cpar = 1.5 * (sum * sum - m2s) / (sum * sum);
-  o.v[3] = cpar > 0.0 ? cpar : 0.0;
+  o.v[3] = c_parameter(sum, mxx, myy, mzz, mxy, mxz, myz);
   P4 hp{0, 0, 0, 0}, hm{0, 0, 0, 0};
   double bp = 0.0, bm = 0.0;
 #pragma unroll
@@ -406,7 +427,7 @@ __device__ __forceinline__ ObsOut reg_observables(const Records& r, uint64_t e, 
       else { hm.e += p.e; hm.x += p.x; hm.y += p.y; hm.z += p.z; bm += kt; }
     }
   }
-  const double mp = mdot(hp, hp), mm = mdot(hm, hm);
+  const double mp = mass2(hp.e, hp.x, hp.y, hp.z), mm = mass2(hm.e, hm.x, hm.y, hm.z);
   const double rho = (mp > mm ? mp : mm) / sh;
   o.v[4] = rho > 0.0 ? rho : 0.0;
   bp /= 2.0 * sum;
@@ -443,9 +464,7 @@ __device__ __forceinline__ ObsOut reg_observables(const Records& r, uint64_t e, 
           if (b >= wmax) break;
           if (b > a && (alive >> b & 1u)) {
             const double dx = uxa - UX[b], dy = uya - UY[b], dz = uza - UZ[b];
-            const double d2 = (dx * dx + dy * dy) + dz * dz;
-            const double em = ea < E[b] ? ea : E[b];
-            const double y = em * em * d2 * inv_s;
+            const double y = jet_y(ea < E[b] ? ea : E[b], dx, dy, dz, inv_s);
             if (ia < 0 || y < ymin) {
               ymin = y;
               ia = a;
