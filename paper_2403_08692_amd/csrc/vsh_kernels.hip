@@ -119,21 +119,57 @@ __global__ void __launch_bounds__(256, kWaves) k_shower_plain(Records r, Summary
 // later pass), computes the observables and fills an LDS histogram that is
 // added to the global one once per block.
 // ---------------------------------------------------------------------------
+// A launch of the pass works on one request (its job in the kernel arguments)
+// or, in serving, on all that an epoch finishes (a table of jobs; each has a
+// range of blocks).  f(job, block within the job, the job's blocks).
+template <bool kMulti>
+struct ObsArgs;
+template <>
+struct ObsArgs<false> {
+  ObsJob job;
+};
+template <>
+struct ObsArgs<true> {
+  const ObsJob* jobs;
+  uint32_t count;
+};
+template <bool kMulti, class F>
+__device__ __forceinline__ void with_job(const ObsArgs<kMulti>& A, int stage, F&& f) {
+  if constexpr (!kMulti) {
+    f(A.job, blockIdx.x, gridDim.x);
+  } else {
+    uint32_t lo = 0, hi = A.count;  // the last job that begins at or before this block
+    while (hi - lo > 1) {
+      const uint32_t mid = (lo + hi) / 2;
+      if (A.jobs[mid].at[stage] <= blockIdx.x) lo = mid;
+      else hi = mid;
+    }
+    const uint32_t from = A.jobs[lo].at[stage], to = lo + 1 < A.count ? A.jobs[lo + 1].at[stage] : gridDim.x;
+    f(A.jobs[lo], blockIdx.x - from, to - from);
+  }
+}
+
 // Zero the counting sort's counters, the histogram copies and, for fixed-point histograms, the
 // integer cells and the largest-weight word (a kernel, not a memset, so the
 // sequence can be captured in a graph).
-__global__ void k_obs_reset(uint32_t* cnt, uint32_t nb, double* hcopy, unsigned long long* ihist,
-                            unsigned long long* wmax) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nb) cnt[i] = 0u;
-  if (i < kHistCopies * (uint32_t)kHistDoubles) {
-    hcopy[i] = 0.0;
-    if (ihist) ihist[i] = 0ull;
-  }
-  if (wmax && i == 0) *wmax = 0ull;
+template <bool kMulti>
+__global__ void __launch_bounds__(256) k_obs_reset(ObsArgs<kMulti> A) {
+  with_job(A, kObsStageHist, [&](const ObsJob& J, uint32_t blk, uint32_t grid) {
+    (void)grid;
+    const uint32_t nb = J.r.cap + 1;
+    uint32_t* cnt = J.sc.cnt;
+    double* hcopy = J.sc.hcopy;
+    unsigned long long* ihist = J.in.fixed_hist ? J.sc.ihist : nullptr;
+    unsigned long long* wmax = J.in.fixed_hist ? J.sc.wmax : nullptr;
+    const uint32_t i = blk * blockDim.x + threadIdx.x;
+    if (i < nb) cnt[i] = 0u;
+    if (i < kHistCopies * (uint32_t)kHistDoubles) {
+      hcopy[i] = 0.0;
+      if (ihist) ihist[i] = 0ull;
+    }
+    if (wmax && i == 0) *wmax = 0ull;
+  });
 }
-
-static uint32_t obs_reset_blocks(uint32_t nb) { return (std::max<uint32_t>(nb, kHistCopies * kHistDoubles) + 255) / 256; }
 
 // The largest |w| of the launch's events (the bits of non-negative doubles
 // order like the integers), one atomic per wave.
@@ -147,24 +183,31 @@ __device__ __forceinline__ void wave_max_weight(double w, unsigned long long* wm
 // the handful of occupied counts do not queue up); with wmax, also the
 // largest |w| of the events (the bits of non-negative doubles order like the
 // integers, so the maximum does not depend on order).
-__global__ void __launch_bounds__(256) k_obs_count(Summary sm, uint32_t n, uint32_t cap, uint32_t* cnt,
-                                                   unsigned long long* wmax) {
-  __shared__ uint32_t lc[kMaxCount + 1];
-  const uint32_t nb = cap + 1;
-  for (uint32_t k = threadIdx.x; k < nb; k += blockDim.x) lc[k] = 0u;
-  double w = 0.0;
-  __syncthreads();
-  const uint64_t e0 = (uint64_t)blockIdx.x * blockDim.x * kObsSortPer;
-  const uint64_t e1 = e0 + (uint64_t)blockDim.x * kObsSortPer < n ? e0 + (uint64_t)blockDim.x * kObsSortPer : n;
-  for (uint64_t e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
-    const uint32_t np = (uint32_t)sm.i[kSiN * sm.stride + e];
-    atomicAdd(&lc[cap - (np < cap ? np : cap)], 1u);
-    if (wmax) w = fmax(w, fabs(sm.d[kSdW * sm.stride + e]));
-  }
-  __syncthreads();
-  for (uint32_t k = threadIdx.x; k < nb; k += blockDim.x)
-    if (lc[k]) atomicAdd(&cnt[k], lc[k]);
-  if (wmax) wave_max_weight(w, wmax);
+template <bool kMulti>
+__global__ void __launch_bounds__(256) k_obs_count(ObsArgs<kMulti> A) {
+  with_job(A, kObsStageSort, [&](const ObsJob& J, uint32_t blk, uint32_t grid) {
+    (void)grid;
+    const Summary sm = J.sm;
+    const uint32_t n = J.n, cap = J.r.cap;
+    uint32_t* cnt = J.sc.cnt;
+    unsigned long long* wmax = J.in.fixed_hist ? J.sc.wmax : nullptr;
+    __shared__ uint32_t lc[kMaxCount + 1];
+    const uint32_t nb = cap + 1;
+    for (uint32_t k = threadIdx.x; k < nb; k += blockDim.x) lc[k] = 0u;
+    double w = 0.0;
+    __syncthreads();
+    const uint64_t e0 = (uint64_t)blk * blockDim.x * kObsSortPer;
+    const uint64_t e1 = e0 + (uint64_t)blockDim.x * kObsSortPer < n ? e0 + (uint64_t)blockDim.x * kObsSortPer : n;
+    for (uint64_t e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
+      const uint32_t np = (uint32_t)sm.i[kSiN * sm.stride + e];
+      atomicAdd(&lc[cap - (np < cap ? np : cap)], 1u);
+      if (wmax) w = fmax(w, fabs(sm.d[kSdW * sm.stride + e]));
+    }
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < nb; k += blockDim.x)
+      if (lc[k]) atomicAdd(&cnt[k], lc[k]);
+    if (wmax) wave_max_weight(w, wmax);
+  });
 }
 
 // The histogram copies into the caller's histogram (accumulated), one cell
@@ -173,87 +216,108 @@ __global__ void __launch_bounds__(256) k_obs_count(Summary sm, uint32_t n, uint3
 // integer cells summed (exactly, in any order), then sum w and sum w^2 scaled
 // back by their powers of two, entries as they are, so the result does not
 // depend on the order of the events.
-__global__ void __launch_bounds__(256) k_hist_finalize(Scratch sc, double* hist, uint32_t fixed) {
-  const uint32_t a = blockIdx.x * 256 + threadIdx.x;
-  if (a >= (uint32_t)kHistDoubles) return;
-  if (fixed) {
-    const FixScale fx = fix_scale(sc);
-    unsigned long long s = 0;
+template <bool kMulti>
+__global__ void __launch_bounds__(256) k_hist_finalize(ObsArgs<kMulti> A) {
+  with_job(A, kObsStageSum, [&](const ObsJob& J, uint32_t blk, uint32_t grid) {
+    (void)grid;
+    const Scratch sc = J.sc;
+    double* hist = J.hist;
+    const bool fixed = J.in.fixed_hist != 0;
+    const uint32_t a = blk * 256 + threadIdx.x;
+    if (a >= (uint32_t)kHistDoubles) return;
+    if (fixed) {
+      const FixScale fx = fix_scale(sc);
+      unsigned long long s = 0;
 #pragma unroll
-    for (uint32_t c = 0; c < kHistCopies; ++c) s += sc.ihist[c * kHistDoubles + a];
-    const double q = (double)(long long)s;
-    const int col = (int)(a % 3);
-    hist[a] += col == 0 ? ldexp(q, -fx.fw) : (col == 1 ? ldexp(q, -fx.fw2) : q);
-  } else {
-    double v = 0.0;
+      for (uint32_t c = 0; c < kHistCopies; ++c) s += sc.ihist[c * kHistDoubles + a];
+      const double q = (double)(long long)s;
+      const int col = (int)(a % 3);
+      hist[a] += col == 0 ? ldexp(q, -fx.fw) : (col == 1 ? ldexp(q, -fx.fw2) : q);
+    } else {
+      double v = 0.0;
 #pragma unroll
-    for (uint32_t c = 0; c < kHistCopies; ++c) v += sc.hcopy[c * kHistDoubles + a];
-    hist[a] += v;
-  }
+      for (uint32_t c = 0; c < kHistCopies; ++c) v += sc.hcopy[c * kHistDoubles + a];
+      hist[a] += v;
+    }
+  });
 }
 
 // exclusive prefix sum of nb counters, in place (one block)
-__global__ void __launch_bounds__(256) k_obs_scan(uint32_t* cnt, uint32_t nb) {
-  __shared__ uint32_t part[256];
-  const uint32_t t = threadIdx.x;
-  const uint32_t per = (nb + 255) / 256;
-  uint32_t sum = 0;
-  for (uint32_t k = t * per; k < nb && k < (t + 1) * per; ++k) sum += cnt[k];
-  part[t] = sum;
-  __syncthreads();
-  if (t == 0) {
-    uint32_t run = 0;
-    for (uint32_t k = 0; k < 256; ++k) {
-      const uint32_t v = part[k];
-      part[k] = run;
+template <bool kMulti>
+__global__ void __launch_bounds__(256) k_obs_scan(ObsArgs<kMulti> A) {
+  with_job(A, kObsStageScan, [&](const ObsJob& J, uint32_t blk, uint32_t grid) {
+    (void)blk;
+    (void)grid;
+    uint32_t* cnt = J.sc.cnt;
+    const uint32_t nb = J.r.cap + 1;
+    __shared__ uint32_t part[256];
+    const uint32_t t = threadIdx.x;
+    const uint32_t per = (nb + 255) / 256;
+    uint32_t sum = 0;
+    for (uint32_t k = t * per; k < nb && k < (t + 1) * per; ++k) sum += cnt[k];
+    part[t] = sum;
+    __syncthreads();
+    if (t == 0) {
+      uint32_t run = 0;
+      for (uint32_t k = 0; k < 256; ++k) {
+        const uint32_t v = part[k];
+        part[k] = run;
+        run += v;
+      }
+    }
+    __syncthreads();
+    uint32_t run = part[t];
+    for (uint32_t k = t * per; k < nb && k < (t + 1) * per; ++k) {
+      const uint32_t v = cnt[k];
+      cnt[k] = run;
       run += v;
     }
-  }
-  __syncthreads();
-  uint32_t run = part[t];
-  for (uint32_t k = t * per; k < nb && k < (t + 1) * per; ++k) {
-    const uint32_t v = cnt[k];
-    cnt[k] = run;
-    run += v;
-  }
+  });
 }
 
 // Each block (kObsSortPer events per thread, as k_obs_count) reserves one
 // range per parton count with a single global atomic and places its events
 // by their LDS rank inside the range.
-__global__ void __launch_bounds__(256) k_obs_scatter(Summary sm, uint32_t n, uint32_t cap, uint32_t* cnt,
-                                                     uint32_t* perm) {
-  __shared__ uint32_t lc[kMaxCount + 1];
-  const uint32_t nb = cap + 1;
-  for (uint32_t k = threadIdx.x; k < nb; k += blockDim.x) lc[k] = 0u;
-  __syncthreads();
-  const uint64_t e0 = (uint64_t)blockIdx.x * blockDim.x * kObsSortPer;
-  uint32_t bin[kObsSortPer], rank[kObsSortPer];
+template <bool kMulti>
+__global__ void __launch_bounds__(256) k_obs_scatter(ObsArgs<kMulti> A) {
+  with_job(A, kObsStageSort, [&](const ObsJob& J, uint32_t blk, uint32_t grid) {
+    (void)grid;
+    const Summary sm = J.sm;
+    const uint32_t n = J.n, cap = J.r.cap;
+    uint32_t *cnt = J.sc.cnt, *perm = J.sc.perm;
+    __shared__ uint32_t lc[kMaxCount + 1];
+    const uint32_t nb = cap + 1;
+    for (uint32_t k = threadIdx.x; k < nb; k += blockDim.x) lc[k] = 0u;
+    __syncthreads();
+    const uint64_t e0 = (uint64_t)blk * blockDim.x * kObsSortPer;
+    uint32_t bin[kObsSortPer], rank[kObsSortPer];
 #pragma unroll
-  for (uint32_t q = 0; q < kObsSortPer; ++q) {
-    const uint64_t e = e0 + (uint64_t)q * blockDim.x + threadIdx.x;
-    bin[q] = 0;
-    rank[q] = 0;
-    if (e < n) {
-      const uint32_t np = (uint32_t)sm.i[kSiN * sm.stride + e];
-      bin[q] = cap - (np < cap ? np : cap);
-      rank[q] = atomicAdd(&lc[bin[q]], 1u);
+    for (uint32_t q = 0; q < kObsSortPer; ++q) {
+      const uint64_t e = e0 + (uint64_t)q * blockDim.x + threadIdx.x;
+      bin[q] = 0;
+      rank[q] = 0;
+      if (e < n) {
+        const uint32_t np = (uint32_t)sm.i[kSiN * sm.stride + e];
+        bin[q] = cap - (np < cap ? np : cap);
+        rank[q] = atomicAdd(&lc[bin[q]], 1u);
+      }
     }
-  }
-  __syncthreads();
-  for (uint32_t k = threadIdx.x; k < nb; k += blockDim.x)
-    if (lc[k]) lc[k] = atomicAdd(&cnt[k], lc[k]);
-  __syncthreads();
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < nb; k += blockDim.x)
+      if (lc[k]) lc[k] = atomicAdd(&cnt[k], lc[k]);
+    __syncthreads();
 #pragma unroll
-  for (uint32_t q = 0; q < kObsSortPer; ++q) {
-    const uint64_t e = e0 + (uint64_t)q * blockDim.x + threadIdx.x;
-    if (e < n) perm[lc[bin[q]] + rank[q]] = (uint32_t)e;
-  }
+    for (uint32_t q = 0; q < kObsSortPer; ++q) {
+      const uint64_t e = e0 + (uint64_t)q * blockDim.x + threadIdx.x;
+      if (e < n) perm[lc[bin[q]] + rank[q]] = (uint32_t)e;
+    }
+  });
 }
 
 template <bool kMassive>
-__global__ void __launch_bounds__(256) k_obs(Records r, Summary sm, EventInputs in, Scratch sc, uint32_t n,
-                                             double* __restrict__ hist) {
+__device__ __forceinline__ void window_events(const Records& r, const Summary& sm, const EventInputs& in,
+                                              const Scratch& sc, uint32_t n, double* __restrict__ hist, uint32_t blk,
+                                              uint32_t grid) {
   __shared__ double lh[kHistDoubles];
   for (int a = threadIdx.x; a < kHistDoubles; a += blockDim.x) lh[a] = 0.0;
   const bool fixed = in.fixed_hist != 0;
@@ -261,8 +325,8 @@ __global__ void __launch_bounds__(256) k_obs(Records r, Summary sm, EventInputs 
   if (fixed) fxs = fix_scale(sc);
   const FixScale* fx = fixed ? &fxs : nullptr;
   __syncthreads();
-  const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const uint64_t step = (uint64_t)gridDim.x * blockDim.x;
+  const uint64_t t = (uint64_t)blk * blockDim.x + threadIdx.x;
+  const uint64_t step = (uint64_t)grid * blockDim.x;
   const uint32_t cap = r.cap;
   // After k_obs_scatter, cnt[b] is the end of bin b (bin = cap - parton
   // count), so cnt[cap - m] counts the events with at least m partons; they
@@ -275,7 +339,7 @@ __global__ void __launch_bounds__(256) k_obs(Records r, Summary sm, EventInputs 
   // nearly the same size and its loops stop at the wave's largest
   __shared__ uint16_t order[256];
   __shared__ uint32_t bin_n[kObsRegSlots + 2];  // events per parton count, then the others
-  for (uint64_t w0 = (uint64_t)blockIdx.x * 256; w0 < n; w0 += (uint64_t)gridDim.x * 256) {
+  for (uint64_t w0 = (uint64_t)blk * 256; w0 < n; w0 += (uint64_t)grid * 256) {
     const uint64_t e_own = w0 + threadIdx.x;
     const int np_own = e_own < n ? sm.i[kSiN * sm.stride + e_own] : kObsRegSlots + 1;
     const bool mine = np_own <= kObsRegSlots && (uint32_t)np_own < sc.threshold;  // else the lane groups
@@ -320,6 +384,19 @@ __global__ void __launch_bounds__(256) k_obs(Records r, Summary sm, EventInputs 
   }
   __syncthreads();
   hist_flush(lh, sc, fixed, threadIdx.x, blockDim.x, kHistCopies, hist);
+}
+
+template <bool kMassive>
+__global__ void __launch_bounds__(256) k_obs(Records r, Summary sm, EventInputs in, Scratch sc, uint32_t n,
+                                             double* __restrict__ hist) {
+  window_events<kMassive>(r, sm, in, sc, n, hist, blockIdx.x, gridDim.x);
+}
+
+template <bool kMassive>
+__global__ void __launch_bounds__(256) k_obs_jobs(ObsArgs<true> A) {
+  with_job(A, kObsStageWindow, [&](const ObsJob& J, uint32_t blk, uint32_t grid) {
+    window_events<kMassive>(J.r, J.sm, J.in, J.sc, J.n, J.hist, blk, grid);
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -599,15 +676,17 @@ __device__ __forceinline__ int group_observables(const Records& r, const EventIn
   return status;
 }
 
-// events with lo_n <= partons < hi_n; `slots` (at most G * MV) LDS parton
-// slots per group
+// Events of 9 to 31 partons (G = 16) or more (G = 64); `slots` (at most G *
+// MV) LDS parton slots per group
 // (four waves per SIMD: 128 registers, a few spilled; stress 10^6 events
 // 6.9 -> 6.0 ms against the three waves of the unconstrained build, LEP
 // unchanged; five waves, 43 spilled, 5.7 ms on stress but 3% slower on LEP)
 template <int G, int MV, bool kMassive>
-__global__ void __launch_bounds__(64, 4) k_obs_group(Records r, Summary sm, EventInputs in, const uint32_t* perm,
-                                                  const uint32_t* cnt, uint32_t cap, uint32_t lo_n, uint32_t hi_n,
-                                                  uint32_t slots, double* __restrict__ hist, Scratch sc) {
+__device__ __forceinline__ void group_events(const Records& r, const Summary& sm, const EventInputs& in,
+                                             const Scratch& sc, uint32_t slots, uint32_t blk, uint32_t grid) {
+  const uint32_t cap = r.cap;
+  const uint32_t lo_n = G == 16 ? kObsWaveThreshold : kObsGroup64, hi_n = G == 16 ? kObsGroup64 : cap + 1;
+  const uint32_t *perm = sc.perm, *cnt = sc.cnt;
   constexpr uint32_t kGroups = 64 / G;
   extern __shared__ double lds[];
   // this block's copy of the global histogram set (block b: copy b mod
@@ -615,7 +694,7 @@ __global__ void __launch_bounds__(64, 4) k_obs_group(Records r, Summary sm, Even
   // the fixed-point integer cells.  A group block holds a few events, so an
   // LDS set would cost more to clear and flush than it saves (k_obs, with
   // 256 events per block, keeps one)
-  const uint32_t c0 = (blockIdx.x % kHistCopies) * (uint32_t)kHistDoubles;
+  const uint32_t c0 = (blk % kHistCopies) * (uint32_t)kHistDoubles;
   const uint32_t lane = threadIdx.x % G, grp = threadIdx.x / G;
   const EventLds L(lds + (size_t)grp * 7 * slots, slots,
                    (uint16_t*)(lds + (size_t)kGroups * 7 * slots) + (size_t)grp * slots);
@@ -624,13 +703,13 @@ __global__ void __launch_bounds__(64, 4) k_obs_group(Records r, Summary sm, Even
   const uint32_t q_hi = lo_n <= cap ? cnt[cap - lo_n] : 0u;
   // the grid is sized for the worst case: blocks without an event of this
   // range leave at once (the whole block, before touching LDS)
-  if (q_lo + blockIdx.x * kGroups >= q_hi) return;
+  if (q_lo + blk * kGroups >= q_hi) return;
   const bool fixed = in.fixed_hist != 0;
   FixScale fxs{0, 0};
   if (fixed) fxs = fix_scale(sc);
   const FixScale* fx = fixed ? &fxs : nullptr;
   __syncthreads();
-  for (uint32_t q = q_lo + blockIdx.x * kGroups + grp; q < q_hi; q += gridDim.x * kGroups) {
+  for (uint32_t q = q_lo + blk * kGroups + grp; q < q_hi; q += grid * kGroups) {
     const uint64_t e = perm[q];
     const int np = sm.i[kSiN * sm.stride + e];
     const double ecm = in.ecm_of(e);
@@ -647,6 +726,19 @@ __global__ void __launch_bounds__(64, 4) k_obs_group(Records r, Summary sm, Even
       if (h % G == lane) sm.d[(kSdY23 + h) * sm.stride + e] = v[h];
     if (lane == 0) sm.i[kSiStatus * sm.stride + e] = status;
   }
+}
+
+template <int G, int MV, bool kMassive>
+__global__ void __launch_bounds__(64, 4) k_obs_group(Records r, Summary sm, EventInputs in, Scratch sc,
+                                                     uint32_t slots) {
+  group_events<G, MV, kMassive>(r, sm, in, sc, slots, blockIdx.x, gridDim.x);
+}
+
+template <int G, int MV, bool kMassive>
+__global__ void __launch_bounds__(64, 4) k_obs_group_jobs(ObsArgs<true> A, uint32_t slots) {
+  with_job(A, kObsStageGroup, [&](const ObsJob& J, uint32_t blk, uint32_t grid) {
+    group_events<G, MV, kMassive>(J.r, J.sm, J.in, J.sc, slots, blk, grid);
+  });
 }
 
 // Observables v of an event of at most kObsRegSlots partons by one wave: the
@@ -869,12 +961,6 @@ __global__ void __launch_bounds__(256, 4) k_obs_few(Records r, Summary sm, Event
 
 static inline uint32_t blocks_for(uint64_t n, uint32_t b) { return (uint32_t)((n + b - 1) / b); }
 
-// one launch of the group observables kernel: function, parton-count range
-// [lo, hi), LDS parton slots per group, dynamic LDS bytes
-struct ObsGroupLaunch {
-  const void* fn;
-  uint32_t lo, hi, slots, lds;
-};
 // the one-wave-per-event launch of small requests
 struct ObsFewLaunch {
   uint32_t blocks, threads, slots, lds, copies;
@@ -882,26 +968,6 @@ struct ObsFewLaunch {
 
 static size_t obs_group_lds(uint32_t g, uint32_t slots) {
   return (size_t)(64 / g) * slots * (7 * 8 + 2) + 64;
-}
-
-// The group launches for records of capacity cap: 16 lanes from
-// kObsWaveThreshold to 31 partons, 64 lanes from 32 (smaller events go to
-// k_obs).
-static uint32_t obs_group_launches(uint32_t cap, bool massive, ObsGroupLaunch out[3]) {
-  uint32_t k = 0;
-  if (cap > kObsWaveMaxCap || kObsWaveThreshold > cap) return 0;
-  const uint32_t t = kObsWaveThreshold;
-  {  // 16 lanes up to 31 partons
-    const uint32_t slots = std::min<uint32_t>(31, cap);
-    const void* fn = massive ? (const void*)k_obs_group<16, 2, true> : (const void*)k_obs_group<16, 2, false>;
-    out[k++] = ObsGroupLaunch{fn, std::max<uint32_t>(t, 9), kObsGroup64, slots, (uint32_t)obs_group_lds(16, slots)};
-  }
-  if (cap >= kObsGroup64) {  // a wave from 32
-    const void* fn = massive ? (const void*)k_obs_group<64, kObsWaveMaxCap / 64, true>
-                             : (const void*)k_obs_group<64, kObsWaveMaxCap / 64, false>;
-    out[k++] = ObsGroupLaunch{fn, std::max<uint32_t>(t, kObsGroup64), cap + 1, cap, (uint32_t)obs_group_lds(64, cap)};
-  }
-  return k;
 }
 
 // One wave per event up to kObsFew events (kObsFewBig with records above 128
@@ -928,8 +994,6 @@ static uint32_t obs_wmax_blocks(uint64_t n) { return (uint32_t)std::min<uint64_t
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-static uint32_t obs_sort_blocks(uint64_t n) { return blocks_for(n, 256u * kObsSortPer); }
-
 void launch_me(const Records& r, const Summary& s, const EventInputs& in, uint32_t n,
                hipStream_t st, double* zero_hist) {
   if (!n) return;
@@ -978,6 +1042,25 @@ uint64_t obs_scratch_bytes(uint64_t n, uint32_t cap) {
          2 * al256(kHistCopies * kHistDoubles * 8) + al256(8) + 256;
 }
 
+// the part of the scratch that every request's pass needs
+static void carve_lists(Scratch& s, char*& p, uint64_t n, uint32_t cap) {
+  auto take = [&](uint64_t bytes) {
+    char* q = p;
+    p += al256(bytes);
+    return q;
+  };
+  s.perm = (uint32_t*)take(n * 4);
+  s.cnt = (uint32_t*)take((cap + 2) * 4);
+  s.hcopy = (double*)take(kHistCopies * kHistDoubles * 8);
+  s.ihist = (unsigned long long*)take(kHistCopies * kHistDoubles * 8);
+  s.wmax = (unsigned long long*)take(8);
+  s.lbits = 0;
+  while ((1ull << s.lbits) < n) ++s.lbits;
+  // events with at least `threshold` partons go to lane groups (LDS holds up
+  // to kObsWaveMaxCap partons); smaller ones to one thread each
+  s.threshold = cap <= kObsWaveMaxCap ? kObsWaveThreshold : 0xFFFFFFFFu;
+}
+
 Scratch carve_obs_scratch(char*& p, uint64_t n, uint32_t cap) {
   Scratch s;
   s.stride = obs_threads(n, cap);
@@ -997,62 +1080,104 @@ Scratch carve_obs_scratch(char*& p, uint64_t n, uint32_t cap) {
   s.dn = (double*)take(m * 8);
   s.nn = (uint16_t*)take(m * 2);
   s.dead = (uint8_t*)take(m);
-  s.perm = (uint32_t*)take(n * 4);
-  s.cnt = (uint32_t*)take((cap + 2) * 4);
-  s.hcopy = (double*)take(kHistCopies * kHistDoubles * 8);
-  s.ihist = (unsigned long long*)take(kHistCopies * kHistDoubles * 8);
-  s.wmax = (unsigned long long*)take(8);
-  s.lbits = 0;
-  while ((1ull << s.lbits) < n) ++s.lbits;
-  // events with at least `threshold` partons go to one wave each (LDS holds
-  // up to kObsWaveMaxCap partons); smaller ones to one thread each
-  s.threshold = cap <= kObsWaveMaxCap ? kObsWaveThreshold : 0xFFFFFFFFu;
+  carve_lists(s, p, n, cap);
   return s;
+}
+
+// The pass over one job or a table of jobs, `blocks` in each stage in all;
+// records of at most `cap` partons.
+template <bool kMulti>
+static void launch_general(const ObsArgs<kMulti>& A, const uint32_t* blocks, uint32_t cap, bool massive,
+                           hipStream_t st) {
+  const dim3 b256(256), b64(64);
+  hipLaunchKernelGGL(k_obs_reset<kMulti>, dim3(blocks[kObsStageHist]), b256, 0, st, A);
+  hipLaunchKernelGGL(k_obs_count<kMulti>, dim3(blocks[kObsStageSort]), b256, 0, st, A);
+  hipLaunchKernelGGL(k_obs_scan<kMulti>, dim3(blocks[kObsStageScan]), b256, 0, st, A);
+  hipLaunchKernelGGL(k_obs_scatter<kMulti>, dim3(blocks[kObsStageSort]), b256, 0, st, A);
+  if constexpr (kMulti) {
+    hipLaunchKernelGGL(massive ? k_obs_jobs<true> : k_obs_jobs<false>, dim3(blocks[kObsStageWindow]), b256, 0, st, A);
+  } else {
+    const ObsJob& j = A.job;
+    hipLaunchKernelGGL(massive ? k_obs<true> : k_obs<false>, dim3(blocks[kObsStageWindow]), b256, 0, st, j.r, j.sm, j.in,
+                       j.sc, j.n, j.hist);
+  }
+  if (cap <= kObsWaveMaxCap && cap >= kObsWaveThreshold) {
+    const uint32_t slots = std::min<uint32_t>(kObsGroup64 - 1, cap);
+    const dim3 gb(blocks[kObsStageGroup]);
+    constexpr int kMv = kObsWaveMaxCap / 64;
+    if constexpr (kMulti) {
+      const auto g16 = massive ? k_obs_group_jobs<16, 2, true> : k_obs_group_jobs<16, 2, false>;
+      const auto g64 = massive ? k_obs_group_jobs<64, kMv, true> : k_obs_group_jobs<64, kMv, false>;
+      hipLaunchKernelGGL(g16, gb, b64, obs_group_lds(16, slots), st, A, slots);
+      if (cap >= kObsGroup64) hipLaunchKernelGGL(g64, gb, b64, obs_group_lds(64, cap), st, A, cap);
+    } else {
+      const ObsJob& j = A.job;
+      const auto g16 = massive ? k_obs_group<16, 2, true> : k_obs_group<16, 2, false>;
+      const auto g64 = massive ? k_obs_group<64, kMv, true> : k_obs_group<64, kMv, false>;
+      hipLaunchKernelGGL(g16, gb, b64, obs_group_lds(16, slots), st, j.r, j.sm, j.in, j.sc, slots);
+      if (cap >= kObsGroup64) hipLaunchKernelGGL(g64, gb, b64, obs_group_lds(64, cap), st, j.r, j.sm, j.in, j.sc, cap);
+    }
+  }
+  hipLaunchKernelGGL(k_hist_finalize<kMulti>, dim3(blocks[kObsStageSum]), b256, 0, st, A);
+}
+
+static void job_blocks(const ObsJob& j, uint32_t most_groups, uint32_t* blocks) {
+  blocks[kObsStageHist] = blocks_for(std::max<uint32_t>(j.r.cap + 1, kHistCopies * kHistDoubles), 256);
+  blocks[kObsStageSort] = blocks_for(j.n, 256u * kObsSortPer);
+  blocks[kObsStageScan] = 1;
+  blocks[kObsStageWindow] = (uint32_t)(std::min<uint64_t>(j.sc.stride, ((uint64_t)j.n + 255) / 256 * 256) / 256);
+  blocks[kObsStageGroup] = std::min<uint32_t>(j.n, most_groups);
+  blocks[kObsStageSum] = kHistBlocks;
 }
 
 void launch_obs(const Records& r, const Summary& s, const EventInputs& in, const Scratch& sc,
                 uint32_t n, double* hist, hipStream_t st) {
   if (!n) return;
-  const uint32_t nb = r.cap + 1;
-  const bool fixed = in.fixed_hist != 0;
-  unsigned long long* ih = fixed ? sc.ihist : nullptr;
-  unsigned long long* wm = fixed ? sc.wmax : nullptr;
-  const dim3 reset(obs_reset_blocks(nb)), b256(256);
+  const bool fixed = in.fixed_hist != 0, massive = in.massive != 0;
+  const ObsArgs<false> A{ObsJob{r, s, in, sc, hist, n, {}}};
+  uint32_t blocks[kObsStages];
+  job_blocks(A.job, kObsWaveBlocks, blocks);
   ObsFewLaunch few;
   if (obs_few_launch(n, r.cap, fixed, &few)) {
-    if (few.copies) hipLaunchKernelGGL(k_obs_reset, reset, b256, 0, st, sc.cnt, nb, sc.hcopy, ih, wm);
-    if (fixed) hipLaunchKernelGGL(k_obs_wmax, dim3(obs_wmax_blocks(n)), b256, 0, st, s, n, wm);
-    if (in.massive) hipLaunchKernelGGL(k_obs_few<true>, dim3(few.blocks), dim3(few.threads), few.lds, st, r, s, in, sc, n,
-                                       few.slots, few.copies, hist);
-    else hipLaunchKernelGGL(k_obs_few<false>, dim3(few.blocks), dim3(few.threads), few.lds, st, r, s, in, sc, n, few.slots,
-                            few.copies, hist);
-    if (few.copies) hipLaunchKernelGGL(k_hist_finalize, dim3(kHistBlocks), b256, 0, st, sc, hist, fixed ? 1u : 0u);
+    const dim3 b256(256);
+    if (few.copies) hipLaunchKernelGGL(k_obs_reset<false>, dim3(blocks[kObsStageHist]), b256, 0, st, A);
+    if (fixed) hipLaunchKernelGGL(k_obs_wmax, dim3(obs_wmax_blocks(n)), b256, 0, st, s, n, sc.wmax);
+    hipLaunchKernelGGL(massive ? k_obs_few<true> : k_obs_few<false>, dim3(few.blocks), dim3(few.threads), few.lds, st,
+                       r, s, in, sc, n, few.slots, few.copies, hist);
+    if (few.copies) hipLaunchKernelGGL(k_hist_finalize<false>, dim3(kHistBlocks), b256, 0, st, A);
     return;
   }
-  hipLaunchKernelGGL(k_obs_reset, reset, b256, 0, st, sc.cnt, nb, sc.hcopy, ih, wm);
-  hipLaunchKernelGGL(k_obs_count, dim3(obs_sort_blocks(n)), dim3(256), 0, st, s, n, r.cap, sc.cnt, wm);
-  hipLaunchKernelGGL(k_obs_scan, dim3(1), dim3(256), 0, st, sc.cnt, nb);
-  hipLaunchKernelGGL(k_obs_scatter, dim3(obs_sort_blocks(n)), dim3(256), 0, st, s, n, r.cap, sc.cnt, sc.perm);
-  const uint32_t blocks = (uint32_t)(std::min<uint64_t>(sc.stride, ((uint64_t)n + 255) / 256 * 256) / 256);
-  if (in.massive) hipLaunchKernelGGL(k_obs<true>, dim3(blocks), dim3(256), 0, st, r, s, in, sc, n, hist);
-  else hipLaunchKernelGGL(k_obs<false>, dim3(blocks), dim3(256), 0, st, r, s, in, sc, n, hist);
-  ObsGroupLaunch gl[3];
-  const uint32_t ng = obs_group_launches(r.cap, in.massive != 0, gl);
-  for (uint32_t k = 0; k < ng; ++k) {
-    const uint32_t wb = (uint32_t)std::min<uint64_t>(n, kObsWaveBlocks);
-    const uint32_t* perm = sc.perm;
-    const uint32_t* cnt = sc.cnt;
-    uint32_t cap = r.cap, lo = gl[k].lo, hi = gl[k].hi, slots = gl[k].slots;
-    Records rr = r;
-    Summary ss = s;
-    EventInputs ii = in;
-    double* hh = hist;
-    Scratch sc2 = sc;
-    void* args[] = {&rr, &ss, &ii, &perm, &cnt, &cap, &lo, &hi, &slots, &hh, &sc2};
-    (void)hipLaunchKernel(gl[k].fn, dim3(wb), dim3(64), args, gl[k].lds, st);
-  }
-  hipLaunchKernelGGL(k_hist_finalize, dim3(kHistBlocks), b256, 0, st, sc, hist, fixed ? 1u : 0u);
+  launch_general(A, blocks, r.cap, massive, st);
 }
 
+uint64_t obs_job_bytes(uint64_t n, uint32_t cap) {
+  return al256(n * 4) + al256((cap + 2) * 4) + 2 * al256(kHistCopies * kHistDoubles * 8) + al256(8);
+}
+
+Scratch carve_obs_job(char*& p, uint64_t n, uint32_t cap) {
+  Scratch s{};
+  s.stride = (n + 255) / 256 * 256;
+  carve_lists(s, p, n, cap);
+  return s;
+}
+
+void plan_obs_jobs(ObsJob* jobs, uint32_t count, ObsPlan* plan) {
+  *plan = ObsPlan{};
+  for (uint32_t q = 0; q < count; ++q) {
+    uint32_t blocks[kObsStages];
+    job_blocks(jobs[q], kObsJobGroupBlocks, blocks);
+    for (int k = 0; k < kObsStages; ++k) {
+      jobs[q].at[k] = plan->blocks[k];
+      plan->blocks[k] += blocks[k];
+    }
+    plan->cap = std::max(plan->cap, jobs[q].r.cap);
+    plan->massive |= jobs[q].in.massive != 0;
+  }
+  plan->count = count;
+}
+
+void launch_obs_jobs(const ObsJob* jobs_dev, const ObsPlan& plan, hipStream_t st) {
+  launch_general(ObsArgs<true>{jobs_dev, plan.count}, plan.blocks, plan.cap, plan.massive, st);
+}
 
 }  // namespace vsh

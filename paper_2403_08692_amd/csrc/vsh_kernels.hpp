@@ -113,6 +113,24 @@ struct Scratch {
   uint32_t lbits;
 };
 
+// One request's observables as the kernels of the pass take it, and where its
+// blocks begin in the launches that serve several requests at once.
+enum { kObsStageHist, kObsStageSort, kObsStageScan, kObsStageWindow, kObsStageGroup, kObsStageSum, kObsStages };
+struct ObsJob {
+  Records r;
+  Summary sm;
+  EventInputs in;
+  Scratch sc;
+  double* hist;
+  uint32_t n;
+  uint32_t at[kObsStages];
+};
+struct ObsPlan {
+  uint32_t blocks[kObsStages] = {};
+  uint32_t count = 0, cap = 0;
+  bool massive = false;  // any of the jobs
+};
+
 constexpr uint32_t kObsWaveThreshold = 9;
 constexpr int kObsRegSlots = 8;  // events of at most this many partons: observables in registers
 constexpr uint32_t kObsWaveMaxCap = 512;
@@ -127,6 +145,7 @@ constexpr uint32_t kObsFewBlocks = 2048;
 // one or a few rounds of resident blocks (stress, 10^6 events: 8192 blocks
 // 7.3 ms, 32768 blocks 6.9 ms; empty blocks leave at once)
 constexpr uint32_t kObsWaveBlocks = 32768;
+constexpr uint32_t kObsJobGroupBlocks = 4096;  // the same for each of several requests in one launch
 
 }  // namespace vsh
 
@@ -143,6 +162,12 @@ void launch_shower_plain(const Records& r, const Summary& s, const EventInputs& 
                          uint32_t block, uint32_t waves, hipStream_t st);
 void launch_obs(const Records& r, const Summary& s, const EventInputs& in, const Scratch& sc,
                 uint32_t n, double* hist, hipStream_t st);
+// the pass over several requests (records of at most kObsWaveMaxCap partons,
+// each with a scratch of its own from carve_obs_job) in one set of launches
+uint64_t obs_job_bytes(uint64_t n, uint32_t cap);
+Scratch carve_obs_job(char*& p, uint64_t n, uint32_t cap);
+void plan_obs_jobs(ObsJob* jobs, uint32_t count, ObsPlan* plan);
+void launch_obs_jobs(const ObsJob* jobs_dev, const ObsPlan& plan, hipStream_t st);
 void launch_load_records(const Records& r, const Summary& s, const CsrStarts& in, uint32_t n, double* ecm,
                          unsigned long long* bad, double* zero_hist, hipStream_t st);
 }  // namespace vsh

@@ -146,6 +146,7 @@ struct Epoch {
   std::vector<uint64_t> finishing;   // tickets whose observables and copy it runs
   ReqDev* reqs_host = nullptr;       // pinned
   Segment* segs_host = nullptr;      // pinned
+  ObsJob* jobs_host = nullptr;       // pinned
   char* dev = nullptr;               // descriptors, counter, slots, end cache
   uint64_t dev_bytes = 0;
   char* scratch = nullptr;           // observables scratch of its drains
@@ -237,7 +238,7 @@ static bool admit(vsh_ctx* ctx, ServeState& S) {
 // Grown on demand; *cached tells whether the cache is there.
 static bool ensure_epoch_memory(vsh_ctx* ctx, Epoch& E, uint64_t lanes, uint32_t cap, bool massive, bool* cached) {
   const uint64_t base = align_up(kMaxEpochReqs * sizeof(ReqDev), 256) + align_up(kMaxEpochReqs * sizeof(Segment), 256) +
-                        256 + slots_bytes(lanes, cap);
+                        align_up(kMaxEpochReqs * sizeof(ObsJob), 256) + 256 + slots_bytes(lanes, cap);
   const uint64_t with_cache = base + align_up(lanes * cap * cache_words(massive) * 8, 256);
   *cached = true;
   if (with_cache <= E.dev_bytes) return true;
@@ -392,6 +393,7 @@ static bool launch_epoch(vsh_ctx* ctx, ServeState& S) {
   Carver c(E->dev);
   ReqDev* rd = (ReqDev*)c.take(kMaxEpochReqs * sizeof(ReqDev));
   Segment* sd = (Segment*)c.take(kMaxEpochReqs * sizeof(Segment));
+  ObsJob* jd = (ObsJob*)c.take(kMaxEpochReqs * sizeof(ObsJob));
   unsigned long long* counter = (unsigned long long*)c.take(256);
   Records slots = carve_slots(c, lanes, cap);
   const EndCache cache{cached ? (uint64_t*)c.take(lanes * cap * cache_words(massive) * 8) : nullptr, cap};
@@ -452,12 +454,29 @@ static bool launch_epoch(vsh_ctx* ctx, ServeState& S) {
     wait_other |= O.busy && r.seg_gen[1 - ei] == O.gen;
   }
   if (wait_other) err = hipStreamWaitEvent(E->stream, O.shower_done, 0);
-  uint64_t scratch_need = 0;
+  // Several requests of more than kObsFew events together go through one set
+  // of launches, each with a scratch of its own: one after the other, each of
+  // a burst's requests took its 60 to 200 us of mostly idle chip (15 requests
+  // of 350000 events: 2.8 ms).
+  uint64_t together_events = 0, together_bytes = 0, scratch_need = 0;
+  uint32_t n_together = 0;
+  auto joins = [](const ServeReq& r) { return r.req.max_partons <= kObsWaveMaxCap; };
   for (uint64_t t : E->finishing) {
     const ServeReq& r = *S.reqs[t];
-    scratch_need = std::max(scratch_need, obs_scratch_bytes(r.req.n_events, r.req.max_partons));
+    if (!joins(r)) continue;
+    ++n_together;
+    together_events += r.req.n_events;
+    together_bytes += obs_job_bytes(r.req.n_events, r.req.max_partons);
+  }
+  const bool together = n_together >= 2 && together_events > kObsFew;
+  if (together) scratch_need = together_bytes;
+  for (uint64_t t : E->finishing) {
+    const ServeReq& r = *S.reqs[t];
+    if (!together || !joins(r))
+      scratch_need = std::max(scratch_need, obs_scratch_bytes(r.req.n_events, r.req.max_partons));
   }
   if (err == hipSuccess && scratch_need > E->scratch_bytes) {
+    scratch_need = std::max<uint64_t>(scratch_need, 64u << 20);  // grown seldom: the free waits for the device
     if (E->scratch) (void)hipFree(E->scratch);  // this stream's earlier work has completed
     E->scratch = nullptr;
     E->scratch_bytes = 0;
@@ -465,16 +484,35 @@ static bool launch_epoch(vsh_ctx* ctx, ServeState& S) {
     if (err == hipSuccess) E->scratch_bytes = scratch_need;
     else E->scratch = nullptr;
   }
+  if (together && err == hipSuccess) {
+    char* at = E->scratch;
+    uint32_t q = 0;
+    for (uint64_t t : E->finishing) {
+      const ServeReq& r = *S.reqs[t];
+      if (!joins(r)) continue;
+      const Scratch sc = carve_obs_job(at, r.req.n_events, r.req.max_partons);
+      E->jobs_host[q++] = ObsJob{r.buf.out, r.buf.sum, request_inputs(r), sc, r.buf.hist, (uint32_t)r.req.n_events, {}};
+    }
+    ObsPlan plan;
+    plan_obs_jobs(E->jobs_host, q, &plan);
+    err = hipMemcpyAsync(jd, E->jobs_host, q * sizeof(ObsJob), hipMemcpyHostToDevice, E->stream);
+    if (err == hipSuccess) {
+      launch_obs_jobs(jd, plan, E->stream);
+      err = hipGetLastError();
+    }
+  }
   for (uint64_t t : E->finishing) {
     ServeReq& r = *S.reqs[t];
     if (err != hipSuccess) break;
     uint64_t bytes = 0;
     err = reserve_staging(S, r, &bytes);
     if (err != hipSuccess) break;
-    Carver sc_c(E->scratch);
-    const Scratch sc = carve_scratch(sc_c, r.req.n_events, r.req.max_partons);
-    launch_obs(r.buf.out, r.buf.sum, request_inputs(r), sc, (uint32_t)r.req.n_events, r.buf.hist, E->stream);
-    err = hipGetLastError();
+    if (!together || !joins(r)) {  // the scratch is free again when these run
+      Carver sc_c(E->scratch);
+      const Scratch sc = carve_scratch(sc_c, r.req.n_events, r.req.max_partons);
+      launch_obs(r.buf.out, r.buf.sum, request_inputs(r), sc, (uint32_t)r.req.n_events, r.buf.hist, E->stream);
+      err = hipGetLastError();
+    }
     if (err == hipSuccess) err = hipMemcpyAsync(r.h_hist, r.buf.hist, bytes, hipMemcpyDeviceToHost, E->stream);
   }
   if (err == hipSuccess) err = hipEventRecord(E->done, E->stream);
@@ -569,6 +607,7 @@ static vsh_status serve_start(vsh_ctx* ctx) {
     if (err == hipSuccess) err = hipEventCreateWithFlags(&E.done, hipEventDisableTiming);
     if (err == hipSuccess) err = hipHostMalloc((void**)&E.reqs_host, kMaxEpochReqs * sizeof(ReqDev), 0);
     if (err == hipSuccess) err = hipHostMalloc((void**)&E.segs_host, kMaxEpochReqs * sizeof(Segment), 0);
+    if (err == hipSuccess) err = hipHostMalloc((void**)&E.jobs_host, kMaxEpochReqs * sizeof(ObsJob), 0);
     if (err != hipSuccess) return hip_fail(ctx, err, "serving setup");
   }
   ctx->serve = S.release();
@@ -598,6 +637,7 @@ void serve_shutdown(vsh_ctx* ctx) {
     if (E.scratch) (void)hipFree(E.scratch);
     if (E.reqs_host) (void)hipHostFree(E.reqs_host);
     if (E.segs_host) (void)hipHostFree(E.segs_host);
+    if (E.jobs_host) (void)hipHostFree(E.jobs_host);
     for (hipEvent_t ev : {E.me_done, E.shower_done, E.done})
       if (ev) (void)hipEventDestroy(ev);
     if (E.stream) (void)hipStreamDestroy(E.stream);
