@@ -146,23 +146,26 @@ __global__ void __launch_bounds__(256) k_shower_persistent(PersistArgs A) {
 // wave's 64 events are spread over its 64 lanes: the work items are the
 // partons of all busy events, taken 64 per round; item (owner o, parton i)
 // runs that parton's dipole ends.  A gluon item (two ends, three Philox
-// blocks and two logs per end) costs about four quark items (one end, one
-// block, one log), so gluon and quark partons get rounds of their own: first
+// blocks and two trials per end) costs about four quark items (one end, one
+// block, one trial), so gluon and quark partons get rounds of their own: first
 // the gluons of every event (event-major), padded to a whole round, then the
 // quarks.  Each event keeps a bit mask of its gluon slots in LDS, so item r of
-// an owner is its r-th set (or clear) bit.  Within a round a segmented max
-// over consecutive lanes of the same owner leaves the owner's round best on
-// its last lane, which folds it into the owner's running best in LDS.  Both
-// compare (larger ln t, then smaller packed (i, k, K)): the paper's loop
-// order keeps the first of equal trials, and this rule picks that one in
-// whatever order the items come.  Each owner then decides its own cycle.
+// an owner is its r-th set (or clear) bit.  Trials are ranked by their
+// single-precision bounds (trial_bound): an item's lowest bound, with its
+// (i, k, K) below it in one 64-bit key, goes into its owner's minimum in LDS by
+// an atomic, what it displaces into the runner-up's.  Each owner then computes
+// the exact scale of its winner and decides its own cycle; where the runner-up
+// is not proven to lose, its lane compares all the cycle's trials exactly in
+// the paper's loop order (the first of equal trials wins).  Against exact
+// logarithms for every trial and a segmented maximum by shuffles, 10^6 events:
+// plain LEP showers 3.04 -> 2.63 ms, t_C = 0.25 GeV^2 at 500 GeV 27.8 -> 20.6.
 // ---------------------------------------------------------------------------
 // Launch-wide constants of the kernels whose events all belong to one
 // request: each event's key is make_keyed(seed, first + its record column)
 // and the cycle limit is one, so neither is kept per event in LDS (kOne),
 // and, for four waves per SIMD (kFour, records of at most 128 partons), the
 // item list (whose free tail holds the stale partons) is shorter (its
-// overflow takes the offsets' path): 9.2 KB + 1 KB of masks, sixteen blocks
+// overflow takes the offsets' path): 8.7 KB + 1 KB of masks, sixteen blocks
 // per CU at 64 partons, fourteen at 128.  With
 // 256-parton records the layout leaves room for one more block per CU.
 struct OneRequest {
@@ -172,7 +175,7 @@ struct OneRequest {
 constexpr uint32_t kOneAboveCap = 64;  // massive plain kernel: the per-event layout up to here
 constexpr uint32_t kFourMaxCap = 128;  // massless: four-wave builds up to here (LDS-bound above)
 
-template <bool kOne_, bool kFour_ = false, bool kRegW_ = false>
+template <bool kMassive_, bool kOne_, bool kFour_ = false, bool kRegW_ = false>
 struct FlatShared {
   static constexpr bool kOne = kOne_, kFour = kFour_, kRegW = kRegW_;
   double lt[64], tcut[64], ltc[64], cfac[64];
@@ -185,18 +188,17 @@ struct FlatShared {
   // once per dipole end, when rounds allow), then quark items, then the
   // stale partons in what the items leave free (two spare entries)
   uint16_t item[1024 + (kFour || kRegW ? 100 : 384) + 4];
-  double best_v[64];
-  uint32_t best_idx[64];  // packed (i, k, K) << 6 | the lane whose item made it
-  double best_c[2][64];   // per owner: those of its running best
+  // per (event, cycle) pair: its trials' lowest bound << 32 | packed (i, k, K),
+  // and the lowest bound of the others
+  uint64_t best[64];
+  uint32_t second[64];
+  // per pair: the lowest one's uniform and coefficients (unless kRedraw); later, of
+  // cycles evaluated ahead, ln t, t, z (and, in best, the weight)
+  double pair[3][64];
   uint32_t counts[64];  // the cycle's trials (low 16 bits) and active ends (high 16 bits) per owner
   uint32_t climit[kOne ? 1 : 64];  // each event's cycle limit
   double wsh[kRegW ? 1 : 64];  // each event's shower weight (weighted veto), unless held in a register
-  union {
-    double coef[2][64];     // massless: per item lane, its best end's 1/ca, 1/cb
-    struct {
-      double mc[64], mb[64];  // massive: each event's charm and bottom masses
-    };
-  };
+  double mc[kMassive_ ? 64 : 1], mb[kMassive_ ? 64 : 1];  // each event's charm and bottom masses
 };
 
 // per-owner gluon masks, then per-owner stale masks (partons whose cached end
@@ -336,101 +338,128 @@ __device__ __forceinline__ void entry_build_massive(double cfac, double tcut, co
   for (int q = 0; q < kMCacheWords; ++q) ent[q] = w[q];
 }
 
-// Trials of parton i of an event with quark masses from its fresh cache
-// entry (the stale rounds rebuilt it): the draws and counts of
-// parton_trials_massive; only the item's best (i, k, K) is kept.
-__device__ __forceinline__ void parton_trials_mcached(const TrialCtx& c, uint64_t col, int i, const EndCache& ec,
-                                                      double& best, uint32_t& widx, uint32_t& trials,
-                                                      uint32_t& ends) {
-  const uint64_t* ent = ec.rec + ((col * ec.cap) + (uint64_t)i) * kMCacheWords;
-  uint64_t w[kMCacheWords];
-#pragma unroll
-  for (int q = 0; q < kMCacheWords; ++q) w[q] = ent[q];
-  const int pid_i = (int)(int8_t)(uint8_t)(w[0] & 0xFFu);
-  const int ks[2] = {(int)((w[0] >> 8) & 0xFFFFu), (int)((w[0] >> 24) & 0xFFFFu)};
-#pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    if (ks[e] == kNoPartner) continue;
-    double cc[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) cc[q] = __longlong_as_double((long long)w[1 + 4 * e + q]);
-    const int K = end_draws_massive(c, i, ks[e], pid_i, cc, best, trials, ends);
-    if (K >= 0) widx = pack_trial(i, ks[e], K);
-  }
-}
-
 // An item's end-cache entry, when loaded ahead of its round.
 struct Ent5 {
   uint64_t w[kCacheWords];
 };
 
-// Trials of one item of a massless event: ends e_lo .. e_hi of parton i (a
-// gluon's item takes one or both of its ends; a quark's both, the second
-// empty as a quark has one colour partner), from the parton's fresh cache
-// entry (cached; the stale rounds rebuilt it) or from the records.  The
-// winning end's reciprocal coefficients come back in (wia, wib).
-__device__ __forceinline__ void item_trials(const TrialCtx& c, const Records& r, uint64_t slot, int i, int e_lo,
-                                            int e_hi, const EndCache& ec, uint64_t col, bool cached, bool pre,
-                                            const Ent5& pw, double& best, uint32_t& widx, double& wia, double& wib,
-                                            uint32_t& trials, uint32_t& ends) {
-  uint64_t w[kCacheWords];
-  int pid_i, k1, k2;
-  P4 pi{0.0, 0.0, 0.0, 0.0};
-  if (cached) {  // the entry as loaded ahead (pre), or from the cache now
-    const uint64_t* ent = ec.rec + ((col * ec.cap) + (uint64_t)i) * kCacheWords;
+// A parton's id, its spectators in ascending order and its ends' trial
+// coefficients: (1/ca, 1/cb), or with quark masses the four of
+// massive_end_coeffs; 0 for no phase space above the cutoff.
+template <bool kMassive>
+struct Ends {
+  static constexpr int kC = kMassive ? 4 : 2;
+  int pid, k[2];
+  double c[2][kC];
+};
+
+// Those of ends e_lo .. e_hi of parton i: from its fresh cache entry
+// (kCached; the stale rounds rebuilt it; already loaded if pre) or from the
+// records.
+template <bool kCached, bool kMassive>
+__device__ __forceinline__ Ends<kMassive> load_ends(const TrialCtx& c, const Records& r, uint64_t slot, int i, int e_lo,
+                                                    int e_hi, const EndCache& ec, uint64_t col, bool pre,
+                                                    const Ent5& pw, const QuarkMasses& qm) {
+  constexpr int kC = Ends<kMassive>::kC;
+  Ends<kMassive> E;
+  if constexpr (kCached) {
+    constexpr int kW = kMassive ? kMCacheWords : kCacheWords;
+    static_assert(kW == 1 + 2 * kC);
+    const uint64_t* ent = ec.rec + ((col * ec.cap) + (uint64_t)i) * kW;
+    uint64_t w[kW];
 #pragma unroll
-    for (int q = 0; q < kCacheWords; ++q) w[q] = pre ? pw.w[q] : ent[q];
-    pid_i = (int)(int8_t)(uint8_t)(w[0] & 0xFFu);
-    k1 = (int)((w[0] >> 8) & 0xFFFFu);
-    k2 = (int)((w[0] >> 24) & 0xFFFFu);
+    for (int q = 0; q < kW; ++q) {
+      if constexpr (kMassive) w[q] = ent[q];
+      else w[q] = pre ? pw.w[q] : ent[q];
+    }
+    E.pid = (int)(int8_t)(uint8_t)(w[0] & 0xFFu);
+    E.k[0] = (int)((w[0] >> 8) & 0xFFFFu);
+    E.k[1] = (int)((w[0] >> 24) & 0xFFFFu);
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int q = 0; q < kC; ++q) E.c[e][q] = __longlong_as_double((long long)w[1 + kC * e + q]);
   } else {
     const uint64_t oi = (uint64_t)i * r.stride + slot;
-    pid_i = r.pid[oi];
-    k1 = r.cpart[oi];
-    k2 = r.apart[oi];
+    E.pid = r.pid[oi];
+    int k1 = r.cpart[oi], k2 = r.apart[oi];
     if (k2 == k1) k2 = kNoPartner;
-    if (k1 > k2) {
-      const int t = k1;
-      k1 = k2;
-      k2 = t;
+    E.k[0] = k1 < k2 ? k1 : k2;
+    E.k[1] = k1 < k2 ? k2 : k1;
+    const P4 pi = r.load(i, slot);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int k = E.k[e];
+#pragma unroll
+      for (int q = 0; q < kC; ++q) E.c[e][q] = 0.0;
+      if (e < e_lo || e > e_hi || k == kNoPartner) continue;
+      if constexpr (kMassive) {
+        massive_end_coeffs(c, E.pid, r.pid[(uint64_t)k * r.stride + slot], pi, r.load(k, slot), qm, E.c[e]);
+      } else {
+        double q2, zm, zp, L;
+        if (!end_coeffs(c.cfac, c.tcut, E.pid, pi, r.load(k, slot), q2, zm, zp, L, E.c[e][0], E.c[e][1]))
+          E.c[e][0] = E.c[e][1] = 0.0;
+      }
     }
-    pi = r.load(i, slot);
   }
+  return E;
+}
+
+// Trials of one item, ranked by their bounds: ends e_lo .. e_hi of parton i (a
+// massless gluon's item takes one or both of its ends; a quark's both, the
+// second empty as a quark has one colour partner).
+template <bool kMassive>
+__device__ __forceinline__ void item_bounds(const TrialCtx& c, int i, const Ends<kMassive>& E, int e_lo, int e_hi,
+                                            LowTrial& low, uint32_t& trials, uint32_t& ends) {
   // the q-th end of the item is end e_lo + q: lanes of gluon items with
   // different ends and of quark items take their first end together
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     const int e = e_lo + q;
-    const int k = e == 0 ? k1 : k2;
+    const int k = e == 0 ? E.k[0] : E.k[1];
     if (e > e_hi || k == kNoPartner) continue;
-    double ia, ib;
-    if (cached) {
-      ia = __longlong_as_double((long long)(e == 0 ? w[1] : w[3]));
-      ib = __longlong_as_double((long long)(e == 0 ? w[2] : w[4]));
+    if constexpr (kMassive) {  // both ends, in order
+      end_bounds_massive(c.key, c.cycle, i, k, E.pid, E.c[q], low, trials, ends);
     } else {
-      double q2, zm, zp, L;
-      if (!end_coeffs(c.cfac, c.tcut, pid_i, pi, r.load(k, slot), q2, zm, zp, L, ia, ib)) ia = ib = 0.0;
-    }
-    if (ia == 0.0) continue;  // no phase space above the cutoff
-    ends += 1;
-    const int K = end_draws(c, i, k, pid_i, ia, ib, best, trials);
-    if (K >= 0) {
-      widx = pack_trial(i, k, K);
-      wia = ia;
-      wib = ib;
+      const double ia = e == 0 ? E.c[0][0] : E.c[1][0], ib = e == 0 ? E.c[0][1] : E.c[1][1];
+      if (ia == 0.0) continue;  // no phase space above the cutoff
+      ends += 1;
+      end_bounds(c.key, c.cycle, i, k, E.pid, ia, ib, low, trials);
     }
   }
 }
 
-// Trials of parton i of an event with quark masses in column `slot`: the
-// massive ends compute their ranges themselves each cycle (no end cache);
-// only the item's best (i, k, K) is kept.
-__device__ __forceinline__ void parton_trials_mflat(const TrialCtx& c, const Records& r, uint64_t slot, int i,
-                                                    const QuarkMasses& qm, double& best, uint32_t& widx,
-                                                    uint32_t& trials, uint32_t& ends) {
-  MWinner W{Winner{0.0, 0.0, 0.0, 0.0, -1, 0, 0}, 0.0, 0.0, 0.0, 0.0, 1.0, false};
-  parton_trials_massive(c, r, slot, i, qm, best, W, trials, ends);
-  if (W.w.i >= 0) widx = pack_trial(W.w.i, W.w.k, W.w.K);
+// The winner of one cycle of the event in column `slot` (n partons) by the
+// exact comparison in the paper's loop order (strict maximum above `best`):
+// packed (i, k, K), its scale in `best` and its end's coefficients.  One lane,
+// where the bounds did not prove the order.
+template <bool kCached, bool kMassive>
+__device__ __forceinline__ uint32_t exact_winner(const TrialCtx& c, const Records& r, uint64_t slot, int n,
+                                                 const EndCache& ec, uint64_t col, const QuarkMasses& qm,
+                                                 double& best, double& ca, double& cb) {
+  uint32_t idx = kNoTrial, trials = 0, ends = 0;
+#pragma unroll 1
+  for (int i = 0; i < n; ++i) {
+    const Ends<kMassive> E =
+        load_ends<kCached, kMassive>(c, r, slot, i, 0, 1, ec, col, false, Ent5{}, qm);
+#pragma unroll 1
+    for (int e = 0; e < 2; ++e) {
+      const int k = e ? E.k[1] : E.k[0];
+      if (k == kNoPartner) continue;
+      double cc[Ends<kMassive>::kC];
+#pragma unroll
+      for (int q = 0; q < Ends<kMassive>::kC; ++q) cc[q] = e ? E.c[1][q] : E.c[0][q];
+      int K = -1;
+      if constexpr (kMassive) K = end_draws_massive(c, i, k, E.pid, cc, best, trials, ends);
+      else if (cc[0] != 0.0) K = end_draws(c, i, k, E.pid, cc[0], cc[1], best, trials);
+      if (K >= 0) {
+        idx = pack_trial(i, k, K);
+        ca = cc[0];
+        cb = cc[1];
+      }
+    }
+  }
+  return idx;
 }
 
 // Load the end-cache entry of the item at list position `at` into pw; false
@@ -443,11 +472,6 @@ __device__ __forceinline__ bool prefetch_entry(const uint16_t* item, uint32_t at
 #pragma unroll
   for (int q = 0; q < kCacheWords; ++q) pw.w[q] = ent[q];
   return true;
-}
-
-// (v, idx) beats (w, jdx): larger ln t, or equal and earlier in loop order
-__device__ __forceinline__ bool beats(double v, uint32_t idx, double w, uint32_t jdx) {
-  return idx != kNoTrial && (jdx == kNoTrial || v > w || (v == w && idx < jdx));
 }
 
 // One veto cycle of every busy event of this wave whose last accepted
@@ -477,11 +501,12 @@ constexpr uint32_t kEmitDiv = 2;
 // kAheadCycles (massless cached events): a wave cycle may evaluate K = 2^m
 // consecutive veto cycles of each event that makes trials.  A trial's scale
 // is ln t + ln(R)/c, with c fixed until an emission changes the event, so
-// between emissions the winner of a veto cycle (the largest ln(R)/c) does
+// between emissions the winner of a veto cycle (the lowest |ln R|/c) does
 // not depend on the scale it starts from; only the decision does.  The
 // rounds therefore draw the trials of cycles c .. c+K-1 together (item j of
 // cycle k at position j K + k of its section, keyed by that cycle), each
-// (event, cycle) pair keeps its best ln(R)/c, then one lane per pair chains
+// (event, cycle) pair keeps its lowest bound, then one lane per pair takes
+// that trial's exact ln(R)/c, chains
 // the scales in order (ln t of cycle k = that of cycle k-1 plus the pair's
 // best, the same additions a cycle-by-cycle evaluation makes) and makes the
 // pair's CheckCutoff, alpha_s and AcceptOrVeto with the pair's accept block.
@@ -504,6 +529,13 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
                                            bool& pend, Pending& pd, const Records& slots, uint64_t slot,
                                            const EndCache& ec, uint64_t wave_col, uint32_t lane,
                                            const QuarkMasses& qm = QuarkMasses{0.0, 0.0, 0.0, 0.0, 0.0}) {
+  // kRedraw: the winner's uniform and coefficients are drawn and read again
+  // when the cycle is decided; otherwise each round's lanes that hold a pair's
+  // best write them to LDS.  The long showers of large records have enough
+  // rounds per cycle for the first (500 GeV, 256 partons: 20.6 against 21.7 ms
+  // per 10^6 events), the others do not (mixed energies: 7.4 against 7.2 ms
+  // per 3 10^6).
+  constexpr bool kRedraw = kCached && !kMassive && kOne && !SH::kFour;
   const bool trial = busy && !pend;
   // this lane's event's shower weight: in LDS, or (kRegW) in the event state
   auto wsh = [&]() -> double& {
@@ -573,9 +605,6 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
     sh.qstart[64] = n_q;
     sh.sstart[64] = n_s;
   }
-  // longest per-event run of items in either section: a round's segmented
-  // max needs only the shuffle steps below it
-  const uint32_t gmax = kge * wave_max((uint32_t)(mine & kF)), qmax = wave_max((uint32_t)((mine >> 21) & kF));
   // list length; a spare entry past its end takes the writes beyond it, so
   // the listing loops need no branch.  The stale partons follow the items.
   constexpr uint32_t kItems = sizeof(sh.item) / sizeof(sh.item[0]) - 2;
@@ -619,8 +648,8 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
     sh.key[3][0] = (uint32_t)(one.seed >> 32);
   }
   sh.cycle[lane] = s.cycle;
-  sh.best_v[lane] = -INFINITY;
-  sh.best_idx[lane] = kNoTrial;
+  sh.best[lane] = ~0ull;
+  sh.second[lane] = kNoBound;
   sh.counts[lane] = 0;
   if (kMassive) {
     sh.mc[lane] = qm.c;
@@ -658,7 +687,6 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
   // lanes finish early, in time the round takes for its gluons anyway); with
   // cycles evaluated ahead, item j of a section takes its positions j K ..
   // j K + K - 1, one per cycle, so each (event, cycle) run strides by K
-  const uint32_t run = gmax > qmax ? gmax : qmax;
   // the end-cache entry of the lane's item in the coming round is loaded
   // while the current round reduces its winners (an item past the list's
   // end loads its own)
@@ -679,11 +707,10 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
       const uint32_t j = (at - vbase) >> lg;  // item index within the section
       const uint32_t k = (at - vbase) & (K - 1u);  // cycle ahead
       const bool active = at < vt;
-      double v = -INFINITY;
-      uint32_t idx = kNoTrial;
-      uint32_t o = 63, first = 0, last = 0, pr = 63;
+      LowTrial low;
+      uint32_t i = 0, pr = 63;
       if (active) {
-        uint32_t i;
+        uint32_t o;
         const uint32_t lp = (gsec ? 0u : n_g) + j;  // list position
         if (lp < kItems) {
           const uint32_t it = sh.item[lp];
@@ -696,66 +723,39 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
         // a gluon item's ends: both, or (two items per gluon) the parity of
         // its place in the owner's run
         const int e_lo = gsec && kge == 2 ? (int)((j - st[o]) & 1u) : 0, e_hi = gsec && kge == 2 ? e_lo : 1;
-        first = vbase + (st[o] << lg) + k;  // position of the owner's first item of this cycle in the section
-        last = (j + 1 == st[o + 1]) || lane + K > 63u;
         pr = A ? ((uint32_t)__popcll(tmask & ((1ull << o) - 1ull)) << lg) | k : o;
-        // ahead: trials compared by ln(R)/c alone (the scale added at the decision)
-        const TrialCtx c{key_of(o),
-                         A ? 0.0 : sh.lt[o], sh.tcut[o], sh.ltc[o], sh.cfac[o], sh.cycle[o] + k};
-        double best = A ? -INFINITY : c.ltc, wia = 0.0, wib = 0.0;
-        uint32_t widx = kNoTrial;
+        const TrialCtx c{key_of(o), 0.0, sh.tcut[o], 0.0, sh.cfac[o], sh.cycle[o] + k};
+        QuarkMasses om{0.0, 0.0, 0.0, 0.0, 0.0};
+        if constexpr (kMassive) om = QuarkMasses{0.0, 0.0, 0.0, sh.mc[o], sh.mb[o]};
+        const Ends<kMassive> E = load_ends<kCached, kMassive>(c, slots, sh.slot[o], (int)i, e_lo, e_hi, ec, wave_col + o,
+                                                              kPre && pre, pw, om);
         uint32_t nt = 0, ne = 0;
-        if constexpr (kMassive && kCached)
-          parton_trials_mcached(c, wave_col + o, (int)i, ec, best, widx, nt, ne);
-        else if constexpr (kMassive)
-          parton_trials_mflat(c, slots, sh.slot[o], (int)i, QuarkMasses{0.0, 0.0, 0.0, sh.mc[o], sh.mb[o]}, best,
-                              widx, nt, ne);
-        else
-          item_trials(c, slots, sh.slot[o], (int)i, e_lo, e_hi, ec, wave_col + o, kCached, kPre && pre, pw, best, widx,
-                      wia, wib, nt, ne);
-        if (widx != kNoTrial) {
-          v = best;
-          idx = (widx << 6) | lane;  // same order as widx: items of one pair differ in i
-          if constexpr (!kMassive) {
-            sh.coef[0][lane] = wia;
-            sh.coef[1][lane] = wib;
-          }
-        }
+        item_bounds(c, (int)i, E, e_lo, e_hi, low, nt, ne);
         atomicAdd(&sh.counts[pr], nt | (ne << 16));  // at most 12 x 1024 trials and 2048 ends per cycle
       }
+      // into the pair's lowest and second-lowest bounds: whichever of the
+      // pair's running best and this item's is not the lower goes, with the
+      // item's own second, into the runner-up
+      const uint64_t key = ((uint64_t)low.m << 32) | ((i << 14) | low.k);
+      if (low.m != kNoBound) {
+        const uint32_t old = (uint32_t)(atomicMin((unsigned long long*)&sh.best[pr], key) >> 32);
+        const uint32_t hi = old > low.m ? old : low.m;
+        atomicMin(&sh.second[pr], hi < low.m2 ? hi : low.m2);
+      }
       if (kPre) pre = prefetch_entry(sh.item, list_pos(r0 + 64 + lane, vg, n_g, lg), n_g + n_q, kItems, ec, wave_col, pw);
-      for (uint32_t d = 1; (d << lg) < 64 && d < run; d <<= 1) {
-        const uint32_t dd = d << lg;
-        const double vn = __shfl_up(v, dd);
-        const uint32_t in = __shfl_up(idx, dd);
-        if (active && lane >= dd && at - dd >= first && beats(vn, in, v, idx)) {
-          v = vn;
-          idx = in;
+      if constexpr (!kRedraw) {
+        __syncthreads();  // one wave: the atomics above are done
+        if (low.m != kNoBound && sh.best[pr] == key) {
+          sh.pair[0][pr] = low.u;
+          sh.pair[1][pr] = low.ca;
+          if constexpr (!kMassive) sh.pair[2][pr] = low.cb;
         }
       }
-      // fold each run's best into its pair's: gluon runs first, then quark
-      // runs (one pair may end a run of each kind in the same round)
-      if (active && last && gsec && beats(v, idx, sh.best_v[pr], sh.best_idx[pr])) {
-        sh.best_v[pr] = v;
-        sh.best_idx[pr] = idx;
-        if constexpr (!kMassive) {
-          sh.best_c[0][pr] = sh.coef[0][idx & 63u];
-          sh.best_c[1][pr] = sh.coef[1][idx & 63u];
-        }
-      }
-      if (active && last && !gsec && beats(v, idx, sh.best_v[pr], sh.best_idx[pr])) {
-        sh.best_v[pr] = v;
-        sh.best_idx[pr] = idx;
-        if constexpr (!kMassive) {
-          sh.best_c[0][pr] = sh.coef[0][idx & 63u];
-          sh.best_c[1][pr] = sh.coef[1][idx & 63u];
-        }
-      }
-      __syncthreads();
     }
   };
   if (ahead) rounds(std::true_type{});
   else rounds(std::false_type{});
+  __syncthreads();
   if (kAhead) {  // the event's trial constants, published to LDS above, come back from there
     s.key = key_of(lane);
     s.lt = sh.lt[lane];
@@ -764,43 +764,84 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
     s.cfac = sh.cfac[lane];
     s.cycle = sh.cycle[lane];
   }
+  // The exact winner of the pair in position pr (event o of n_o partons, cycle
+  // `cyc`), its scale counted from lt0: packed (i, k, K) or kNoTrial.
+  auto winner = [&](uint32_t pr, uint32_t o, int n_o, uint32_t cyc, double lt0, double& v, double& ca,
+                    double& cb) -> uint32_t {
+#pragma clang fp contract(off)  // as in end_draws
+    const uint64_t key = sh.best[pr];
+    uint32_t idx = (uint32_t)key;
+    if (key == ~0ull) return kNoTrial;
+    const TrialCtx c{key_of(o), lt0, sh.tcut[o], 0.0, sh.cfac[o], cyc};
+    const int W = (int)(idx & 15u);
+    double u;
+    if constexpr (kRedraw) {
+      const int i = (int)(idx >> 14), k = (int)((idx >> 4) & 1023u);
+      const Ends<kMassive> E = load_ends<kCached, kMassive>(c, slots, sh.slot[o], i, 0, 1, ec, wave_col + o, false,
+                                                            Ent5{}, qm);
+      const bool e1 = k == E.k[1];
+      u = trial_uniform(c.key, cyc, i, k, W);
+      ca = e1 ? E.c[1][0] : E.c[0][0];
+      cb = e1 ? E.c[1][1] : E.c[0][1];
+    } else {
+      u = sh.pair[0][pr];
+      ca = sh.pair[1][pr];
+      if constexpr (!kMassive) cb = sh.pair[2][pr];
+    }
+    double d;
+    if constexpr (kMassive) d = log_fast(u) / ca;
+    else d = log_fast(u) * (W <= 10 ? ca : cb);
+    v = lt0 + d;
+    // (no runner-up: NaN; 1e-13 covers scales that round to equal doubles)
+    constexpr double kLn2 = 0.69314718055994530942;
+    if ((double)__uint_as_float(sh.second[pr]) * kLn2 <= 1e-13 - d) {
+      QuarkMasses om{0.0, 0.0, 0.0, 0.0, 0.0};
+      if constexpr (kMassive) om = QuarkMasses{0.0, 0.0, 0.0, sh.mc[o], sh.mb[o]};
+      v = -INFINITY;
+      idx = exact_winner<kCached, kMassive>(c, slots, sh.slot[o], n_o, ec, wave_col + o, om, v, ca, cb);
+    }
+    return idx;
+  };
   // --- each owner that made trials decides its cycle
   if (ahead) {
     // one lane per (event, cycle) pair: the pair's scale, cutoff and veto;
-    // its outcome goes into the low bits of its best_idx entry (the lane
-    // of the winning item is not needed any more)
+    // its outcome goes into `second`, above it the winner
     const uint32_t n_pairs = (uint32_t)__popcll(tmask) << lg;
     const uint32_t o = lane < n_pairs ? select64(tmask, lane >> lg) : lane;  // the pair's event
     const double asmax = __shfl(s.asmax, (int)o);                              // its trial alpha_s
+    const int n_o = __shfl(s.n, (int)o);
+    const uint32_t rk = lane >> lg, k = lane & (K - 1u), cyc = sh.cycle[o] + k;
+    uint32_t wi = kNoTrial;
+    double v = 0.0, wia = 0.0, wib = 0.0;
+    if (lane < n_pairs && cyc < climit_of(o)) wi = winner(lane, o, n_o, cyc, 0.0, v, wia, wib);
+    sh.pair[0][lane] = v;
+    __syncthreads();
+    double l = sh.lt[o];
+    if (lane < n_pairs)
+      for (uint32_t q = 0; q <= k; ++q) l += sh.pair[0][(rk << lg) | q];  // the winners' scales, in cycle order
+    __syncthreads();
     if (lane < n_pairs) {
-      const uint32_t rk = lane >> lg, k = lane & (K - 1u);
-      const uint32_t cyc = sh.cycle[o] + k, bi = sh.best_idx[lane];
       uint32_t f = kPairVeto;
-      double l = sh.lt[o], t = 0.0, z = 0.0, wf = 1.0;
+      double t = 0.0, z = 0.0, wf = 1.0;
       if (cyc >= climit_of(o)) {
         f = kPairLimit;
-      } else if (bi == kNoTrial) {
-        f = kPairDone;  // no end with phase space above the cutoff
+      } else if (wi == kNoTrial || !(l > sh.ltc[o])) {
+        f = kPairDone;  // no end with phase space above the cutoff, or below it
       } else {
-        for (uint32_t q = 0; q <= k; ++q) l += sh.best_v[(rk << lg) | q];  // the winners' scales, in cycle order
-        if (!(l > sh.ltc[o])) {
-          f = kPairDone;
-        } else {
-          Winner w{0.0, 0.0, 0.0, 0.0, -1, 0, 0};
-          w.K = (int)((bi >> 6) & 15u);
-          end_from_inverse(sh.cfac[o], sh.tcut[o], w.K, sh.best_c[0][lane], sh.best_c[1][lane], w);
-          t = exp(l);
-          const U4 a = key_of(o).draw(cyc, kPurposeAccept, 0);
-          z = trial_z(w, unit(a.x, a.y));
-          const double prob = massless_ratio(w.K, l, t, z, w.rq2, asmax);
-          if (prob >= 0.0 && accept_test(prob, a, wf)) f = kPairAccept;
-        }
+        Winner w{0.0, 0.0, 0.0, 0.0, -1, 0, 0};
+        w.K = (int)(wi & 15u);
+        end_from_inverse(sh.cfac[o], sh.tcut[o], w.K, wia, wib, w);
+        t = exp(l);
+        const U4 a = key_of(o).draw(cyc, kPurposeAccept, 0);
+        z = trial_z(w, unit(a.x, a.y));
+        const double prob = massless_ratio(w.K, l, t, z, w.rq2, asmax);
+        if (prob >= 0.0 && accept_test(prob, a, wf)) f = kPairAccept;
       }
-      sh.best_idx[lane] = (bi & ~63u) | f;
-      sh.coef[0][lane] = l;  // the cycle's scale (its own reads of coef are over)
-      sh.coef[1][lane] = wf;
-      sh.best_c[0][lane] = t;
-      sh.best_c[1][lane] = z;
+      sh.second[lane] = (wi << 6) | f;
+      sh.pair[0][lane] = l;
+      sh.pair[1][lane] = t;
+      sh.pair[2][lane] = z;
+      sh.best[lane] = (uint64_t)__double_as_longlong(wf);
     }
     __syncthreads();
     // each event takes its pairs in cycle order up to the first that ends
@@ -809,7 +850,7 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
       const uint32_t rk = (uint32_t)__popcll(tmask & ((1ull << lane) - 1ull));
       for (uint32_t k = 0; k < K; ++k) {
         const uint32_t pr = (rk << lg) | k;
-        const uint32_t f = sh.best_idx[pr] & 63u;
+        const uint32_t f = sh.second[pr] & 63u;
         if (f == kPairLimit) {
           s.status = kCycleLimitHit;
           break;
@@ -821,14 +862,14 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
           s.status = kDone;
           break;
         }
-        s.lt = sh.coef[0][pr];
-        wsh() *= sh.coef[1][pr];
+        s.lt = sh.pair[0][pr];
+        wsh() *= __longlong_as_double((long long)sh.best[pr]);
         if (f == kPairAccept) {
           if (s.n == s.cap) {
             s.status = kOverflow;
           } else {
-            const uint32_t wi = sh.best_idx[pr] >> 6;
-            pd = Pending{sh.best_c[0][pr], sh.best_c[1][pr], (int)(wi >> 14), (int)((wi >> 4) & 1023u),
+            const uint32_t wi = sh.second[pr] >> 6;
+            pd = Pending{sh.pair[1][pr], sh.pair[2][pr], (int)(wi >> 14), (int)((wi >> 4) & 1023u),
                          (int)(wi & 15u), this_cycle};
             pend = true;
           }
@@ -836,36 +877,27 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
         }
       }
     }
-  } else if (trial && kMassive) {
-    s.trials += sh.counts[lane] & 0xFFFFu;
-    s.ends += sh.counts[lane] >> 16;
-    const uint32_t bi = sh.best_idx[lane];
-    MWinner W{Winner{0.0, 0.0, 0.0, 0.0, -1, 0, 0}, 0.0, 0.0, 0.0, 0.0, 1.0, false};
-    double best = s.ltc;
-    if (bi != kNoTrial) {
-      const uint32_t wi = bi >> 6;
-      best = sh.best_v[lane];
-      W = massive_winner(trial_ctx(s), slots, slot, (int)(wi >> 14), (int)((wi >> 4) & 1023u), (int)(wi & 15u), qm);
-    }
-    pend = veto_decide_massive(s, best, W, acc, pd, wsh());
   } else if (trial) {
     s.trials += sh.counts[lane] & 0xFFFFu;
     s.ends += sh.counts[lane] >> 16;
-    const uint32_t bi = sh.best_idx[lane];
-    Winner w{0.0, 0.0, 0.0, 0.0, -1, 0, 0};
-    double best = s.ltc;
-    if (bi != kNoTrial) {
-      const uint32_t wi = bi >> 6;
-      w.i = (int)(wi >> 14);
-      w.k = (int)((wi >> 4) & 1023u);
-      w.K = (int)(wi & 15u);
-      best = sh.best_v[lane];
-      // the winning end's coefficients, passed on by the item that drew the
-      // winner: its cache entry's numbers (or, without a cache, what the item
-      // computed from the records, the same numbers)
-      end_from_inverse(s.cfac, s.tcut, w.K, sh.best_c[0][lane], sh.best_c[1][lane], w);
+    double best = s.ltc, wia = 0.0, wib = 0.0;
+    uint32_t wi = winner(lane, lane, s.n, s.cycle, s.lt, best, wia, wib);
+    if (wi != kNoTrial && !(best > s.ltc)) wi = kNoTrial;  // below the cutoff
+    if constexpr (kMassive) {
+      MWinner W{Winner{0.0, 0.0, 0.0, 0.0, -1, 0, 0}, 0.0, 0.0, 0.0, 0.0, 1.0, false};
+      if (wi != kNoTrial)
+        W = massive_winner(trial_ctx(s), slots, slot, (int)(wi >> 14), (int)((wi >> 4) & 1023u), (int)(wi & 15u), qm);
+      pend = veto_decide_massive(s, best, W, acc, pd, wsh());
+    } else {
+      Winner w{0.0, 0.0, 0.0, 0.0, -1, 0, 0};
+      if (wi != kNoTrial) {
+        w.i = (int)(wi >> 14);
+        w.k = (int)((wi >> 4) & 1023u);
+        w.K = (int)(wi & 15u);
+        end_from_inverse(s.cfac, s.tcut, w.K, wia, wib, w);
+      }
+      pend = veto_decide_drawn(s, best, w, acc, pd, wsh());
     }
-    pend = veto_decide_drawn(s, best, w, acc, pd, wsh());
   }
   // --- pending emissions, built together; the new parton's type goes into the mask
   const uint32_t n_pend = __popcll(__ballot(pend));
@@ -922,13 +954,13 @@ static uint32_t events_per_wave(uint64_t n, uint64_t waves) {
 // consecutive events of the batch (already started by k_me) from start to
 // cutoff, with no refill; finished lanes only stop contributing trial work.
 // kFour (massless, at most 128 partons): four resident waves per SIMD (128
-// registers, a few spilled; 9.2 + 1 KB of LDS), the trial constants
+// registers, a few spilled; 8.7 + 1 KB of LDS), the trial constants
 // reloaded from LDS after the rounds (kAhead); otherwise three waves, the
 // massive instantiation reloading them too to fit without spilling.
 template <bool kMassive, bool kOne, bool kFour = false>
 __global__ void __launch_bounds__(64, kFour ? 4 : 3)
     k_shower_plain_flat(Records r, Summary sm, EventInputs in, uint32_t n, EndCache ec, uint32_t per_wave) {
-  __shared__ FlatShared<kOne, kFour> sh;
+  __shared__ FlatShared<kMassive, kOne, kFour> sh;
   const OneRequest one{in.seed, in.first, in.cycle_limit};
   const uint32_t lane = threadIdx.x;
   const uint32_t words = mask_words(r.cap);
@@ -999,7 +1031,7 @@ __global__ void __launch_bounds__(64, kFour ? 4 : (kInPlace || (kCached && !kMas
   // three waves in place: the shower weight in a register and the short
   // item list, so that 256-parton records fit twelve blocks per CU
   constexpr bool kRegW = kOne && !kFour;
-  __shared__ FlatShared<kOne, kFour, kRegW> sh;
+  __shared__ FlatShared<kMassive, kOne, kFour, kRegW> sh;
   const OneRequest one = kOne ? OneRequest{A.reqs[0].seed, A.reqs[0].first, A.reqs[0].cycle_limit}
                               : OneRequest{0ull, 0ull, 0u};
   const uint32_t lane = threadIdx.x;

@@ -266,6 +266,85 @@ __device__ __forceinline__ int end_draws(const TrialCtx& c, int i, int k, int pi
   return K;
 }
 
+// Single-precision bounds that pick a cycle's winner.  A trial at uniform u
+// with reciprocal coefficient ia lies |ln u| ia below the cycle's scale, and
+// only the closest one matters; comparing exact logarithms spent a quarter of
+// a trial's instructions.  So a trial is ranked by a number that is never
+// above its |log2 u| ia (trial_bound), and the exact double-precision scale is
+// computed for the lowest alone.  Where the runner-up's bound is not above the
+// winner's exact distance the order is not proven, and the cycle's trials are
+// compared exactly instead (a few cycles in 10^5): the winner and its scale
+// are those of the exact comparison in every case.
+//
+// The bound: rounding u to float moves log2 u by at most 8.6e-8 (relative
+// 2^-24), v_log_f32 is within 1.2e-7 |log2 u| (measured over every float from
+// 2^-54 to 1), and rounding or inverting the coefficient, the fma and the
+// product add at most 3.6e-7 of the result; the constants taken cover twice
+// that.
+constexpr float kBoundAbs = 2e-7f, kBoundRel = 1.0f - 0x1p-20f;
+__device__ __forceinline__ uint32_t trial_bound(double u, float ia) {
+  const float l = -__builtin_amdgcn_logf((float)u);
+  return __float_as_uint(fmaxf(fmaf(l, kBoundRel, -kBoundAbs), 0.0f) * ia);  // >= 0: orders as its bits
+}
+
+// The lowest bound of a set of trials with that trial's kernel, spectator,
+// uniform and coefficients, and the lowest bound of the others.
+constexpr uint32_t kNoBound = 0xFFFFFFFFu;
+struct LowTrial {
+  uint32_t m = kNoBound, m2 = kNoBound;
+  uint32_t k = 0;  // spectator << 4 | kernel
+  double u = 1.0, ca = 0.0, cb = 0.0;
+  __device__ __forceinline__ void take(uint32_t v, uint32_t vk, double vu, double va, double vb) {
+    const uint32_t hi = v > m ? v : m;
+    m2 = hi < m2 ? hi : m2;
+    if (v < m) {
+      m = v;
+      k = vk;
+      u = vu;
+      ca = va;
+      cb = vb;
+    }
+  }
+};
+
+// The uniform of kernel K of the end (i, k), drawn again: kernel q = 0 (a
+// quark's, g -> g g), 1, ..., 5 (g -> f fbar) takes half q & 1 of block q / 2.
+__device__ __forceinline__ double trial_uniform(const Keyed& key, uint32_t cycle, int i, int k, int K) {
+  const uint32_t q = K <= 10 ? 0u : (uint32_t)(K - 10);
+  const U4 d = key.draw(cycle, kPurposeTrial, trial_slot(i, k, q >> 1));
+  return q & 1u ? unit(d.z, d.w) : unit(d.x, d.y);
+}
+
+// end_draws with the trials ranked by their bounds (same draws and counts).
+__device__ __forceinline__ void end_bounds(const Keyed& key, uint32_t cycle, int i, int k, int pid_i, double ia,
+                                           double ib, LowTrial& low, uint32_t& trials) {
+  const bool gluon = pid_i == kGluon;
+  const U4 d0 = key.draw(cycle, kPurposeTrial, trial_slot(i, k, 0));
+  const double u0 = unit(d0.x, d0.y);
+  low.take(trial_bound(u0, (float)ia),
+           ((uint32_t)k << 4) | (uint32_t)(gluon ? 10 : (pid_i > 0 ? pid_i - 1 : 4 - pid_i)), u0, ia, ib);
+  trials += gluon ? 6u : 1u;
+  if (gluon) {
+    uint64_t bm = unit_bits(d0.z, d0.w);
+    uint32_t fm = 1;
+#pragma unroll  // the two Philox blocks interleave
+    for (uint32_t g = 1; g < 3; ++g) {
+      const U4 d = key.draw(cycle, kPurposeTrial, trial_slot(i, k, g));
+      const uint64_t b0 = unit_bits(d.x, d.y), b1 = unit_bits(d.z, d.w);
+      if (b0 > bm) {  // first flavour wins ties, as in the kernel loop
+        bm = b0;
+        fm = 2 * g;
+      }
+      if (b1 > bm) {
+        bm = b1;
+        fm = 2 * g + 1;
+      }
+    }
+    const double um = unit_of_bits(bm);
+    low.take(trial_bound(um, (float)ib), ((uint32_t)k << 4) | (10u + fm), um, ia, ib);
+  }
+}
+
 // All trials of the dipole end (i, k): one per kernel of the splitter.
 __device__ __forceinline__ void end_trials(const TrialCtx& c, int i, int k, int pid_i, const P4& pi,
                                            const P4& pk, double& best, Winner& w, uint32_t& trials,
@@ -730,6 +809,53 @@ __device__ __forceinline__ int end_draws_massive(const TrialCtx& c, int i, int k
     }
   }
   return K;
+}
+
+// end_draws_massive with the trials ranked by their bounds (same draws and
+// counts); each with its own coefficient.
+__device__ __forceinline__ void end_bounds_massive(const Keyed& key, uint32_t cycle, int i, int k, int pid_i,
+                                                   const double cc[4], LowTrial& low, uint32_t& trials,
+                                                   uint32_t& ends) {
+  auto take = [&](double u, double c, int K) {
+    low.take(trial_bound(u, __builtin_amdgcn_rcpf((float)c)), ((uint32_t)k << 4) | (uint32_t)K, u, c, 0.0);
+  };
+  if (pid_i != kGluon) {
+    if (cc[0] == 0.0) return;
+    ends += 1;
+    trials += 1;
+    const U4 d = key.draw(cycle, kPurposeTrial, trial_slot(i, k, 0));
+    take(unit(d.x, d.y), cc[0], pid_i > 0 ? pid_i - 1 : 4 - pid_i);
+    return;
+  }
+  if (cc[0] == 0.0 && cc[2] == 0.0 && cc[3] == 0.0) return;
+  ends += 1;
+  const U4 d0 = key.draw(cycle, kPurposeTrial, trial_slot(i, k, 0));
+  const U4 d1 = key.draw(cycle, kPurposeTrial, trial_slot(i, k, 1));
+  const U4 d2 = key.draw(cycle, kPurposeTrial, trial_slot(i, k, 2));
+  if (cc[0] != 0.0) {
+    trials += 4;
+    take(unit(d0.x, d0.y), cc[0], 10);
+    uint64_t bm = unit_bits(d0.z, d0.w);
+    int fm = 1;
+    const uint64_t bu = unit_bits(d1.x, d1.y), bs = unit_bits(d1.z, d1.w);
+    if (bu > bm) {  // the first flavour wins ties, as in the kernel loop
+      bm = bu;
+      fm = 2;
+    }
+    if (bs > bm) {
+      bm = bs;
+      fm = 3;
+    }
+    take(unit_of_bits(bm), cc[1], 10 + fm);
+  }
+  if (cc[2] != 0.0) {
+    trials += 1;
+    take(unit(d2.x, d2.y), cc[2], 14);
+  }
+  if (cc[3] != 0.0) {
+    trials += 1;
+    take(unit(d2.z, d2.w), cc[3], 15);
+  }
 }
 
 // The winner record of kernel K of the end (i, k) of the event in column e,
