@@ -498,7 +498,7 @@ constexpr uint32_t kEmitDiv = 2;
 // take it to fit 128 registers; at three waves the plain kernel takes it
 // with quark masses only (for massless events it measured 1% slower there).
 //
-// kAheadCycles (massless cached events): a wave cycle may evaluate K = 2^m
+// kAheadCycles (cached events): a wave cycle may evaluate K = 2^m
 // consecutive veto cycles of each event that makes trials.  A trial's scale
 // is ln t + ln(R)/c, with c fixed until an emission changes the event, so
 // between emissions the winner of a veto cycle (the lowest |ln R|/c) does
@@ -514,9 +514,11 @@ constexpr uint32_t kEmitDiv = 2;
 // cycle sequence (cutoff, acceptance, cycle limit); later pairs are dropped
 // and drawn again, keyed by the same cycles, after the emission.  K is the
 // largest power of two with at most 64 pairs, at most kAheadMax cycles and
-// at most kAheadRounds more rounds than one cycle's items take.
+// at most kAheadRounds more rounds than one cycle's items take (2, 3, 5, 8 and
+// 16 rounds at 500 GeV: 21.1, 20.5, 20.0, 19.8, 19.8 ms per 10^6 events; LEP
+// within 1%).  With quark masses it took 250000 events from 1.71 to 1.36 ms.
 constexpr uint32_t kAheadLgMax = 3;  // kAheadMax = 8
-constexpr uint32_t kAheadRounds = 3;
+constexpr uint32_t kAheadRounds = 8;
 enum : uint32_t { kPairVeto = 0, kPairAccept = 1, kPairDone = 2, kPairLimit = 3 };
 
 __device__ __forceinline__ uint32_t list_pos(uint32_t v, uint32_t vg, uint32_t n_g, uint32_t lg) {
@@ -564,9 +566,6 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
   // sections and of the stale partons (counts in 21-bit fields: at most 64
   // events of 1024 partons)
   constexpr uint64_t kF = (1ull << 21) - 1;
-  // the cycle's accept block depends on the event and cycle only: drawn here,
-  // where its arithmetic overlaps the waits of the publishing
-  const U4 acc = trial ? accept_draw(s) : U4{0u, 0u, 0u, 0u};
   uint32_t ng = 0, ns = 0;
   if (trial)
     for (uint32_t w = 0; w < words; ++w) {
@@ -590,7 +589,11 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
       ++lg_;
   }
   const uint32_t lg = lg_, K = 1u << lg_;
-  const bool ahead = kAheadCycles && lg_ > 0;  // one cycle at a time otherwise
+  // (kPairs: the pairs' decision serves K = 1 too: one copy of its arithmetic,
+  // and fewer registers; kRedraw's kernels keep the owners' own for K = 1, 2.5%
+  // faster at 500 GeV)
+  constexpr bool kPairs = kAheadCycles && !kRedraw;
+  const bool ahead = kPairs || (kAheadCycles && lg_ > 0);
   // A massless gluon's two dipole ends become two items (half the longest
   // lane's work in a round) whenever that takes no more rounds than one item
   // per gluon; otherwise, and with quark masses, one item per gluon.
@@ -754,7 +757,7 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
     }
   };
   if (ahead) rounds(std::true_type{});
-  else rounds(std::false_type{});
+  else if constexpr (!kPairs) rounds(std::false_type{});
   __syncthreads();
   if (kAhead) {  // the event's trial constants, published to LDS above, come back from there
     s.key = key_of(lane);
@@ -808,7 +811,7 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
     // its outcome goes into `second`, above it the winner
     const uint32_t n_pairs = (uint32_t)__popcll(tmask) << lg;
     const uint32_t o = lane < n_pairs ? select64(tmask, lane >> lg) : lane;  // the pair's event
-    const double asmax = __shfl(s.asmax, (int)o);                              // its trial alpha_s
+    const double asmax = __shfl(s.asmax, (int)o);  // its trial alpha_s
     const int n_o = __shfl(s.n, (int)o);
     const uint32_t rk = lane >> lg, k = lane & (K - 1u), cyc = sh.cycle[o] + k;
     uint32_t wi = kNoTrial;
@@ -828,13 +831,22 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
       } else if (wi == kNoTrial || !(l > sh.ltc[o])) {
         f = kPairDone;  // no end with phase space above the cutoff, or below it
       } else {
-        Winner w{0.0, 0.0, 0.0, 0.0, -1, 0, 0};
-        w.K = (int)(wi & 15u);
-        end_from_inverse(sh.cfac[o], sh.tcut[o], w.K, wia, wib, w);
-        t = exp(l);
         const U4 a = key_of(o).draw(cyc, kPurposeAccept, 0);
-        z = trial_z(w, unit(a.x, a.y));
-        const double prob = massless_ratio(w.K, l, t, z, w.rq2, asmax);
+        double prob;
+        t = exp(l);
+        if constexpr (kMassive) {
+          const MWinner W = massive_winner(
+              TrialCtx{key_of(o), 0.0, sh.tcut[o], 0.0, sh.cfac[o], cyc}, slots, sh.slot[o], (int)(wi >> 14),
+              (int)((wi >> 4) & 1023u), (int)(wi & 15u), QuarkMasses{0.0, 0.0, 0.0, sh.mc[o], sh.mb[o]});
+          z = trial_z(W.w, unit(a.x, a.y));
+          prob = massive_prob(W, l, t, z, asmax);
+        } else {
+          Winner w{0.0, 0.0, 0.0, 0.0, -1, 0, 0};
+          w.K = (int)(wi & 15u);
+          end_from_inverse(sh.cfac[o], sh.tcut[o], w.K, wia, wib, w);
+          z = trial_z(w, unit(a.x, a.y));
+          prob = massless_ratio(w.K, l, t, z, w.rq2, asmax);
+        }
         if (prob >= 0.0 && accept_test(prob, a, wf)) f = kPairAccept;
       }
       sh.second[lane] = (wi << 6) | f;
@@ -877,12 +889,13 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
         }
       }
     }
-  } else if (trial) {
+  } else if (!kPairs && trial) {
     s.trials += sh.counts[lane] & 0xFFFFu;
     s.ends += sh.counts[lane] >> 16;
     double best = s.ltc, wia = 0.0, wib = 0.0;
     uint32_t wi = winner(lane, lane, s.n, s.cycle, s.lt, best, wia, wib);
     if (wi != kNoTrial && !(best > s.ltc)) wi = kNoTrial;  // below the cutoff
+    const U4 acc = accept_draw(s);
     if constexpr (kMassive) {
       MWinner W{Winner{0.0, 0.0, 0.0, 0.0, -1, 0, 0}, 0.0, 0.0, 0.0, 0.0, 1.0, false};
       if (wi != kNoTrial)
@@ -929,12 +942,12 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
 
 // Waves that a launch of the flattened kernels spreads its events over: the
 // resident ones of 256 compute units (sixteen blocks per CU up to 64 partons
-// per record, fourteen up to 128, eleven above: LDS).  With quark masses one
-// per SIMD: those waves evaluate one veto cycle at a time, so a sparse wave
-// saves less than a second one costs.
+// per record, fourteen up to 128, eleven above: LDS), twelve with quark masses
+// (three per SIMD; against one per SIMD, calls of 5000 events 393 and 372 us,
+// 20000 566 and 618, 60000 875 and 978).
 static uint32_t flat_waves(uint32_t cap, bool massive) {
   constexpr uint32_t kCUs = 256;
-  return kCUs * (massive ? 4u : cap <= 64 ? 16u : cap <= kFourMaxCap ? 14u : 11u);
+  return kCUs * (massive ? 12u : cap <= 64 ? 16u : cap <= kFourMaxCap ? 14u : 11u);
 }
 
 // Events that a wave holds at once.  A small launch is bound by the chain of
@@ -978,7 +991,7 @@ __global__ void __launch_bounds__(64, kFour ? 4 : 3)
     mask_init(flat_gmask + (uint64_t)lane * words, flat_gmask + (uint64_t)(64 + lane) * words, words, r, e, s.n);
   }
   while (__any(busy)) {
-    flat_cycle<true, kMassive, kMassive || kFour, !kMassive, kOne>(sh, one, flat_gmask, words, s, busy, pend, pd, r, e, ec,
+    flat_cycle<true, kMassive, kMassive || kFour, true, kOne>(sh, one, flat_gmask, words, s, busy, pend, pd, r, e, ec,
                                                           e - lane, lane, in.qm);
     if (busy && s.status != kRunning) {
       s.wsh = sh.wsh[lane];
@@ -1059,7 +1072,7 @@ __global__ void __launch_bounds__(64, kFour ? 4 : (kInPlace || (kCached && !kMas
       busy = true;
     }
     if (!__any(busy)) break;
-    flat_cycle<kCached, kMassive, kInPlace, kCached && !kMassive, kOne>(
+    flat_cycle<kCached, kMassive, kInPlace, kCached, kOne>(
         sh, one, flat_gmask, words, s, busy, pend, pd, A.slots, slot, A.cache, L - lane, lane, A.reqs[req].qm);
     if (busy && s.status != kRunning) {
       if constexpr (!kRegW) s.wsh = sh.wsh[lane];

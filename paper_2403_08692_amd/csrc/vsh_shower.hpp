@@ -903,6 +903,14 @@ __device__ __forceinline__ void parton_trials_massive(const TrialCtx& c, const R
                        trials, ends);
 }
 
+// True over trial density of a winner with quark masses at scale t = e^lt;
+// negative outside the phase space.
+__device__ __forceinline__ double massive_prob(const MWinner& W, double lt, double t, double z, double asmax) {
+  if (!W.massive) return massless_ratio(W.w.K, lt, t, z, W.w.rq2, asmax);
+  const double ratio = massive_ratio(W.w.K, t, z, W.Q2, W.mi, W.mj, W.mk, W.fo);
+  return ratio < 0.0 ? -1.0 : alpha_s_of_log(lt) / asmax * ratio;
+}
+
 __device__ __forceinline__ bool veto_decide_massive(EvState& s, double best, const MWinner& W, const U4& a,
                                                     Pending& p, double& wsh) {
   const Winner& w = W.w;
@@ -914,15 +922,8 @@ __device__ __forceinline__ bool veto_decide_massive(EvState& s, double best, con
   s.lt = best;
   const double t = exp(best);
   const double z = trial_z(w, unit(a.x, a.y));
-  double prob;
-  if (!W.massive) {
-    prob = massless_ratio(w.K, best, t, z, w.rq2, s.asmax);
-    if (prob < 0.0) return false;  // y >= 1
-  } else {
-    const double ratio = massive_ratio(w.K, t, z, W.Q2, W.mi, W.mj, W.mk, W.fo);
-    if (ratio < 0.0) return false;  // outside the phase space
-    prob = alpha_s_of_log(best) / s.asmax * ratio;
-  }
+  const double prob = massive_prob(W, best, t, z, s.asmax);
+  if (prob < 0.0) return false;  // outside the phase space
   if (!accept_test(prob, a, wsh)) return false;
   if (s.n == s.cap) {
     s.status = kOverflow;
