@@ -165,8 +165,9 @@ __global__ void __launch_bounds__(256) k_shower_persistent(PersistArgs A) {
 // and the cycle limit is one, so neither is kept per event in LDS (kOne),
 // and, for four waves per SIMD (kFour, records of at most 128 partons), the
 // item list (whose free tail holds the stale partons) is shorter (its
-// overflow takes the offsets' path): 8.7 KB + 1 KB of masks, sixteen blocks
-// per CU at 64 partons, fourteen at 128.  With
+// overflow takes the offsets' path): 8.1 KB + 1 or 2 KB of masks, sixteen
+// blocks per CU (a list of 1124 entries, fourteen at 128 partons: 2% slower at
+// 200 GeV).  With
 // 256-parton records the layout leaves room for one more block per CU.
 struct OneRequest {
   uint64_t seed, first;
@@ -182,12 +183,14 @@ struct FlatShared {
   uint32_t slot[64];  // record columns (a launch covers fewer than 2^32)
   uint32_t key[4][kOne ? 1 : 64];
   uint32_t cycle[64];
+  uint8_t rank[64];     // of the events that make trials: their first pair
+  uint8_t ranked[64];   // and the events in order of rank
   uint32_t gstart[65], qstart[65];  // per-owner item offsets in the gluon and quark sections
   uint32_t sstart[65];              // per-owner offsets in the list of stale partons
   // the cycle's items, owner << 10 | parton: gluon items (a gluon twice,
   // once per dipole end, when rounds allow), then quark items, then the
   // stale partons in what the items leave free (two spare entries)
-  uint16_t item[1024 + (kFour || kRegW ? 100 : 384) + 4];
+  alignas(4) uint16_t item[(kFour ? 768 : kRegW ? 1124 : 1408) + 4];
   // per (event, cycle) pair: its trials' lowest bound << 32 | packed (i, k, K),
   // and the lowest bound of the others
   uint64_t best[64];
@@ -276,11 +279,25 @@ __device__ __forceinline__ uint64_t pack_meta(int pid, int k1, int k2) {
   return (uint64_t)(uint8_t)(int8_t)pid | ((uint64_t)(uint16_t)k1 << 8) | ((uint64_t)(uint16_t)k2 << 24);
 }
 
+// The entry of parton i of column o of a wave's cache (the wave's first column
+// at ec.rec): the base is the same for all lanes and the offset fits 32 bits,
+// so the address costs three instructions instead of a dozen.
+template <int kW>
+__device__ __forceinline__ uint64_t* entry_at(const EndCache& ec, uint32_t o, uint32_t i) {
+  return (uint64_t*)((char*)ec.rec + (o * ec.cap + i) * (uint32_t)(8 * kW));
+}
+template <int kW>
+__device__ __forceinline__ EndCache wave_cache(const EndCache& ec, uint64_t wave_col) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)wave_col),
+                 hi = __builtin_amdgcn_readfirstlane((uint32_t)(wave_col >> 32));
+  return EndCache{ec.rec ? ec.rec + (((uint64_t)hi << 32) | lo) * ec.cap * kW : ec.rec, ec.cap};
+}
+
 // Rebuild the cache entry of parton i of the event in column `slot` from the
 // records (the stale rounds of a cycle).
 __device__ __forceinline__ void entry_build(double cfac, double tcut, const Records& r, uint64_t slot, int i,
-                                            const EndCache& ec, uint64_t col) {
-  uint64_t* ent = ec.rec + ((col * ec.cap) + (uint64_t)i) * kCacheWords;
+                                            const EndCache& ec, uint32_t col) {
+  uint64_t* ent = entry_at<kCacheWords>(ec, col, (uint32_t)i);
   const uint64_t oi = (uint64_t)i * r.stride + slot;
   const int pid_i = r.pid[oi];
   int k1 = r.cpart[oi], k2 = r.apart[oi];
@@ -311,8 +328,8 @@ __device__ __forceinline__ void entry_build(double cfac, double tcut, const Reco
 // The same for an event with quark masses: per end the four class
 // coefficients of massive_end_coeffs.
 __device__ __forceinline__ void entry_build_massive(double cfac, double tcut, const Records& r, uint64_t slot, int i,
-                                                    const EndCache& ec, uint64_t col, const QuarkMasses& qm) {
-  uint64_t* ent = ec.rec + ((col * ec.cap) + (uint64_t)i) * kMCacheWords;
+                                                    const EndCache& ec, uint32_t col, const QuarkMasses& qm) {
+  uint64_t* ent = entry_at<kMCacheWords>(ec, col, (uint32_t)i);
   const uint64_t oi = (uint64_t)i * r.stride + slot;
   const int pid_i = r.pid[oi];
   int k1 = r.cpart[oi], k2 = r.apart[oi];
@@ -358,14 +375,14 @@ struct Ends {
 // records.
 template <bool kCached, bool kMassive>
 __device__ __forceinline__ Ends<kMassive> load_ends(const TrialCtx& c, const Records& r, uint64_t slot, int i, int e_lo,
-                                                    int e_hi, const EndCache& ec, uint64_t col, bool pre,
+                                                    int e_hi, const EndCache& ec, uint32_t col, bool pre,
                                                     const Ent5& pw, const QuarkMasses& qm) {
   constexpr int kC = Ends<kMassive>::kC;
   Ends<kMassive> E;
   if constexpr (kCached) {
     constexpr int kW = kMassive ? kMCacheWords : kCacheWords;
     static_assert(kW == 1 + 2 * kC);
-    const uint64_t* ent = ec.rec + ((col * ec.cap) + (uint64_t)i) * kW;
+    const uint64_t* ent = entry_at<kW>(ec, col, (uint32_t)i);
     uint64_t w[kW];
 #pragma unroll
     for (int q = 0; q < kW; ++q) {
@@ -435,7 +452,7 @@ __device__ __forceinline__ void item_bounds(const TrialCtx& c, int i, const Ends
 // where the bounds did not prove the order.
 template <bool kCached, bool kMassive>
 __device__ __forceinline__ uint32_t exact_winner(const TrialCtx& c, const Records& r, uint64_t slot, int n,
-                                                 const EndCache& ec, uint64_t col, const QuarkMasses& qm,
+                                                 const EndCache& ec, uint32_t col, const QuarkMasses& qm,
                                                  double& best, double& ca, double& cb) {
   uint32_t idx = kNoTrial, trials = 0, ends = 0;
 #pragma unroll 1
@@ -465,10 +482,10 @@ __device__ __forceinline__ uint32_t exact_winner(const TrialCtx& c, const Record
 // Load the end-cache entry of the item at list position `at` into pw; false
 // (nothing loaded) past the cycle's items or the list's end.
 __device__ __forceinline__ bool prefetch_entry(const uint16_t* item, uint32_t at, uint32_t n_items, uint32_t n_list,
-                                               const EndCache& ec, uint64_t wave_col, Ent5& pw) {
+                                               const EndCache& ec, Ent5& pw) {
   if (at >= n_items || at >= n_list) return false;
   const uint32_t it = item[at];
-  const uint64_t* ent = ec.rec + (((wave_col + (it >> 10)) * ec.cap) + (uint64_t)(it & 1023u)) * kCacheWords;
+  const uint64_t* ent = entry_at<kCacheWords>(ec, it >> 10, it & 1023u);
 #pragma unroll
   for (int q = 0; q < kCacheWords; ++q) pw.w[q] = ent[q];
   return true;
@@ -529,7 +546,7 @@ template <bool kCached, bool kMassive = false, bool kAhead = false, bool kAheadC
           class SH>
 __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64_t* gm, uint32_t words, EvState& s, bool busy,
                                            bool& pend, Pending& pd, const Records& slots, uint64_t slot,
-                                           const EndCache& ec, uint64_t wave_col, uint32_t lane,
+                                           const EndCache& cache, uint64_t wave_col, uint32_t lane,
                                            const QuarkMasses& qm = QuarkMasses{0.0, 0.0, 0.0, 0.0, 0.0}) {
   // kRedraw: the winner's uniform and coefficients are drawn and read again
   // when the cycle is decided; otherwise each round's lanes that hold a pair's
@@ -538,6 +555,7 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
   // per 10^6 events), the others do not (mixed energies: 7.4 against 7.2 ms
   // per 3 10^6).
   constexpr bool kRedraw = kCached && !kMassive && kOne && !SH::kFour;
+  const EndCache ec = wave_cache<kMassive ? kMCacheWords : kCacheWords>(cache, wave_col);
   const bool trial = busy && !pend;
   // this lane's event's shower weight: in LDS, or (kRegW) in the event state
   auto wsh = [&]() -> double& {
@@ -600,6 +618,11 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
   const uint32_t kge = !kMassive && (K * (2 * n_g1 + n_q) + 63) / 64 == (K * (n_g1 + n_q) + 63) / 64 ? 2u : 1u;
   const uint32_t n_g = kge * n_g1;
   const uint32_t vg = K * n_g, vt = vg + K * n_q;  // positions of the rounds: gluon items, then quark items
+  if (kAheadCycles && trial) {
+    const uint32_t rk = __builtin_amdgcn_mbcnt_hi((uint32_t)(tmask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)tmask, 0u));
+    sh.rank[lane] = (uint8_t)(rk << lg_);
+    sh.ranked[rk] = (uint8_t)lane;
+  }
   sh.gstart[lane] = kge * (uint32_t)(excl & kF);
   sh.qstart[lane] = (uint32_t)((excl >> 21) & kF);
   sh.sstart[lane] = (uint32_t)(excl >> 42);
@@ -612,7 +635,26 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
   // the listing loops need no branch.  The stale partons follow the items.
   constexpr uint32_t kItems = sizeof(sh.item) / sizeof(sh.item[0]) - 2;
   const uint32_t sbase = n_g + n_q < kItems ? n_g + n_q : kItems;
-  if (trial) {  // list this event's items (beyond the lists' lengths rounds search the offsets instead)
+  if (n_g + n_q + n_s <= kItems && !__any(trial && s.n > 32)) {
+    // all in the list, and each event's masks one word: half the instructions
+    // of the general listing below, which are a tenth of an LEP shower's
+    if (trial) {
+      const uint32_t live = s.n >= 32 ? ~0u : (1u << s.n) - 1u, m = (uint32_t)mym[0], top = lane << 10;
+      uint16_t* w = sh.item + n_g + (uint32_t)((excl >> 21) & kF);
+      for (uint32_t x = ~m & live; x; x &= x - 1) *w++ = (uint16_t)(top | (uint32_t)__builtin_ctz(x));  // quarks
+      if (kge == 2) {  // both of a gluon's ends at once
+        uint32_t* w2 = (uint32_t*)sh.item + (uint32_t)(excl & kF);
+        for (uint32_t x = m & live; x; x &= x - 1) *w2++ = (top | (uint32_t)__builtin_ctz(x)) * 0x10001u;
+      } else {
+        w = sh.item + (uint32_t)(excl & kF);
+        for (uint32_t x = m & live; x; x &= x - 1) *w++ = (uint16_t)(top | (uint32_t)__builtin_ctz(x));
+      }
+      if (kCached) {
+        w = sh.item + sbase + (uint32_t)(excl >> 42);
+        for (uint32_t x = (uint32_t)mys[0] & live; x; x &= x - 1) *w++ = (uint16_t)(top | (uint32_t)__builtin_ctz(x));
+      }
+    }
+  } else if (trial) {  // list this event's items (beyond the lists' lengths rounds search the offsets instead)
     uint32_t gpos = kge * (uint32_t)(excl & kF), qpos = n_g + (uint32_t)((excl >> 21) & kF),
              spos = (uint32_t)(excl >> 42);
     for (uint32_t w = 0; w < words; ++w) {
@@ -674,10 +716,10 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
           i = select_slot(sm + (uint64_t)o * words, words, at - sh.sstart[o], true);
         }
         if constexpr (kMassive)
-          entry_build_massive(sh.cfac[o], sh.tcut[o], slots, sh.slot[o], (int)i, ec, wave_col + o,
+          entry_build_massive(sh.cfac[o], sh.tcut[o], slots, sh.slot[o], (int)i, ec, o,
                               QuarkMasses{0.0, 0.0, 0.0, sh.mc[o], sh.mb[o]});
         else
-          entry_build(sh.cfac[o], sh.tcut[o], slots, sh.slot[o], (int)i, ec, wave_col + o);
+          entry_build(sh.cfac[o], sh.tcut[o], slots, sh.slot[o], (int)i, ec, o);
       }
     }
     __threadfence_block();  // the rebuilt entries are stored before any trial round reads them
@@ -696,7 +738,7 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
   constexpr bool kPre = kAhead && kCached && !kMassive;
   Ent5 pw{{0ull, 0ull, 0ull, 0ull, 0ull}};
   bool pre = false;
-  if (kPre) pre = prefetch_entry(sh.item, list_pos(lane, vg, n_g, lg), n_g + n_q, kItems, ec, wave_col, pw);
+  if (kPre) pre = prefetch_entry(sh.item, list_pos(lane, vg, n_g, lg), n_g + n_q, kItems, ec, pw);
   // (the rounds' code compiled twice: one cycle at a time it takes no cycle
   // index and no pair rank)
   auto rounds = [&](auto kA) {
@@ -726,11 +768,11 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
         // a gluon item's ends: both, or (two items per gluon) the parity of
         // its place in the owner's run
         const int e_lo = gsec && kge == 2 ? (int)((j - st[o]) & 1u) : 0, e_hi = gsec && kge == 2 ? e_lo : 1;
-        pr = A ? ((uint32_t)__popcll(tmask & ((1ull << o) - 1ull)) << lg) | k : o;
+        pr = A ? sh.rank[o] | k : o;
         const TrialCtx c{key_of(o), 0.0, sh.tcut[o], 0.0, sh.cfac[o], sh.cycle[o] + k};
         QuarkMasses om{0.0, 0.0, 0.0, 0.0, 0.0};
         if constexpr (kMassive) om = QuarkMasses{0.0, 0.0, 0.0, sh.mc[o], sh.mb[o]};
-        const Ends<kMassive> E = load_ends<kCached, kMassive>(c, slots, sh.slot[o], (int)i, e_lo, e_hi, ec, wave_col + o,
+        const Ends<kMassive> E = load_ends<kCached, kMassive>(c, slots, sh.slot[o], (int)i, e_lo, e_hi, ec, o,
                                                               kPre && pre, pw, om);
         uint32_t nt = 0, ne = 0;
         item_bounds(c, (int)i, E, e_lo, e_hi, low, nt, ne);
@@ -745,7 +787,7 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
         const uint32_t hi = old > low.m ? old : low.m;
         atomicMin(&sh.second[pr], hi < low.m2 ? hi : low.m2);
       }
-      if (kPre) pre = prefetch_entry(sh.item, list_pos(r0 + 64 + lane, vg, n_g, lg), n_g + n_q, kItems, ec, wave_col, pw);
+      if (kPre) pre = prefetch_entry(sh.item, list_pos(r0 + 64 + lane, vg, n_g, lg), n_g + n_q, kItems, ec, pw);
       if constexpr (!kRedraw) {
         __syncthreads();  // one wave: the atomics above are done
         if (low.m != kNoBound && sh.best[pr] == key) {
@@ -780,7 +822,7 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
     double u;
     if constexpr (kRedraw) {
       const int i = (int)(idx >> 14), k = (int)((idx >> 4) & 1023u);
-      const Ends<kMassive> E = load_ends<kCached, kMassive>(c, slots, sh.slot[o], i, 0, 1, ec, wave_col + o, false,
+      const Ends<kMassive> E = load_ends<kCached, kMassive>(c, slots, sh.slot[o], i, 0, 1, ec, o, false,
                                                             Ent5{}, qm);
       const bool e1 = k == E.k[1];
       u = trial_uniform(c.key, cyc, i, k, W);
@@ -801,7 +843,7 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
       QuarkMasses om{0.0, 0.0, 0.0, 0.0, 0.0};
       if constexpr (kMassive) om = QuarkMasses{0.0, 0.0, 0.0, sh.mc[o], sh.mb[o]};
       v = -INFINITY;
-      idx = exact_winner<kCached, kMassive>(c, slots, sh.slot[o], n_o, ec, wave_col + o, om, v, ca, cb);
+      idx = exact_winner<kCached, kMassive>(c, slots, sh.slot[o], n_o, ec, o, om, v, ca, cb);
     }
     return idx;
   };
@@ -810,7 +852,7 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
     // one lane per (event, cycle) pair: the pair's scale, cutoff and veto;
     // its outcome goes into `second`, above it the winner
     const uint32_t n_pairs = (uint32_t)__popcll(tmask) << lg;
-    const uint32_t o = lane < n_pairs ? select64(tmask, lane >> lg) : lane;  // the pair's event
+    const uint32_t o = lane < n_pairs ? sh.ranked[lane >> lg] : lane;  // the pair's event
     const double asmax = __shfl(s.asmax, (int)o);  // its trial alpha_s
     const int n_o = __shfl(s.n, (int)o);
     const uint32_t rk = lane >> lg, k = lane & (K - 1u), cyc = sh.cycle[o] + k;
@@ -859,9 +901,8 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
     // each event takes its pairs in cycle order up to the first that ends
     // the sequence: the steps of a cycle-by-cycle decision
     if (trial) {
-      const uint32_t rk = (uint32_t)__popcll(tmask & ((1ull << lane) - 1ull));
       for (uint32_t k = 0; k < K; ++k) {
-        const uint32_t pr = (rk << lg) | k;
+        const uint32_t pr = sh.rank[lane] | k;
         const uint32_t f = sh.second[pr] & 63u;
         if (f == kPairLimit) {
           s.status = kCycleLimitHit;
@@ -941,13 +982,15 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
 }
 
 // Waves that a launch of the flattened kernels spreads its events over: the
-// resident ones of 256 compute units (sixteen blocks per CU up to 64 partons
-// per record, fourteen up to 128, eleven above: LDS), twelve with quark masses
-// (three per SIMD; against one per SIMD, calls of 5000 events 393 and 372 us,
-// 20000 566 and 618, 60000 875 and 978).
-static uint32_t flat_waves(uint32_t cap, bool massive) {
+// resident ones of 256 compute units: sixteen blocks per CU up to 128 partons
+// per record, eleven above (LDS); twelve with quark masses or in the serving
+// epochs' staging slots, eight with both (registers).  With quark masses,
+// twelve against four per CU: calls of 5000 events 393 and 372 us, 20000 566
+// and 618, 60000 875 and 978.
+static uint32_t flat_waves(uint32_t cap, bool massive, bool in_place) {
   constexpr uint32_t kCUs = 256;
-  return kCUs * (massive ? 12u : cap <= 64 ? 16u : cap <= kFourMaxCap ? 14u : 11u);
+  if (massive) return kCUs * (in_place ? 12u : 8u);
+  return kCUs * (cap > kFourMaxCap ? 11u : in_place ? 16u : 12u);
 }
 
 // Events that a wave holds at once.  A small launch is bound by the chain of
@@ -967,7 +1010,7 @@ static uint32_t events_per_wave(uint64_t n, uint64_t waves) {
 // consecutive events of the batch (already started by k_me) from start to
 // cutoff, with no refill; finished lanes only stop contributing trial work.
 // kFour (massless, at most 128 partons): four resident waves per SIMD (128
-// registers, a few spilled; 8.7 + 1 KB of LDS), the trial constants
+// registers, a few spilled; 8.1 KB of LDS and the masks), the trial constants
 // reloaded from LDS after the rounds (kAhead); otherwise three waves, the
 // massive instantiation reloading them too to fit without spilling.
 template <bool kMassive, bool kOne, bool kFour = false>
@@ -1009,11 +1052,11 @@ void launch_shower_plain_flat(const Records& r, const Summary& s, const EventInp
                               uint64_t* cache, hipStream_t st) {
   if (!n) return;
   const EndCache ec{cache, r.cap};
-  const uint32_t pw = events_per_wave(n, flat_waves(r.cap, in.massive != 0));
+  const uint32_t pw = events_per_wave(n, flat_waves(r.cap, in.massive != 0, true));
   const dim3 g((n + pw - 1) / pw), b(64);
   const size_t lds = flat_lds_bytes(r.cap);
   // Massless events: the single-request LDS layout; up to 128 partons per
-  // record it leaves room for 3.5 to 4 blocks per SIMD, which the four-wave
+  // record it leaves room for four blocks per SIMD, which the four-wave
   // build fills with 128 registers by reloading its trial constants from
   // LDS after the rounds (and loading the next round's cache entries
   // ahead); above that the masks make LDS the bound and the three-wave
@@ -1031,8 +1074,8 @@ void launch_shower_plain_flat(const Records& r, const Summary& s, const EventInp
 // kCached: A.cache holds an end cache per lane (always when in place; the
 // serving epochs' staging slots have one unless it could not be allocated).
 // In place (one request, kOne): four resident waves per SIMD for massless
-// events with at most 128 partons (kFour: 128 registers, no spills; LDS
-// allows 3.5 at 128), three with more partons or with quark masses.  Three for
+// events with at most 128 partons (kFour: 128 registers, no spills), three
+// with more partons or with quark masses.  Three for
 // massless events in the serving epochs' cached staging slots (a few
 // spilled registers, outweighed by the third wave: 4000 requests/s of the
 // serving mix keep p99 below 40 ms instead of 80); two otherwise.
@@ -1072,7 +1115,7 @@ __global__ void __launch_bounds__(64, kFour ? 4 : (kInPlace || (kCached && !kMas
       busy = true;
     }
     if (!__any(busy)) break;
-    flat_cycle<kCached, kMassive, kInPlace, kCached, kOne>(
+    flat_cycle<kCached, kMassive, kInPlace || kCached, kCached, kOne>(
         sh, one, flat_gmask, words, s, busy, pend, pd, A.slots, slot, A.cache, L - lane, lane, A.reqs[req].qm);
     if (busy && s.status != kRunning) {
       if constexpr (!kRegW) s.wsh = sh.wsh[lane];
@@ -1215,9 +1258,10 @@ const void* persistent_kernel(uint32_t mapping, bool in_place, bool massive, boo
 
 uint32_t persistent_block(uint32_t mapping, uint32_t block) { return mapping == kMapFlat ? 64u : block; }
 
-uint32_t persistent_per_wave(uint64_t total, uint64_t lanes, uint32_t mapping, uint32_t cap, bool massive) {
+uint32_t persistent_per_wave(uint64_t total, uint64_t lanes, uint32_t mapping, bool in_place, uint32_t cap,
+                             bool massive) {
   if (mapping != kMapFlat) return 64;
-  return events_per_wave(total, std::min<uint64_t>(lanes / 64, flat_waves(cap, massive)));
+  return events_per_wave(total, std::min<uint64_t>(lanes / 64, flat_waves(cap, massive, in_place)));
 }
 
 // Blocks of a persistent launch: no more waves than the first claims serve.
@@ -1300,7 +1344,7 @@ vsh_status run_batch(vsh_ctx* ctx, const vsh_request* req, uint64_t first_idx, u
   A.next = L.counter;
   A.threshold = ctx->tuned.refill_threshold;
   A.period = ctx->tuned.refill_period;
-  A.per_wave = persistent_per_wave(n, lanes, mapping, cap, request_massive(*req) != 0);
+  A.per_wave = persistent_per_wave(n, lanes, mapping, true, cap, request_massive(*req) != 0);
   A.cache = L.cache;
   EventInputs in{};
   in.ecm = ecm_dev;
@@ -1415,7 +1459,7 @@ vsh_status generate_persistent(vsh_ctx* ctx, const vsh_request* req, vsh_result*
     A.next = L.counter;
     A.threshold = ctx->tuned.refill_threshold;
     A.period = ctx->tuned.refill_period;
-    A.per_wave = persistent_per_wave(n, lanes, ctx->tuned.mapping, cap, in.massive != 0);
+    A.per_wave = persistent_per_wave(n, lanes, ctx->tuned.mapping, true, cap, in.massive != 0);
     A.cache = L.cache;
     (void)hipEventRecord(ctx->ev[1], st);
     launch_persistent(A, lanes, ctx->tuned.pers_block, ctx->tuned.mapping, true, in.massive != 0, st);

@@ -81,7 +81,8 @@ struct BatchLayout {
 };
 
 // events a wave of a persistent launch over `total` events holds at once
-uint32_t persistent_per_wave(uint64_t total, uint64_t lanes, uint32_t mapping, uint32_t cap, bool massive);
+uint32_t persistent_per_wave(uint64_t total, uint64_t lanes, uint32_t mapping, bool in_place, uint32_t cap,
+                             bool massive);
 uint64_t slots_bytes(uint64_t lanes, uint32_t cap);
 uint64_t request_out_bytes(uint64_t n, uint32_t cap, bool partners);
 uint64_t obs_scratch_bytes(uint64_t n, uint32_t cap);
