@@ -358,19 +358,22 @@ void tally_fields(ResultBox* b, const int32_t* si0, uint64_t stride, const doubl
 // add up the counts and the histogram, and with summaries place the fields in
 // the result: in its own pinned block, the counts made from the span's head
 // while the rest arrives, or through the staging buffer.  *n_host (optional)
-// points at the parton counts.
+// points at the parton counts.  direct: the kernels wrote the fields into the
+// pinned block themselves, only the histogram is copied.
 vsh_status copy_back_chunk(vsh_ctx* ctx, hipStream_t st, const double* dev_hist, const Summary& dev_sum,
                            uint64_t count, uint32_t flags, ResultBox* box, uint64_t first_idx,
-                           const int32_t** n_host) {
+                           const int32_t** n_host, bool direct) {
   static_assert(kSiStatus == 1 && kSiEnds == kNSumI - 1 && kSdW == 0, "the counts read the span's head");
   const ResultSpan sp(count);
   const char* dev = reinterpret_cast<const char*>(dev_hist);
-  if (reinterpret_cast<const char*>(dev_sum.i) != dev + sp.i || reinterpret_cast<const char*>(dev_sum.d) != dev + sp.d ||
-      reinterpret_cast<const char*>(dev_sum.hash) != dev + sp.hash || dev_sum.stride != count) {
+  const bool span = reinterpret_cast<const char*>(dev_sum.i) == dev + sp.i &&
+                    reinterpret_cast<const char*>(dev_sum.d) == dev + sp.d &&
+                    reinterpret_cast<const char*>(dev_sum.hash) == dev + sp.hash && dev_sum.stride == count;
+  if (direct ? !box->sum_block.ptr : !span) {
     set_error(ctx, "results are not in one span (internal error)");
     return VSH_E_INTERNAL;
   }
-  const uint64_t bytes = (flags & VSH_SUMMARY) ? sp.bytes : sp.head;
+  const uint64_t bytes = direct ? kHistDoubles * 8 : (flags & VSH_SUMMARY) ? sp.bytes : sp.head;
   char* host = static_cast<char*>(box->sum_block.ptr);
   if (!host) {
     vsh_status rc = ctx->stage.reserve(ctx, bytes);

@@ -149,7 +149,7 @@ void tally_fields(ResultBox* b, const int32_t* si0, uint64_t stride, const doubl
 ResultBox* new_call_result(vsh_ctx* ctx, const vsh_request* req, bool whole);
 vsh_status copy_back_chunk(vsh_ctx* ctx, hipStream_t st, const double* dev_hist, const Summary& dev_sum,
                            uint64_t count, uint32_t flags, ResultBox* box, uint64_t first_idx,
-                           const int32_t** n_host);
+                           const int32_t** n_host, bool direct = false);
 uint64_t plain_layout_bytes(uint64_t stride, uint32_t cap, bool massive);
 PlainLayout carve_plain(void* base, uint64_t n, uint32_t cap, bool massive);
 
