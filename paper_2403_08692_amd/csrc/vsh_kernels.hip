@@ -314,6 +314,14 @@ __global__ void __launch_bounds__(256) k_obs_scatter(ObsArgs<kMulti> A) {
   });
 }
 
+// Orders a wave's LDS accesses on either side (the LDS takes them in program
+// order; the compiler may not move them across).
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 template <bool kMassive>
 __device__ __forceinline__ void window_events(const Records& r, const Summary& sm, const EventInputs& in,
                                               const Scratch& sc, uint32_t n, double* __restrict__ hist, uint32_t blk,
@@ -333,37 +341,66 @@ __device__ __forceinline__ void window_events(const Records& r, const Summary& s
   // sit at the front of perm, largest first.
   const uint64_t n_big = sc.threshold <= cap ? sc.cnt[cap - sc.threshold] : 0u;  // done by k_obs_group
   const uint64_t n_mid = (uint32_t)kObsRegSlots < cap ? sc.cnt[cap - (kObsRegSlots + 1)] : n_big;
-  // events of at most kObsRegSlots partons, in windows of 256 consecutive
-  // events (coalesced counts; the records of a window share cache lines),
-  // each window ordered by parton count in LDS so that a wave's events have
-  // nearly the same size and its loops stop at the wave's largest
-  __shared__ uint16_t order[256];
-  __shared__ uint32_t bin_n[kObsRegSlots + 2];  // events per parton count, then the others
-  for (uint64_t w0 = (uint64_t)blk * 256; w0 < n; w0 += (uint64_t)grid * 256) {
-    const uint64_t e_own = w0 + threadIdx.x;
-    const int np_own = e_own < n ? sm.i[kSiN * sm.stride + e_own] : kObsRegSlots + 1;
-    const bool mine = np_own <= kObsRegSlots && (uint32_t)np_own < sc.threshold;  // else the lane groups
-    const int bin = mine ? np_own : kObsRegSlots + 1;
-    if (threadIdx.x < kObsRegSlots + 2) bin_n[threadIdx.x] = 0;
-    __syncthreads();
-    const uint32_t rank = atomicAdd(&bin_n[bin], 1u);
-    __syncthreads();
-    uint32_t start = 0;
-    for (int b = 0; b < bin; ++b) start += bin_n[b];
-    order[start + rank] = (uint16_t)threadIdx.x;
-    __syncthreads();
-    const uint64_t e = w0 + order[threadIdx.x];
-    const int np = e < n ? sm.i[kSiN * sm.stride + e] : kObsRegSlots + 1;
-    const bool ok = np <= kObsRegSlots && (uint32_t)np < sc.threshold;
-    const int wmax = (int)wave_max(ok ? (uint32_t)np : 0u);
-    if (ok) {
-      const int status = sm.i[kSiStatus * sm.stride + e];
-      const ObsOut o = reg_observables<kObsRegSlots, kMassive>(r, e, np, wmax, in.ecm_of(e), status, in);
-      if (o.status == kDone) hist_fill(lh, o, sm.d[kSdW * sm.stride + e], sm.d[kSdCos * sm.stride + e], fx);
-      for (int h = 0; h < 7; ++h) sm.d[(kSdY23 + h) * sm.stride + e] = o.v[h];
-      sm.i[kSiStatus * sm.stride + e] = o.status;
+  // events of at most kObsRegSlots partons, in windows of consecutive events
+  // (coalesced counts; the records of a window share cache lines), each
+  // window ordered by parton count in LDS so that the 64 events a wave takes
+  // at a time have nearly the same size and its loops stop at the largest.
+  // A grid that covers the events has a window of 256 per block, 64 for each
+  // wave.  A smaller one has windows of up to 256 per wave, which works
+  // through all of its window: shared out over the block, the waves with the
+  // small events waited for the one with the largest (36% of the issue slots
+  // used; k_obs on 10^6 LEP events 427 and 304 us, 3 10^6 of mixed energies
+  // 1197 and 711).
+  constexpr uint32_t kWaves = 4;  // per block
+  __shared__ uint8_t orders[kWaves][256];
+  __shared__ uint32_t bins_n[kWaves][kObsRegSlots + 2];  // events per parton count, then the others
+  const uint32_t chunks = (uint32_t)std::min<uint64_t>(4, ((uint64_t)n + grid * 256ull - 1) / (grid * 256ull));
+  const bool shared = chunks == 1;  // one window, and one pass of the loop, for the block
+  const uint32_t wave = shared ? 0 : threadIdx.x / 64, lane = shared ? threadIdx.x : threadIdx.x % 64;
+  const uint32_t span = shared ? 256 : 64 * chunks, teams = shared ? 1 : kWaves;
+  uint8_t* order = orders[wave];
+  uint32_t* bin_n = bins_n[wave];
+  auto fence = [&] {
+    if (shared) __syncthreads();
+    else wave_fence();
+  };
+  for (uint64_t w0 = ((uint64_t)blk * teams + wave) * span; w0 < n; w0 += (uint64_t)grid * teams * span) {
+    if (lane < kObsRegSlots + 2) bin_n[lane] = 0;
+    fence();
+    uint32_t bin[4], rank[4];
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+      bin[q] = rank[q] = 0;
+      if (q >= chunks) continue;
+      const uint64_t e_own = w0 + q * 64 + lane;
+      const int np_own = e_own < n ? sm.i[kSiN * sm.stride + e_own] : kObsRegSlots + 1;
+      const bool mine = np_own <= kObsRegSlots && (uint32_t)np_own < sc.threshold;  // else the lane groups
+      bin[q] = mine ? (uint32_t)np_own : kObsRegSlots + 1;
+      rank[q] = atomicAdd(&bin_n[bin[q]], 1u);
     }
-    __syncthreads();  // order and bin_n serve the next window
+    fence();
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+      if (q >= chunks) continue;
+      uint32_t start = 0;
+      for (uint32_t b = 0; b < bin[q]; ++b) start += bin_n[b];
+      order[start + rank[q]] = (uint8_t)(q * 64 + lane);
+    }
+    fence();
+    for (uint32_t q = 0; q < chunks; ++q) {
+      const uint64_t e = w0 + order[q * 64 + lane];
+      const int np = e < n ? sm.i[kSiN * sm.stride + e] : kObsRegSlots + 1;
+      const bool ok = np <= kObsRegSlots && (uint32_t)np < sc.threshold;
+      const int wmax = (int)wave_max(ok ? (uint32_t)np : 0u);
+      if (ok) {
+        const int status = sm.i[kSiStatus * sm.stride + e];
+        const ObsOut o = reg_observables<kObsRegSlots, kMassive>(r, e, np, wmax, in.ecm_of(e), status, in);
+        if (o.status == kDone) hist_fill(lh, o, sm.d[kSdW * sm.stride + e], sm.d[kSdCos * sm.stride + e], fx);
+        for (int h = 0; h < 7; ++h) sm.d[(kSdY23 + h) * sm.stride + e] = o.v[h];
+        sm.i[kSiStatus * sm.stride + e] = o.status;
+      }
+    }
+    fence();  // order and bin_n serve the next window
   }
   // the rest below the wave threshold, sorted by size, through the scratch
   for (uint64_t q = n_big + t; q < n_mid; q += step) {
@@ -1121,11 +1158,17 @@ static void launch_general(const ObsArgs<kMulti>& A, const uint32_t* blocks, uin
   hipLaunchKernelGGL(k_hist_finalize<kMulti>, dim3(blocks[kObsStageSum]), b256, 0, st, A);
 }
 
-static void job_blocks(const ObsJob& j, uint32_t most_groups, uint32_t* blocks) {
+// `all`: the events of every job of the launch.  k_obs takes 64 events per wave
+// up to two rounds of the 2048 resident waves, then 192 or 256 ordered together
+// (window_events derives the number from the grid).  The whole pass, 64 per
+// wave and more: 140000 events at 200 GeV 310 and 340 us, 262144 at LEP 219
+// and 203, 300000 261 and 235.
+static void job_blocks(const ObsJob& j, uint64_t all, uint32_t most_groups, uint32_t* blocks) {
+  const uint64_t per = 256 * (all <= 262144 ? 1 : std::min<uint64_t>(4, (all + 131071) / 131072));
   blocks[kObsStageHist] = blocks_for(std::max<uint32_t>(j.r.cap + 1, kHistCopies * kHistDoubles), 256);
   blocks[kObsStageSort] = blocks_for(j.n, 256u * kObsSortPer);
   blocks[kObsStageScan] = 1;
-  blocks[kObsStageWindow] = (uint32_t)(std::min<uint64_t>(j.sc.stride, ((uint64_t)j.n + 255) / 256 * 256) / 256);
+  blocks[kObsStageWindow] = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(j.sc.stride / 256, (j.n + per - 1) / per));
   blocks[kObsStageGroup] = std::min<uint32_t>(j.n, most_groups);
   blocks[kObsStageSum] = kHistBlocks;
 }
@@ -1136,7 +1179,7 @@ void launch_obs(const Records& r, const Summary& s, const EventInputs& in, const
   const bool fixed = in.fixed_hist != 0, massive = in.massive != 0;
   const ObsArgs<false> A{ObsJob{r, s, in, sc, hist, n, {}}};
   uint32_t blocks[kObsStages];
-  job_blocks(A.job, kObsWaveBlocks, blocks);
+  job_blocks(A.job, n, kObsWaveBlocks, blocks);
   ObsFewLaunch few;
   if (obs_few_launch(n, r.cap, fixed, &few)) {
     const dim3 b256(256);
@@ -1163,9 +1206,11 @@ Scratch carve_obs_job(char*& p, uint64_t n, uint32_t cap) {
 
 void plan_obs_jobs(ObsJob* jobs, uint32_t count, ObsPlan* plan) {
   *plan = ObsPlan{};
+  uint64_t all = 0;
+  for (uint32_t q = 0; q < count; ++q) all += jobs[q].n;
   for (uint32_t q = 0; q < count; ++q) {
     uint32_t blocks[kObsStages];
-    job_blocks(jobs[q], kObsJobGroupBlocks, blocks);
+    job_blocks(jobs[q], all, kObsJobGroupBlocks, blocks);
     for (int k = 0; k < kObsStages; ++k) {
       jobs[q].at[k] = plan->blocks[k];
       plan->blocks[k] += blocks[k];
