@@ -153,8 +153,7 @@ vsh_status copy_back_chunk(vsh_ctx* ctx, hipStream_t st, const double* dev_hist,
 uint64_t plain_layout_bytes(uint64_t stride, uint32_t cap, bool massive);
 PlainLayout carve_plain(void* base, uint64_t n, uint32_t cap, bool massive);
 
-vsh_status gather_records(vsh_ctx* ctx, const Records& r, const int32_t* n_dev, const int32_t* n_host,
-                          uint64_t count, ResultBox* box);
+vsh_status gather_records(vsh_ctx* ctx, const Records& r, const int32_t* n_host, uint64_t count, ResultBox* box);
 
 vsh_status generate_plain(vsh_ctx* ctx, const vsh_request* req, const uint64_t* offsets, const double* p,
                           const int8_t* pid, const uint16_t* col, const uint16_t* acol, vsh_result** out);

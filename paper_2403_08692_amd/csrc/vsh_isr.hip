@@ -497,7 +497,7 @@ extern "C" vsh_status vsh_generate_isr(vsh_ctx* ctx, const vsh_request* req, dou
     float ms = 0.0f;
     if (hipEventElapsedTime(&ms, ctx->ev[1], ctx->ev[2]) == hipSuccess) t_sh += ms;
     if (req->flags & VSH_RECORDS) {
-      rc = gather_records(ctx, r, sm.i + kSiN * count, n_host, count, box);
+      rc = gather_records(ctx, r, n_host, count, box);
       if (rc) {
         delete box;
         return rc;

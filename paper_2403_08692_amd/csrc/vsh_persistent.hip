@@ -1479,7 +1479,7 @@ vsh_status generate_persistent(vsh_ctx* ctx, const vsh_request* req, vsh_result*
     if (hipEventElapsedTime(&ms, ctx->ev[1], ctx->ev[2]) == hipSuccess) t_sh += ms;
     if (hipEventElapsedTime(&ms, ctx->ev[2], ctx->ev[3]) == hipSuccess) t_obs += ms;
     if (req->flags & VSH_RECORDS) {
-      vsh_status rc2 = gather_records(ctx, L.buf.out, L.buf.sum.i + kSiN * n, n_host, n, box);
+      vsh_status rc2 = gather_records(ctx, L.buf.out, n_host, n, box);
       if (rc2) {
         delete box;
         return rc2;
