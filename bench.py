@@ -36,29 +36,30 @@ VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12  # 39.32 T lane-operations/s
 # VALU issue-slot costs per lane of the arithmetic building blocks, from the
 # gfx950 assembly of this library's own build (costmodel/isa_costs.py; a CPU
 # test keeps this table equal to what the probe measures).
-COST = {"philox": 99, "unit": 3, "log": 97, "log_fast": 38, "exp": 41, "sqrt": 21, "div": 11, "sincos": 162}
+COST = {"philox": 99, "unit": 3, "bound": 8, "log": 97, "log_fast": 38, "exp": 41, "sqrt": 21, "div": 11,
+        "sincos": 162}
 # The FP64 instructions alone of the same blocks (isa_costs.measure(fp64=True)):
 # the FP64 roofline counts these, and the formula arithmetic of the cost
 # model below (dot products, the dipole map, the matrix element), which is
 # FP64; Philox's integer work is left out.
-COST_F64 = {"philox": 0, "unit": 1, "log": 76, "log_fast": 33, "exp": 19, "sqrt": 14, "div": 11, "sincos": 117}
+COST_F64 = {"philox": 0, "unit": 1, "bound": 2, "log": 76, "log_fast": 33, "exp": 19, "sqrt": 14, "div": 11, "sincos": 117}
 
 
 def algorithmic_ops(n_events, ends, trials, cycles, emissions, cost=None):
     """VALU lane-operations the veto algorithm needs for a batch, under the
     random-number contract (one Philox block per two kernel trials of a
     dipole end).  Per active dipole end and cycle: per kernel trial its
-    uniform, and a log and a divide per trial scale (a gluon end's five
-    g -> f fbar trials share one coefficient, so only the largest of their
-    uniforms needs the log).  An end's dipole mass, z limits, overestimate
+    uniform, and a single-precision bound of each trial scale (a gluon end's
+    five g -> f fbar trials share one coefficient, so only the largest of
+    their uniforms needs one).  An end's dipole mass, z limits, overestimate
     integral and coefficients (a divide, a square root and a log) change only
     when an emission touches the end: they are charged for the two ends of
     the initial dipole and for at most eight ends per emission (the new
     parton's two, the emitter's and the spectator's towards it, and those of
-    their other colour partners).  Per cycle with a winner: the accept block,
-    t = exp(ln t), z from the overestimate (one exp), y, alpha_s from ln t,
-    kernel over overestimate.  Per accepted emission: the azimuth block,
-    sincos and the dipole map.  Per event: the matrix element and the
+    their other colour partners).  Per cycle with a winner: its exact scale
+    (a log and a multiply), the accept block, t = exp(ln t), z from the
+    overestimate (one exp), y, alpha_s from ln t, kernel over overestimate.
+    Per accepted emission: the azimuth block, sincos and the dipole map.  Per event: the matrix element and the
     shower's start-up.  cost: the per-block table (COST, or COST_F64 for the
     FP64 work alone)."""
     g_ends = (trials - ends) / 5.0      # gluon ends make 6 trials, quark ends 1
@@ -67,9 +68,9 @@ def algorithmic_ops(n_events, ends, trials, cycles, emissions, cost=None):
     c = COST if cost is None else cost
     end_setup = 8 + c["div"] + c["sqrt"] + c["log_fast"] + c["div"] + 6
     setups = 2 * n_events + 8 * emissions
-    per_q_end = c["philox"] + c["unit"] + c["log_fast"] + c["div"] + 3
-    per_g_end = 3 * c["philox"] + 6 * c["unit"] + 2 * c["log_fast"] + 2 * c["div"] + 12
-    per_winner = 2 * c["exp"] + c["philox"] + 2 * c["unit"] + 6 * c["div"] + 25
+    per_q_end = c["philox"] + c["unit"] + c["bound"] + 3
+    per_g_end = 3 * c["philox"] + 6 * c["unit"] + 2 * c["bound"] + 12
+    per_winner = c["log_fast"] + 1 + 2 * c["exp"] + c["philox"] + 2 * c["unit"] + 6 * c["div"] + 25
     per_emission = c["philox"] + c["unit"] + c["sincos"] + 3 * c["sqrt"] + 8 * c["div"] + 140
     per_event = 2 * c["philox"] + 3 * c["unit"] + c["sincos"] + c["sqrt"] + 3 * c["div"] + 60 + 2 * c["log_fast"]
     return (q_ends * per_q_end + g_ends * per_g_end + setups * end_setup + winners * per_winner +
@@ -606,7 +607,7 @@ def main():
                                                   tuning=tuned),
                                "plain": time_form(ctx, P, torch, st_w, st_w.n_events, "plain", 3)}
         # the initial-state shower with the stand-in parton density: Drell-Yan at 1960 GeV
-        # through vsh_generate_isr (one lane per event; host results: histograms and counts)
+        # through vsh_generate_isr (host results: histograms and counts)
         ctx.generate_isr(1 << 16, summary=False)
         t0 = time.perf_counter()
         for _ in range(3):

@@ -252,7 +252,7 @@ vsh_status vsh_shower_records(vsh_ctx *ctx, const vsh_request *req, const uint64
    as vsh_generate's (flavour +f with the quark from beam A, -f from B).
    Histograms: 0 log10(p_T,V / GeV) [-1, 3], 1 y_V [-5, 5], 2 emitted gluons
    [0, 50], 3 log10(p_T / GeV) of the hardest gluon [-1, 3] (rows 4-7 unused;
-   hist_lo / hist_hi give the ranges).  One lane per event, plain form.
+   hist_lo / hist_hi give the ranges).  Plain form, 2 to 16 lanes per event.
    Errors: those of vsh_generate, and VSH_E_INVALID for flags other than
    VSH_SUMMARY | VSH_RECORDS, per-event arrays, a cycle limit, t_over or
    masses, max_partons < 3, sqrt_s_hadron <= Q, or t_cut >= Q^2 / 4. */
@@ -319,8 +319,8 @@ typedef struct {
   uint32_t mapping;          /* persistent form: 0 = one lane per event,
                                 1 = each cycle's trials spread over the wave's lanes   */
   uint32_t waves_per_cu;     /* persistent waves launched per compute unit, 1..16 (the
-                                flattened kernel keeps 8 resident per CU; later waves
-                                start as earlier ones exit)                           */
+                                flattened kernels keep 8 to 16 resident per CU; later
+                                waves start as earlier ones exit)                     */
   uint32_t block;            /* threads per block of mapping 0: 64, 128 or 256          */
   uint32_t refill_threshold; /* idle lanes a wave waits for before refilling, 1..64;
                                 batches evolve in their output records and claim whole
@@ -328,8 +328,9 @@ typedef struct {
   uint32_t refill_period;    /* veto cycles between refill checks, 1..64               */
   uint32_t plain_waves;      /* register budget of the plain kernel, as resident waves
                                 per SIMD: 2, 3 or 4 (more waves, fewer registers)     */
-  uint32_t plain_mapping;    /* plain form: 0 = one lane per event, 1 = each wave's 64
-                                events with their cycle's trials spread over its lanes */
+  uint32_t plain_mapping;    /* plain form: 0 = one lane per event, 1 = each wave's (up
+                                to 64) events with their cycle's trials spread over
+                                its lanes                                             */
   uint32_t from_cache;       /* set by vsh_autotune: 1 when the settings came from the
                                 context's tuner cache file (nothing was timed)       */
 } vsh_tuning;

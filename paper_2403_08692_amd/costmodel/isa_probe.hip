@@ -6,6 +6,7 @@
 
 #include "../csrc/vsh_device.hpp"
 #include "../csrc/vsh_math.hpp"
+#include "../csrc/vsh_shower.hpp"
 
 using namespace vsh;
 
@@ -23,6 +24,7 @@ PROBE_D(add, x + y)
 PROBE_D(log, log(x))
 PROBE_D(log_fast, log_series(x))
 PROBE_D(exp, exp(x))
+PROBE_D(bound, __hiloint2double((int)trial_bound(x, (float)y), 0))
 PROBE_D(pow, pow(x, y))
 PROBE_D(sqrt, sqrt(x))
 PROBE_D(div, x / y)
