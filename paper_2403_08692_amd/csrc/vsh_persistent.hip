@@ -1016,7 +1016,11 @@ static uint32_t events_per_wave(uint64_t n, uint64_t waves) {
 template <bool kMassive, bool kOne, bool kFour = false>
 __global__ void __launch_bounds__(64, kFour ? 4 : 3)
     k_shower_plain_flat(Records r, Summary sm, EventInputs in, uint32_t n, EndCache ec, uint32_t per_wave) {
-  __shared__ FlatShared<kMassive, kOne, kFour> sh;
+  // above 128 partons: the weight in a register and the shorter list, for
+  // twelve blocks per CU instead of eleven at 256 (500 GeV, 10^6 events: 18.9 ->
+  // 18.1 ms)
+  constexpr bool kRegW = kOne && !kFour && !kMassive;
+  __shared__ FlatShared<kMassive, kOne, kFour, kRegW> sh;
   const OneRequest one{in.seed, in.first, in.cycle_limit};
   const uint32_t lane = threadIdx.x;
   const uint32_t words = mask_words(r.cap);
@@ -1030,14 +1034,14 @@ __global__ void __launch_bounds__(64, kFour ? 4 : 3)
     init_state(s, r, e, make_keyed(in.seed, in.first + e), in.ecm_of(e), in.tcut_of(e), in.t_over,
                sm.i[kSiN * sm.stride + e], (int)r.cap);
     if constexpr (!kOne) sh.climit[lane] = in.cycle_limit;
-    sh.wsh[lane] = 1.0;
+    if constexpr (!kRegW) sh.wsh[lane] = 1.0;
     mask_init(flat_gmask + (uint64_t)lane * words, flat_gmask + (uint64_t)(64 + lane) * words, words, r, e, s.n);
   }
   while (__any(busy)) {
     flat_cycle<true, kMassive, kMassive || kFour, true, kOne>(sh, one, flat_gmask, words, s, busy, pend, pd, r, e, ec,
                                                           e - lane, lane, in.qm);
     if (busy && s.status != kRunning) {
-      s.wsh = sh.wsh[lane];
+      if constexpr (!kRegW) s.wsh = sh.wsh[lane];
       write_state(s, sm, e);
       busy = false;
     }
