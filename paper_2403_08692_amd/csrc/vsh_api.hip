@@ -629,7 +629,7 @@ static vsh_status run_plain_chunk(vsh_ctx* ctx, const vsh_request* req, uint64_t
   else launch_shower_plain(L.rec, L.sum, in, (uint32_t)count, ctx->tuned.plain_block, ctx->tuned.plain_waves, st);
   HIPCHK(hipGetLastError());
   HIPCHK(hipEventRecord(ctx->ev[2], st));
-  launch_obs(L.rec, L.sum, in, L.sc, (uint32_t)count, L.hist, st);
+  launch_obs(L.rec, L.sum, in, L.sc, (uint32_t)count, L.hist, nullptr, st);
   HIPCHK(hipGetLastError());
   HIPCHK(hipEventRecord(ctx->ev[3], st));
   const int32_t* n_host = nullptr;
@@ -733,12 +733,12 @@ vsh_status plain_into(vsh_ctx* ctx, const vsh_request* req, hipStream_t st, void
   if (dev_hash) sum.hash = dev_hash;
   hipEvent_t* tev = timed ? timing_slot(ctx) : nullptr;
   if (tev) (void)hipEventRecord(tev[0], st);
-  launch_me(L.rec, sum, in, (uint32_t)n, st);
+  launch_me(L.rec, sum, in, (uint32_t)n, st, L.hist);
   if (tev) (void)hipEventRecord(tev[1], st);
   if (ctx->tuned.plain_mapping == kMapFlat) launch_shower_plain_flat(L.rec, sum, in, (uint32_t)n, L.cache, st);
   else launch_shower_plain(L.rec, sum, in, (uint32_t)n, ctx->tuned.plain_block, ctx->tuned.plain_waves, st);
   if (tev) (void)hipEventRecord(tev[2], st);
-  launch_obs(L.rec, sum, in, L.sc, (uint32_t)n, dev_hist, st);
+  launch_obs(L.rec, sum, in, L.sc, (uint32_t)n, dev_hist, L.hist, st);
   if (tev) (void)hipEventRecord(tev[3], st);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return hip_fail(ctx, err, "kernel launch");

@@ -242,6 +242,12 @@ __global__ void __launch_bounds__(256) k_hist_finalize(ObsArgs<kMulti> A) {
   });
 }
 
+// A small launch's histogram (collected in the workspace) into the caller's.
+__global__ void __launch_bounds__(256) k_hist_add(const double* __restrict__ own, double* __restrict__ hist) {
+  const uint32_t a = blockIdx.x * 256 + threadIdx.x;
+  if (a < (uint32_t)kHistDoubles) hist[a] += own[a];
+}
+
 // exclusive prefix sum of nb counters, in place (one block)
 template <bool kMulti>
 __global__ void __launch_bounds__(256) k_obs_scan(ObsArgs<kMulti> A) {
@@ -954,7 +960,7 @@ __global__ void __launch_bounds__(256) k_obs_wmax(Summary sm, uint32_t n, unsign
 
 // Small launches: one wave per event of any size, in event order, a block's
 // waves (up to four) sharing an LDS histogram set, which ends in one of
-// `copies` copies of the global set (0: in the caller's histogram itself).
+// `copies` copies of the global set (0: in hist itself).
 // With few events the general path is bound by its chain of eight launches
 // and by one lane's (or sixteen lanes') scan over all of an event's planes and
 // pairs: 100 LEP events took 118 us; spread over a wave, 27 us.  `slots`: LDS
@@ -1013,8 +1019,11 @@ static size_t obs_group_lds(uint32_t g, uint32_t slots) {
 // 5003 148 and 54, 20000 166 and 95, 50000 170 and 193; at 200 GeV and t_C =
 // 0.5, 30000 events 279 and 255, 60000 283 and 467; at 500 GeV and t_C = 0.5,
 // 10000 events 598 and 340, 100000 644 and 1831.  FP64 sums go straight into
-// the caller's histogram: copies would add two launches, and the additions of
-// up to 2048 blocks do not queue up.
+// one histogram of the library's: copies would add two launches, and the
+// additions of up to 2048 blocks do not queue up.  A caller's histogram gets
+// that one added by plain loads and stores, as k_hist_finalize does (one launch
+// more): hardware FP64 atomics lose additions where the memory is not ordinary
+// device memory (pinned host or managed).
 static bool obs_few_launch(uint64_t n, uint32_t cap, bool fixed, ObsFewLaunch* out) {
   if (cap > kObsWaveMaxCap || n > (cap > 128 ? kObsFewBig : kObsFew)) return false;
   const uint32_t waves = cap <= 128 ? 4 : cap <= 256 ? 2 : 1;  // at most 30 KB of LDS
@@ -1181,7 +1190,7 @@ static void job_blocks(const ObsJob& j, uint64_t all, uint32_t most_groups, uint
 }
 
 void launch_obs(const Records& r, const Summary& s, const EventInputs& in, const Scratch& sc,
-                uint32_t n, double* hist, hipStream_t st) {
+                uint32_t n, double* hist, double* own, hipStream_t st) {
   if (!n) return;
   const bool fixed = in.fixed_hist != 0, massive = in.massive != 0;
   const ObsArgs<false> A{ObsJob{r, s, in, sc, hist, n, {}}};
@@ -1193,8 +1202,9 @@ void launch_obs(const Records& r, const Summary& s, const EventInputs& in, const
     if (few.copies) hipLaunchKernelGGL(k_obs_reset<false>, dim3(blocks[kObsStageHist]), b256, 0, st, A);
     if (fixed) hipLaunchKernelGGL(k_obs_wmax, dim3(obs_wmax_blocks(n)), b256, 0, st, s, n, sc.wmax);
     hipLaunchKernelGGL(massive ? k_obs_few<true> : k_obs_few<false>, dim3(few.blocks), dim3(few.threads), few.lds, st,
-                       r, s, in, sc, n, few.slots, few.copies, hist);
+                       r, s, in, sc, n, few.slots, few.copies, own ? own : hist);
     if (few.copies) hipLaunchKernelGGL(k_hist_finalize<false>, dim3(kHistBlocks), b256, 0, st, A);
+    else if (own) hipLaunchKernelGGL(k_hist_add, dim3(kHistBlocks), b256, 0, st, own, hist);
     return;
   }
   launch_general(A, blocks, r.cap, massive, st);

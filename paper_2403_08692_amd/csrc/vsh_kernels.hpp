@@ -160,8 +160,11 @@ void launch_me(const Records& r, const Summary& s, const EventInputs& in, uint32
                hipStream_t st, double* zero_hist = nullptr);
 void launch_shower_plain(const Records& r, const Summary& s, const EventInputs& in, uint32_t n,
                          uint32_t block, uint32_t waves, hipStream_t st);
+// hist is accumulated into.  The kernels' FP64 atomics reach only memory that
+// the library lays out: where hist is the caller's, `own` is a cleared histogram
+// of the workspace that small launches collect in first.
 void launch_obs(const Records& r, const Summary& s, const EventInputs& in, const Scratch& sc,
-                uint32_t n, double* hist, hipStream_t st);
+                uint32_t n, double* hist, double* own, hipStream_t st);
 // the pass over several requests (records of at most kObsWaveMaxCap partons,
 // each with a scratch of its own from carve_obs_job) in one set of launches
 uint64_t obs_job_bytes(uint64_t n, uint32_t cap);

@@ -574,8 +574,9 @@ __device__ __forceinline__ void hist_fill(double* lh, const ObsOut& o, double w,
 }
 
 // One LDS histogram set into this block's copy of the global one (block b:
-// copy b mod copies; with no copies FP64 sums go straight into hist): FP64
-// atomics, or integer atomics into the fixed-point cells.
+// copy b mod copies; with no copies FP64 sums go straight into hist, which is
+// then memory of the library's own): FP64 atomics, or integer atomics into the
+// fixed-point cells.
 __device__ __forceinline__ void hist_flush(const double* lh, const Scratch& sc, bool fixed, uint32_t t0,
                                            uint32_t step, uint32_t copies, double* hist) {
   const unsigned long long* lq = reinterpret_cast<const unsigned long long*>(lh);

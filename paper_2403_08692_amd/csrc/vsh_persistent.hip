@@ -1365,11 +1365,11 @@ vsh_status run_batch(vsh_ctx* ctx, const vsh_request* req, uint64_t first_idx, u
   hipEvent_t* tev = timing_slot(ctx);
   if (tev) (void)hipEventRecord(tev[0], st);
   launch_setup(L.reqs, d, L.segs, sg, L.counter, st);
-  launch_me(L.buf.out, L.buf.sum, in, (uint32_t)n, st);
+  launch_me(L.buf.out, L.buf.sum, in, (uint32_t)n, st, L.buf.hist);
   if (tev) (void)hipEventRecord(tev[1], st);
   launch_persistent(A, lanes, block, mapping, true, in.massive != 0, st);
   if (tev) (void)hipEventRecord(tev[2], st);
-  launch_obs(L.buf.out, L.buf.sum, in, L.sc, (uint32_t)n, hist, st);
+  launch_obs(L.buf.out, L.buf.sum, in, L.sc, (uint32_t)n, hist, L.buf.hist, st);
   if (tev) (void)hipEventRecord(tev[3], st);
   err = hipGetLastError();
   if (err != hipSuccess) return hip_fail(ctx, err, "kernel launch");
@@ -1468,7 +1468,7 @@ vsh_status generate_persistent(vsh_ctx* ctx, const vsh_request* req, vsh_result*
     (void)hipEventRecord(ctx->ev[1], st);
     launch_persistent(A, lanes, ctx->tuned.pers_block, ctx->tuned.mapping, true, in.massive != 0, st);
     (void)hipEventRecord(ctx->ev[2], st);
-    launch_obs(L.buf.out, L.buf.sum, in, L.sc, (uint32_t)n, L.buf.hist, st);
+    launch_obs(L.buf.out, L.buf.sum, in, L.sc, (uint32_t)n, L.buf.hist, nullptr, st);
     (void)hipEventRecord(ctx->ev[3], st);
     err = hipGetLastError();
     if (err != hipSuccess) { delete box; return hip_fail(ctx, err, "kernel launch"); }

@@ -510,7 +510,8 @@ static bool launch_epoch(vsh_ctx* ctx, ServeState& S) {
     if (!together || !joins(r)) {  // the scratch is free again when these run
       Carver sc_c(E->scratch);
       const Scratch sc = carve_scratch(sc_c, r.req.n_events, r.req.max_partons);
-      launch_obs(r.buf.out, r.buf.sum, request_inputs(r), sc, (uint32_t)r.req.n_events, r.buf.hist, E->stream);
+      launch_obs(r.buf.out, r.buf.sum, request_inputs(r), sc, (uint32_t)r.req.n_events, r.buf.hist, nullptr,
+                 E->stream);
       err = hipGetLastError();
     }
     if (err == hipSuccess) err = hipMemcpyAsync(r.h_hist, r.buf.hist, bytes, hipMemcpyDeviceToHost, E->stream);
