@@ -2,6 +2,8 @@
 // arena, request validation, the blocking and device-side generation calls
 // and the caller-supplied-start shower.  Serving lives in vsh_serve.hip.
 #include <hip/hip_runtime.h>
+#include <pthread.h>
+#include <sys/mman.h>
 
 #include <algorithm>
 #include <chrono>
@@ -189,8 +191,72 @@ void HostStage::release() {
   size = 0;
 }
 
+// The process's pools, and what becomes of their blocks in use when it forks:
+// copied to ordinary memory before, the copies moved to the blocks' addresses
+// in the child and dropped in the parent.  A block whose copy found no memory
+// is missing in the child.
+static std::mutex g_pools_mu;
+static PinnedPool* g_pools = nullptr;
+
+static void before_fork() {
+  g_pools_mu.lock();
+  for (PinnedPool* p = g_pools; p; p = p->after) {
+    p->mu.lock();
+    if (p->forked) continue;  // ordinary memory already
+    for (PinnedBlock& b : p->used) {
+      b.copy = mmap(nullptr, b.size, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS, -1, 0);
+      if (b.copy == MAP_FAILED) b.copy = nullptr;
+      else std::memcpy(b.copy, b.ptr, b.size);
+    }
+  }
+}
+
+static void after_fork_parent() {
+  for (PinnedPool* p = g_pools; p; p = p->after) {
+    for (PinnedBlock& b : p->used) {
+      if (b.copy) (void)munmap(b.copy, b.size);
+      b.copy = nullptr;
+    }
+    p->mu.unlock();
+  }
+  g_pools_mu.unlock();
+}
+
+static void after_fork_child() {
+  for (PinnedPool* p = g_pools; p; p = p->after) {
+    if (!p->forked) {
+      size_t kept = 0;  // release() unmaps what is listed
+      for (const PinnedBlock& b : p->used)
+        if (b.copy && mremap(b.copy, b.size, b.size, MREMAP_MAYMOVE | MREMAP_FIXED, b.ptr) == b.ptr)
+          p->used[kept++] = PinnedBlock{b.ptr, b.size, nullptr};
+      p->used.resize(kept);
+      p->idle.clear();
+      p->forked = true;
+    }
+    p->mu.unlock();
+  }
+  g_pools_mu.unlock();
+}
+
+PinnedPool::PinnedPool() {
+  static std::once_flag once;
+  std::call_once(once, [] { (void)pthread_atfork(before_fork, after_fork_parent, after_fork_child); });
+  std::lock_guard<std::mutex> lk(g_pools_mu);
+  after = g_pools;
+  if (after) after->before = this;
+  g_pools = this;
+}
+
+PinnedPool::~PinnedPool() {
+  std::lock_guard<std::mutex> lk(g_pools_mu);
+  (before ? before->after : g_pools) = after;
+  if (after) after->before = before;
+}
+
 PinnedBlock PinnedPool::acquire(uint64_t bytes) {
   std::lock_guard<std::mutex> lk(mu);
+  if (forked) return PinnedBlock{};
+  if (used.size() == used.capacity()) used.reserve(2 * used.size() + 16);
   size_t best = idle.size();
   for (size_t k = 0; k < idle.size(); ++k)
     if (idle[k].size >= bytes && idle[k].size <= 2 * bytes + (1u << 20) &&
@@ -199,6 +265,7 @@ PinnedBlock PinnedPool::acquire(uint64_t bytes) {
   if (best < idle.size()) {
     const PinnedBlock b = idle[best];
     idle.erase(idle.begin() + (long)best);
+    used.push_back(b);
     return b;
   }
   const uint64_t size = align_up(bytes, 65536);
@@ -217,12 +284,24 @@ PinnedBlock PinnedPool::acquire(uint64_t bytes) {
   }
   b.size = size;
   held += size;
+  used.push_back(b);
   return b;
 }
 
 void PinnedPool::release(PinnedBlock b) {
   if (!b.ptr) return;
   std::lock_guard<std::mutex> lk(mu);
+  size_t k = 0;
+  while (k < used.size() && used[k].ptr != b.ptr) ++k;
+  const bool listed = k < used.size();
+  if (listed) {
+    used[k] = used.back();
+    used.pop_back();
+  }
+  if (forked) {
+    if (listed) (void)munmap(b.ptr, b.size);
+    return;
+  }
   if (closed || idle.size() == idle.capacity()) {
     (void)hipHostFree(b.ptr);
     held -= b.size;

@@ -48,17 +48,27 @@ struct HostStage {
 // by DMA and nothing is cleared, faulted in page by page or copied again on
 // the host.  A context's blocks are kept for its later results, kMost bytes
 // of them at most, in use and idle together (acquire returns none beyond);
-// idle ones are freed with the context, one in use when its result is.
+// idle ones are freed with the context, one in use when its result is.  The
+// driver's mapping of such memory is not copied on fork; a forked child gets
+// the blocks in use as ordinary memory at the same addresses (and no new ones),
+// so that its parent's results stay readable there.
 struct PinnedBlock {
   void* ptr = nullptr;
   uint64_t size = 0;
+  void* copy = nullptr;  // while the process forks: the contents for the child
 };
 struct PinnedPool {
   static constexpr uint64_t kMost = 1ull << 30;
   std::mutex mu;
-  std::vector<PinnedBlock> idle;
+  std::vector<PinnedBlock> idle, used;
   uint64_t held = 0;  // bytes of every block, in use and idle
   bool closed = false;
+  bool forked = false;  // in a forked child: the blocks in use are ordinary memory
+  PinnedPool *before = nullptr, *after = nullptr;  // the process's pools
+  PinnedPool();
+  ~PinnedPool();
+  PinnedPool(const PinnedPool&) = delete;
+  PinnedPool& operator=(const PinnedPool&) = delete;
   PinnedBlock acquire(uint64_t bytes);
   void release(PinnedBlock b);
   void close();

@@ -1,0 +1,84 @@
+// host_paths.cpp -- one scenario of the library's host code per run (argv[1]),
+// on the fake runtime.  Exit status 0: as it should be.
+#include <sys/wait.h>
+#include <unistd.h>
+
+#include "fake_hip.hpp"
+#include "vsh.h"
+
+#define CHECK(x)                                                \
+  do {                                                          \
+    if (!(x)) {                                                 \
+      std::fprintf(stderr, "line %d: %s\n", __LINE__, #x);      \
+      _exit(1);                                                 \
+    }                                                           \
+  } while (0)
+
+static vsh_ctx* context(uint64_t budget = 0) {
+  vsh_ctx_opts o{};
+  o.mem_budget_bytes = budget;
+  vsh_ctx* c = nullptr;
+  CHECK(vsh_create(&o, &c) == VSH_OK);
+  return c;
+}
+
+static vsh_request request(uint64_t n, uint32_t flags) {
+  vsh_request r{};
+  r.n_events = n;
+  r.seed = 1;
+  r.ecm = 91.2;
+  r.t_cut = 1.0;
+  r.max_partons = 16;
+  r.flags = flags;
+  return r;
+}
+
+static vsh_result* generate(vsh_ctx* c, uint64_t n, uint32_t flags) {
+  const vsh_request r = request(n, flags);
+  vsh_result* out = nullptr;
+  CHECK(vsh_generate(c, &r, &out) == VSH_OK);
+  return out;
+}
+
+// A forked child reads, writes and frees the results that its parent holds;
+// the parent's stay as they were and its blocks go on serving.
+static void forked_child() {
+  vsh_ctx* c = context();
+  const uint64_t n = 5000;
+  vsh_result* r = generate(c, n, VSH_SUMMARY | VSH_RECORDS);
+  double* d = const_cast<double*>(r->sum_d);
+  for (uint64_t k = 0; k < VSH_NSUM_D * n; ++k) d[k] = 0.5 * (double)k;
+  for (int round = 0; round < 2; ++round) {
+    const pid_t pid = fork();
+    CHECK(pid >= 0);
+    if (pid == 0) {
+      for (uint64_t k = 0; k < VSH_NSUM_D * n; ++k) CHECK(d[k] == 0.5 * (double)k);
+      CHECK(r->rec_offsets[n] == 0);
+      d[7] = -1.0;
+      const pid_t sub = fork();  // a child's child too
+      CHECK(sub >= 0);
+      if (sub == 0) {
+        CHECK(d[7] == -1.0 && d[8] == 4.0);
+        _exit(0);
+      }
+      int s = 0;
+      CHECK(waitpid(sub, &s, 0) == sub && s == 0);
+      vsh_result_free(r);
+      _exit(0);
+    }
+    int status = 0;
+    CHECK(waitpid(pid, &status, 0) == pid);
+    CHECK(WIFEXITED(status) && WEXITSTATUS(status) == 0);
+    CHECK(d[7] == 3.5);
+  }
+  vsh_result_free(r);
+  vsh_result_free(generate(c, n, VSH_SUMMARY));
+  vsh_destroy(c);
+}
+
+int main(int argc, char** argv) {
+  const std::map<std::string, void (*)()> scenarios{{"forked child", forked_child}};
+  CHECK(argc == 2 && scenarios.count(argv[1]));
+  scenarios.at(argv[1])();
+  return 0;
+}
