@@ -468,21 +468,37 @@ static bool launch_epoch(vsh_ctx* ctx, ServeState& S) {
     together_events += r.req.n_events;
     together_bytes += obs_job_bytes(r.req.n_events, r.req.max_partons);
   }
-  const bool together = n_together >= 2 && together_events > kObsFew;
-  if (together) scratch_need = together_bytes;
-  for (uint64_t t : E->finishing) {
-    const ServeReq& r = *S.reqs[t];
-    if (!together || !joins(r))
-      scratch_need = std::max(scratch_need, obs_scratch_bytes(r.req.n_events, r.req.max_partons));
-  }
+  bool together = n_together >= 2 && together_events > kObsFew;
+  auto need = [&] {
+    scratch_need = together ? together_bytes : 0;
+    for (uint64_t t : E->finishing) {
+      const ServeReq& r = *S.reqs[t];
+      if (!together || !joins(r))
+        scratch_need = std::max(scratch_need, obs_scratch_bytes(r.req.n_events, r.req.max_partons));
+    }
+  };
+  need();
   if (err == hipSuccess && scratch_need > E->scratch_bytes) {
-    scratch_need = std::max<uint64_t>(scratch_need, 64u << 20);  // grown seldom: the free waits for the device
     if (E->scratch) (void)hipFree(E->scratch);  // this stream's earlier work has completed
     E->scratch = nullptr;
     E->scratch_bytes = 0;
-    err = hipMalloc(&E->scratch, scratch_need);
-    if (err == hipSuccess) E->scratch_bytes = scratch_need;
-    else E->scratch = nullptr;
+    auto grow = [&](uint64_t bytes) {
+      err = hipMalloc(&E->scratch, bytes);
+      if (err == hipSuccess) E->scratch_bytes = bytes;
+      else E->scratch = nullptr;
+      return err == hipSuccess;
+    };
+    // 64 MB at least, so that it grows seldom (the free waits for the device);
+    // where the device has less left, what the requests need, together and
+    // then one after the other
+    bool got = scratch_need < (64u << 20) && grow(64u << 20);
+    if (!got) got = grow(scratch_need);
+    if (!got && together) {
+      together = false;
+      need();
+      got = grow(scratch_need);
+    }
+    if (got) (void)hipGetLastError();  // of what did not fit before
   }
   if (together && err == hipSuccess) {
     char* at = E->scratch;

@@ -27,6 +27,7 @@ struct State {
   size_t dev_bytes = 0, dev_limit = (size_t)64 << 30;
   int pinned_allocs = 0;
   hipError_t last = hipSuccess;
+  bool running = false;  // events are not reached while set
   std::map<std::string, int> fail;  // call -> number of its next calls that fail
 };
 inline State& st() {
@@ -188,6 +189,7 @@ hipError_t hipEventSynchronize(hipEvent_t) {
 }
 hipError_t hipEventQuery(hipEvent_t) {
   FAKE("hipEventQuery");
+  if (fake::st().running) return hipErrorNotReady;
   fake::drain();
   return hipSuccess;
 }

@@ -76,8 +76,44 @@ static void forked_child() {
   vsh_destroy(c);
 }
 
+// A served request with little device memory left: the observables' scratch is
+// no larger than it has to be.
+static void serving_little_memory() {
+  vsh_ctx* c = context((uint64_t)256 << 20);
+  const vsh_request r = request(200, 0);
+  vsh_result* out = nullptr;
+  uint64_t t = 0;
+  CHECK(vsh_test_fail_epochs(c, 1) == VSH_OK);  // allocates an epoch's memory, ends before its scratch
+  CHECK(vsh_submit(c, &r, &t) == VSH_OK);
+  CHECK(vsh_wait(c, t, &out) == VSH_E_DEVICE);
+  {
+    fake::Lock l(fake::st().mu);
+    fake::st().dev_limit = fake::st().dev_bytes + ((size_t)2 << 20);
+  }
+  CHECK(vsh_submit(c, &r, &t) == VSH_OK);
+  CHECK(vsh_wait(c, t, &out) == VSH_OK);
+  vsh_result_free(out);
+  // many requests finished by one epoch, whose scratch together does not fit
+  {
+    fake::Lock l(fake::st().mu);
+    fake::st().running = true;
+  }
+  std::vector<uint64_t> tickets(200);
+  for (uint64_t& q : tickets) CHECK(vsh_submit(c, &r, &q) == VSH_OK);
+  {
+    fake::Lock l(fake::st().mu);
+    fake::st().running = false;
+  }
+  for (uint64_t q : tickets) {
+    CHECK(vsh_wait(c, q, &out) == VSH_OK);
+    vsh_result_free(out);
+  }
+  vsh_destroy(c);
+}
+
 int main(int argc, char** argv) {
-  const std::map<std::string, void (*)()> scenarios{{"forked child", forked_child}};
+  const std::map<std::string, void (*)()> scenarios{{"forked child", forked_child},
+                                                        {"serving, little memory", serving_little_memory}};
   CHECK(argc == 2 && scenarios.count(argv[1]));
   scenarios.at(argv[1])();
   return 0;
