@@ -369,6 +369,12 @@ ResultBox* new_call_result(vsh_ctx* ctx, const vsh_request* req, bool whole) {
   return box;
 }
 
+void drop_result(vsh_ctx* ctx, ResultBox* box) {
+  (void)hipStreamSynchronize(ctx->stream);
+  (void)hipGetLastError();  // this call's, not the next one's
+  delete box;
+}
+
 // CSR records in one span: offsets, momenta, flavours, colours, anticolours.
 struct RecordSpan {
   uint64_t p, pid, col, acol, bytes;
@@ -762,7 +768,7 @@ vsh_status generate_plain(vsh_ctx* ctx, const vsh_request* req, const uint64_t* 
     const uint64_t count = std::min(chunk, req->n_events - a);
     vsh_status rc = run_plain_chunk(ctx, req, a, count, offsets, p, pid, col, acol, box, tm);
     if (rc) {
-      delete box;
+      drop_result(ctx, box);
       return rc;
     }
   }

@@ -157,6 +157,9 @@ void finish_result(ResultBox* b);
 void tally_fields(ResultBox* b, const int32_t* si0, uint64_t stride, const double* w, uint64_t count);
 // A generating call's result; `whole`: the request is processed in one piece.
 ResultBox* new_call_result(vsh_ctx* ctx, const vsh_request* req, bool whole);
+// The result of a call that failed: given up once nothing is in flight any
+// more that may write its blocks.
+void drop_result(vsh_ctx* ctx, ResultBox* box);
 vsh_status copy_back_chunk(vsh_ctx* ctx, hipStream_t st, const double* dev_hist, const Summary& dev_sum,
                            uint64_t count, uint32_t flags, ResultBox* box, uint64_t first_idx,
                            const int32_t** n_host, bool direct = false);

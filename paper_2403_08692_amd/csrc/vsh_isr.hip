@@ -454,7 +454,7 @@ extern "C" vsh_status vsh_generate_isr(vsh_ctx* ctx, const vsh_request* req, dou
                           16 * 256;
     rc = ctx->arena.reserve(ctx, need);
     if (rc) {
-      delete box;
+      drop_result(ctx, box);
       return rc;
     }
     Carver c(ctx->arena.ptr);
@@ -483,15 +483,13 @@ extern "C" vsh_status vsh_generate_isr(vsh_ctx* ctx, const vsh_request* req, dou
     (void)hipEventRecord(ctx->ev[2], st);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) {
-      (void)hipStreamSynchronize(st);  // the kernel writes into the block that goes back
-      delete box;
+      drop_result(ctx, box);
       return hip_fail(ctx, err, "k_isr launch");
     }
     const int32_t* n_host = nullptr;
     rc = copy_back_chunk(ctx, st, hist, sm, count, req->flags, box, a, &n_host, direct);
     if (rc) {
-      (void)hipStreamSynchronize(st);
-      delete box;
+      drop_result(ctx, box);
       return rc;
     }
     float ms = 0.0f;
@@ -499,7 +497,7 @@ extern "C" vsh_status vsh_generate_isr(vsh_ctx* ctx, const vsh_request* req, dou
     if (req->flags & VSH_RECORDS) {
       rc = gather_records(ctx, r, n_host, count, box);
       if (rc) {
-        delete box;
+        drop_result(ctx, box);
         return rc;
       }
     }

@@ -1419,7 +1419,7 @@ vsh_status generate_persistent(vsh_ctx* ctx, const vsh_request* req, vsh_result*
     const uint64_t n = std::min(chunk, req->n_events - a);
     vsh_status rc = ctx->arena.reserve(ctx, batch_bytes(n, cap, request_massive(*req) != 0));
     if (rc) {
-      delete box;
+      drop_result(ctx, box);
       return rc;
     }
     BatchLayout L = carve_batch(ctx->arena.ptr, n, cap, request_massive(*req) != 0);
@@ -1428,12 +1428,12 @@ vsh_status generate_persistent(vsh_ctx* ctx, const vsh_request* req, vsh_result*
     const double* tcut_dev = nullptr;
     if (req->ecm_per_event) {
       err = hipMemcpyAsync(L.buf.ecm, req->ecm_per_event + a, n * 8, hipMemcpyHostToDevice, st);
-      if (err != hipSuccess) { delete box; return hip_fail(ctx, err, "input copy"); }
+      if (err != hipSuccess) { drop_result(ctx, box); return hip_fail(ctx, err, "input copy"); }
       ecm_dev = L.buf.ecm;
     }
     if (req->tcut_per_event) {
       err = hipMemcpyAsync(L.buf.tcut, req->tcut_per_event + a, n * 8, hipMemcpyHostToDevice, st);
-      if (err != hipSuccess) { delete box; return hip_fail(ctx, err, "input copy"); }
+      if (err != hipSuccess) { drop_result(ctx, box); return hip_fail(ctx, err, "input copy"); }
       tcut_dev = L.buf.tcut;
     }
     (void)hipEventRecord(ctx->ev[0], st);
@@ -1471,11 +1471,11 @@ vsh_status generate_persistent(vsh_ctx* ctx, const vsh_request* req, vsh_result*
     launch_obs(L.buf.out, L.buf.sum, in, L.sc, (uint32_t)n, L.buf.hist, nullptr, st);
     (void)hipEventRecord(ctx->ev[3], st);
     err = hipGetLastError();
-    if (err != hipSuccess) { delete box; return hip_fail(ctx, err, "kernel launch"); }
+    if (err != hipSuccess) { drop_result(ctx, box); return hip_fail(ctx, err, "kernel launch"); }
     const int32_t* n_host = nullptr;
     rc = copy_back_chunk(ctx, st, L.buf.hist, L.buf.sum, n, req->flags, box, a, &n_host);
     if (rc) {
-      delete box;
+      drop_result(ctx, box);
       return rc;
     }
     float ms;
@@ -1485,7 +1485,7 @@ vsh_status generate_persistent(vsh_ctx* ctx, const vsh_request* req, vsh_result*
     if (req->flags & VSH_RECORDS) {
       vsh_status rc2 = gather_records(ctx, L.buf.out, n_host, n, box);
       if (rc2) {
-        delete box;
+        drop_result(ctx, box);
         return rc2;
       }
     }

@@ -1,5 +1,6 @@
 // fake_hip.hpp -- the HIP runtime calls that libvsh makes, over host memory
-// and without kernels, for tests of the host code on machines without a GPU.
+// and without kernels (but the one that copies results out), for tests of the
+// host code on machines without a GPU.
 // An executable that includes this once and links libvsh.so answers the
 // library's calls itself.  Copies and launches wait in a queue until something
 // synchronises with them; a chosen call can be made to fail.
@@ -28,7 +29,7 @@ struct State {
   int pinned_allocs = 0;
   hipError_t last = hipSuccess;
   bool running = false;  // events are not reached while set
-  std::map<std::string, int> fail;  // call -> number of its next calls that fail
+  std::map<std::string, int> fail;  // call -> which of its next calls fails (1: the next)
 };
 inline State& st() {
   static State* s = new State();
@@ -42,8 +43,8 @@ inline hipError_t done(hipError_t e) {
 }
 inline bool told_to_fail(const char* call) {
   auto it = st().fail.find(call);
-  if (it == st().fail.end() || it->second == 0) return false;
-  --it->second;
+  if (it == st().fail.end() || --it->second > 0) return false;
+  st().fail.erase(it);
   return true;
 }
 inline void drain() {
@@ -53,6 +54,11 @@ inline void drain() {
 inline void* pages(size_t n, int kind) {
   void* p = mmap(nullptr, n, PROT_READ | PROT_WRITE, kind | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
   return p == MAP_FAILED ? nullptr : p;
+}
+// the kernels by their host stubs
+inline std::map<const void*, std::string>& kernels() {
+  static auto* k = new std::map<const void*, std::string>();
+  return *k;
 }
 inline hipError_t release(std::map<void*, size_t>& m, void* p, size_t* bytes) {
   if (!p) return hipSuccess;
@@ -149,11 +155,28 @@ hipError_t hipMemsetAsync(void* to, int v, size_t n, hipStream_t) {
   fake::st().queue.push_back([=] { std::memset(to, v, n); });
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t) {
   FAKE("hipLaunchKernel");
-  fake::st().queue.push_back([] {});
+  if (fake::kernels()[f].find("k_copy_out") != std::string::npos) {
+    const uint64_t* from = *static_cast<const uint64_t**>(args[0]);
+    uint64_t* to = *static_cast<uint64_t**>(args[1]);
+    const uint32_t n = *static_cast<uint32_t*>(args[2]);
+    fake::st().queue.push_back([=] { std::memcpy(to, from, n * 8ull); });
+  } else {
+    fake::st().queue.push_back([] {});
+  }
   return hipSuccess;
 }
+void** __hipRegisterFatBinary(const void*) {
+  static void* module = nullptr;
+  return &module;
+}
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void* stub, char*, const char* name, unsigned int, void*, void*, dim3*, dim3*,
+                           int*) {
+  fake::kernels()[stub] = name;
+}
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
 
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned int) {
   *s = reinterpret_cast<hipStream_t>(std::malloc(1));

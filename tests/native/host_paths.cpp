@@ -111,9 +111,61 @@ static void serving_little_memory() {
   vsh_destroy(c);
 }
 
+// Whichever runtime call fails, a failed call leaves nothing in flight (its
+// memory serves the next one) and the next call works.
+static void failing_calls() {
+  int failed = 0;
+  for (const uint64_t n : {(uint64_t)100, (uint64_t)5000}) {
+    std::vector<uint64_t> off(n + 1);
+    std::vector<double> p(8 * n, 1.0);
+    std::vector<int8_t> pid(2 * n);
+    std::vector<uint16_t> col(2 * n), acol(2 * n);
+    for (uint64_t k = 0; k <= n; ++k) off[k] = 2 * k;
+    for (uint64_t k = 0; k < n; ++k) {
+      pid[2 * k] = col[2 * k] = acol[2 * k + 1] = 1;
+      pid[2 * k + 1] = -1;
+    }
+    for (int call = 0; call < 4; ++call) {
+      vsh_ctx* c = context();  // its memory starts at zero, and no kernel writes it
+      for (const uint32_t flags : {VSH_SUMMARY, VSH_SUMMARY | VSH_RECORDS, 0u}) {
+        const vsh_request r = request(n, flags | (call == 1 ? VSH_FORM_PERSISTENT : 0u));
+        auto run = [&](vsh_result** out) {
+          if (call == 2) return vsh_generate_isr(c, &r, 1960.0, out);
+          if (call == 3) return vsh_shower_records(c, &r, off.data(), p.data(), pid.data(), col.data(), acol.data(), out);
+          return vsh_generate(c, &r, out);
+        };
+        for (const char* name : {"hipMemcpyAsync", "hipEventRecord", "hipLaunchKernel", "hipStreamSynchronize",
+                                 "hipEventSynchronize", "hipHostMalloc", "hipHostGetDevicePointer"})
+          for (int k = 1;; ++k) {
+            vsh_result* out = nullptr;
+            fake::st().fail[name] = k;
+            const vsh_status rc = run(&out);
+            const bool hit = !fake::st().fail.count(name);
+            fake::st().fail.clear();
+            if (rc == VSH_OK) vsh_result_free(out);
+            else {
+              ++failed;
+              const bool idle = fake::st().queue.empty();
+              const bool next = run(&out) == VSH_OK;
+              if (!idle || !next)
+                std::fprintf(stderr, "call %d of %d events, flags %u, %s number %d: %s\n", call, (int)n, flags, name, k,
+                             vsh_last_error(c));
+              CHECK(idle && next);
+              vsh_result_free(out);
+            }
+            if (!hit) break;
+          }
+      }
+      vsh_destroy(c);
+    }
+  }
+  CHECK(failed > 100);
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> scenarios{{"forked child", forked_child},
-                                                        {"serving, little memory", serving_little_memory}};
+                                                        {"serving, little memory", serving_little_memory},
+                                                        {"failing calls", failing_calls}};
   CHECK(argc == 2 && scenarios.count(argv[1]));
   scenarios.at(argv[1])();
   return 0;
