@@ -444,6 +444,13 @@ void tally_fields(ResultBox* b, const int32_t* si0, uint64_t stride, const doubl
   b->pub = r;
 }
 
+void* device_address(void* host) {
+  void* dev = nullptr;
+  if (hipHostGetDevicePointer(&dev, host, 0) == hipSuccess) return dev;
+  (void)hipGetLastError();  // handled here: not the next launch's
+  return nullptr;
+}
+
 // n words, to host memory: in line with the kernels before it, without the
 // wait that a copy starts with (calls of 100 events 172 -> 157 us).
 __global__ void __launch_bounds__(256) k_copy_out(const uint64_t* __restrict__ from, uint64_t* __restrict__ to,
@@ -481,8 +488,8 @@ vsh_status copy_back_chunk(vsh_ctx* ctx, hipStream_t st, const double* dev_hist,
   // small results in one copy
   const uint64_t first = bytes <= (1u << 18) ? bytes : sp.head;
   hipError_t err = hipSuccess;
-  void* host_dev = nullptr;
-  if (first == bytes && first <= (1u << 18) && hipHostGetDevicePointer(&host_dev, host, 0) == hipSuccess) {
+  void* host_dev = first == bytes && first <= (1u << 18) ? device_address(host) : nullptr;
+  if (host_dev) {
     hipLaunchKernelGGL(k_copy_out, dim3((uint32_t)((first / 8 + 255) / 256)), dim3(256), 0, st, (const uint64_t*)dev,
                        (uint64_t*)host_dev, (uint32_t)(first / 8));
     err = hipGetLastError();
@@ -569,9 +576,8 @@ vsh_status gather_records(vsh_ctx* ctx, const Records& r, const int32_t* n_host,
   // the records into it: two copies less (calls of 1000 events 259 -> 236 us,
   // 20000 591 -> 572; 200000 the same, 10^6 1% slower than by the copy engine).
   constexpr uint64_t kDirectRecords = 32u << 20;
-  void* dev = nullptr;
-  const bool direct =
-      block.ptr && sp.bytes <= kDirectRecords && hipHostGetDevicePointer(&dev, block.ptr, 0) == hipSuccess;
+  void* dev = block.ptr && sp.bytes <= kDirectRecords ? device_address(block.ptr) : nullptr;
+  const bool direct = dev != nullptr;
   char* q = (char*)dev;
   if (!direct) {
     vsh_status rc = ctx->arena2.reserve(ctx, sp.bytes + 256);

@@ -155,6 +155,8 @@ vsh_status validate_request(vsh_ctx* ctx, const vsh_request* req, bool need_ener
 ResultBox* new_result(uint64_t n_events, bool summary);  // null when out of memory
 void finish_result(ResultBox* b);
 void tally_fields(ResultBox* b, const int32_t* si0, uint64_t stride, const double* w, uint64_t count);
+// The device's address of pinned host memory, or null.
+void* device_address(void* host);
 // A generating call's result; `whole`: the request is processed in one piece.
 ResultBox* new_call_result(vsh_ctx* ctx, const vsh_request* req, bool whole);
 // The result of a call that failed: given up once nothing is in flight any

@@ -162,10 +162,26 @@ static void failing_calls() {
   CHECK(failed > 100);
 }
 
+// Where the device address of pinned memory is not to be had, results come by
+// copies instead: the calls work, and their errors end with them.
+static void no_device_address() {
+  vsh_ctx* c = context();
+  for (const uint64_t n : {(uint64_t)100, (uint64_t)5000})
+    for (const uint32_t flags : {VSH_SUMMARY, VSH_SUMMARY | VSH_RECORDS, 0u})
+      for (int k = 1; k <= 2; ++k) {
+        fake::st().fail["hipHostGetDevicePointer"] = k;
+        vsh_result_free(generate(c, n, flags));
+        fake::st().fail.clear();
+        CHECK(hipGetLastError() == hipSuccess);
+      }
+  vsh_destroy(c);
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> scenarios{{"forked child", forked_child},
                                                         {"serving, little memory", serving_little_memory},
-                                                        {"failing calls", failing_calls}};
+                                                        {"failing calls", failing_calls},
+                                                        {"no device address", no_device_address}};
   CHECK(argc == 2 && scenarios.count(argv[1]));
   scenarios.at(argv[1])();
   return 0;
