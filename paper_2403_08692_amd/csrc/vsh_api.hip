@@ -268,14 +268,16 @@ PinnedBlock PinnedPool::acquire(uint64_t bytes) {
     used.push_back(b);
     return b;
   }
+  PinnedBlock b;
   const uint64_t size = align_up(bytes, 65536);
+  uint64_t in_use = held;
+  for (const PinnedBlock& k : idle) in_use -= k.size;
+  if (in_use + size > kMost) return b;  // whatever of the idle ones went
   while (held + size > kMost && !idle.empty()) {  // make room: the oldest first
     (void)hipHostFree(idle.front().ptr);
     held -= idle.front().size;
     idle.erase(idle.begin());
   }
-  PinnedBlock b;
-  if (held + size > kMost) return b;
   idle.reserve(idle.size() + 64);  // release() never allocates
   if (hipHostMalloc(&b.ptr, size, 0) != hipSuccess) {
     (void)hipGetLastError();

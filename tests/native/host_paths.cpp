@@ -177,11 +177,38 @@ static void no_device_address() {
   vsh_destroy(c);
 }
 
+// A result that the pool cannot hold, by itself or beside those in use, goes
+// through the staging memory and leaves the pool's idle blocks where they are.
+static void result_beyond_the_pool() {
+  vsh_ctx* c = context();
+  vsh_result_free(generate(c, 5000, VSH_SUMMARY));
+  vsh_request r = request(9300000, VSH_SUMMARY);  // 1.08 GB of summaries
+  r.max_partons = 2;
+  vsh_result* out = nullptr;
+  CHECK(vsh_generate(c, &r, &out) == VSH_OK);
+  vsh_result_free(out);
+  const int allocs = fake::st().pinned_allocs;
+  vsh_result_free(generate(c, 5000, VSH_SUMMARY));
+  CHECK(fake::st().pinned_allocs == allocs);
+  r.n_events = 8000000;  // 0.93 GB
+  CHECK(vsh_generate(c, &r, &out) == VSH_OK);
+  r.n_events = 2000000;
+  vsh_result* second = nullptr;
+  CHECK(vsh_generate(c, &r, &second) == VSH_OK);  // no room beside the first
+  const int more = fake::st().pinned_allocs;
+  vsh_result_free(generate(c, 5000, VSH_SUMMARY));
+  CHECK(fake::st().pinned_allocs == more);
+  vsh_result_free(out);
+  vsh_result_free(second);
+  vsh_destroy(c);
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> scenarios{{"forked child", forked_child},
                                                         {"serving, little memory", serving_little_memory},
                                                         {"failing calls", failing_calls},
-                                                        {"no device address", no_device_address}};
+                                                        {"no device address", no_device_address},
+                                                        {"result beyond the pool", result_beyond_the_pool}};
   CHECK(argc == 2 && scenarios.count(argv[1]));
   scenarios.at(argv[1])();
   return 0;

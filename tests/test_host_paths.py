@@ -23,7 +23,8 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["forked child", "serving, little memory", "failing calls", "no device address"])
+@pytest.mark.parametrize("scenario", ["forked child", "serving, little memory", "failing calls", "no device address",
+                                      "result beyond the pool"])
 def test_host_path(program, scenario):
     r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stderr
