@@ -253,7 +253,7 @@ PinnedPool::~PinnedPool() {
   if (after) after->before = before;
 }
 
-PinnedBlock PinnedPool::acquire(uint64_t bytes) {
+PinnedBlock PinnedPool::acquire(uint64_t bytes) try {
   std::lock_guard<std::mutex> lk(mu);
   if (forked) return PinnedBlock{};
   if (used.size() == used.capacity()) used.reserve(2 * used.size() + 16);
@@ -288,6 +288,8 @@ PinnedBlock PinnedPool::acquire(uint64_t bytes) {
   held += size;
   used.push_back(b);
   return b;
+} catch (const std::bad_alloc&) {  // of the lists, before anything was taken
+  return PinnedBlock{};
 }
 
 void PinnedPool::release(PinnedBlock b) {

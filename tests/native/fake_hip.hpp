@@ -21,6 +21,14 @@
 
 namespace fake {
 
+// which of this thread's next allocations outside these calls fails (0: none)
+inline thread_local int fail_new = 0;
+struct Aside {
+  const int was = fail_new;
+  Aside() { fail_new = 0; }
+  ~Aside() { fail_new = was; }
+};
+
 struct State {
   std::recursive_mutex mu;
   std::vector<std::function<void()>> queue;  // copies and launches in flight
@@ -74,6 +82,7 @@ inline hipError_t release(std::map<void*, size_t>& m, void* p, size_t* bytes) {
 }  // namespace fake
 
 #define FAKE(call)                \
+  fake::Aside fake_aside;         \
   fake::Lock fake_lock(fake::st().mu); \
   if (fake::told_to_fail(call)) return fake::done(hipErrorUnknown)
 

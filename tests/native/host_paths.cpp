@@ -3,8 +3,18 @@
 #include <sys/wait.h>
 #include <unistd.h>
 
+#include <new>
+
 #include "fake_hip.hpp"
 #include "vsh.h"
+
+void* operator new(size_t n) {
+  if (fake::fail_new > 0 && --fake::fail_new == 0) throw std::bad_alloc();
+  if (void* p = std::malloc(n ? n : 1)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
 
 #define CHECK(x)                                                \
   do {                                                          \
@@ -203,12 +213,35 @@ static void result_beyond_the_pool() {
   vsh_destroy(c);
 }
 
+// Where host memory runs out while a result is set up, the call says so (or
+// does without a pinned block); no exception leaves it.
+static void no_host_memory() {
+  for (int call = 0; call < 3; ++call)
+    for (int k = 1;; ++k) {
+      vsh_ctx* c = context();
+      const vsh_request r = request(5000, VSH_SUMMARY | (call == 1 ? VSH_FORM_PERSISTENT : 0u));
+      vsh_result* out = nullptr;
+      fake::fail_new = k;
+      const vsh_status rc = call == 2 ? vsh_generate_isr(c, &r, 1960.0, &out) : vsh_generate(c, &r, &out);
+      const bool hit = fake::fail_new == 0;
+      fake::fail_new = 0;
+      CHECK(rc == VSH_OK || rc == VSH_E_NOMEM);
+      vsh_result_free(out);
+      vsh_destroy(c);
+      if (!hit) {
+        CHECK(rc == VSH_OK && k > 3);
+        break;
+      }
+    }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> scenarios{{"forked child", forked_child},
                                                         {"serving, little memory", serving_little_memory},
                                                         {"failing calls", failing_calls},
                                                         {"no device address", no_device_address},
-                                                        {"result beyond the pool", result_beyond_the_pool}};
+                                                        {"result beyond the pool", result_beyond_the_pool},
+                                                        {"no host memory", no_host_memory}};
   CHECK(argc == 2 && scenarios.count(argv[1]));
   scenarios.at(argv[1])();
   return 0;
