@@ -359,10 +359,10 @@ __global__ void __launch_bounds__(256, 3) k_isr(Records r, Summary sm, IsrInputs
 // Lanes per event: as many as leave every event resident.  k_isr alone, one
 // lane per event as before and this rule: 100 events 347 and 40 us, 5000 452
 // and 65, 20000 463 and 111, 50000 455 and 199, 200003 1161 and 566, 10^6
-// 4396 and 2385 (sixteen lanes there: 4252).
+// 4396 and 2385 (sixteen lanes there: 4252), on 256 compute units.
 static void launch_isr(const Records& r, const Summary& sm, const IsrInputs& in, uint32_t n, double* hist,
-                       hipStream_t st) {
-  const uint32_t K = n <= 4096 ? 16 : n <= 32768 ? 8 : n <= 131072 ? 4 : 2;
+                       uint32_t n_cu, hipStream_t st) {
+  const uint32_t K = n <= 16 * n_cu ? 16 : n <= 128 * n_cu ? 8 : n <= 512 * n_cu ? 4 : 2;
   // events past the grid's are taken in further rounds of its blocks, so
   // that their histograms are not flushed too often
   const dim3 g((uint32_t)std::min<uint64_t>(((uint64_t)n * K + 255) / 256, 8192)), b(256);
@@ -476,7 +476,7 @@ extern "C" vsh_status vsh_generate_isr(vsh_ctx* ctx, const vsh_request* req, dou
     launch_zero(hist, kHistDoubles, st);
     const IsrInputs in{req->seed, req->first_event + a, sqrt_s_hadron, req->ecm, req->t_cut};
     (void)hipEventRecord(ctx->ev[1], st);
-    launch_isr(r, sm, in, (uint32_t)count, hist, st);
+    launch_isr(r, sm, in, (uint32_t)count, hist, (uint32_t)ctx->n_cu, st);
     (void)hipEventRecord(ctx->ev[2], st);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) {

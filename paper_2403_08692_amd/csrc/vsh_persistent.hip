@@ -981,16 +981,52 @@ __device__ __forceinline__ void flat_cycle(SH& sh, const OneRequest& one, uint64
   if (busy && !pend && s.status == kRunning && s.cycle >= climit_of(lane)) s.status = kCycleLimitHit;
 }
 
-// Waves that a launch of the flattened kernels spreads its events over: the
-// resident ones of 256 compute units: sixteen blocks per CU up to 128 partons
-// per record, eleven above (LDS); twelve with quark masses or in the serving
-// epochs' staging slots, eight with both (registers).  With quark masses,
-// twelve against four per CU: calls of 5000 events 393 and 372 us, 20000 566
-// and 618, 60000 875 and 978.
-static uint32_t flat_waves(uint32_t cap, bool massive, bool in_place) {
-  constexpr uint32_t kCUs = 256;
-  if (massive) return kCUs * (in_place ? 12u : 8u);
-  return kCUs * (cap > kFourMaxCap ? 11u : in_place ? 16u : 12u);
+// The flattened kernels' shared state: plain; in place; in staging slots.
+template <bool kMassive, bool kOne, bool kFour>
+using PlainShared = FlatShared<kMassive, kOne, kFour, kOne && !kFour && !kMassive>;
+template <bool kMassive, bool kOne, bool kFour>
+using PersistShared = FlatShared<kMassive, kOne, kFour, kOne && !kFour>;
+
+size_t flat_lds_bytes(uint32_t cap) { return (size_t)2 * 64 * ((cap + 63) / 64) * 8; }
+
+// Blocks of a flattened kernel that a CU's LDS holds (allocated in units of
+// 1280 bytes).
+template <class SH>
+static uint32_t lds_blocks(uint32_t cap) {
+  constexpr size_t kLds = 160 * 1024, kUnit = 1280;
+  return (uint32_t)(kLds / ((sizeof(SH) + flat_lds_bytes(cap) + kUnit - 1) / kUnit * kUnit));
+}
+
+// Waves that a launch of the flattened kernels spreads its events over: those
+// that the device's compute units hold at once.  By registers sixteen blocks
+// per CU in the four-wave builds, twelve in the others, eight in staging slots
+// with quark masses; by LDS fewer in large records (the masks: twelve at 256
+// partons, six at 1024).  Massless records above 128 partons take eleven: at 256
+// partons twelve are 5% faster for 150000 events and 5% slower for 20000.  With
+// quark masses, twelve against four per CU: calls of 5000 events 393 and 372 us,
+// 20000 566 and 618, 60000 875 and 978.  By registers alone and by LDS too, plain
+// showers at 500 GeV: 256 partons with masses (12 and 10) 2800 events 0.93 and
+// 0.99 ms, 20000 1.93 and 1.67, 150000 6.9 and 5.7; 512 massless (11 and 9) 2800
+// 0.75 and 0.70, 60000 2.7 and 2.2; 1024 (11 and 6) 20000 1.69 and 1.48.
+enum class FlatKind { kPlain, kInPlace, kStaged };
+static uint32_t flat_waves(uint32_t n_cu, uint32_t cap, bool massive, FlatKind kind) {
+  const bool four = !massive && cap <= kFourMaxCap;
+  uint32_t lds = 0, regs = massive ? 12u : 11u;
+  if (kind == FlatKind::kStaged) {
+    lds = massive ? lds_blocks<PersistShared<true, false, false>>(cap) : lds_blocks<PersistShared<false, false, false>>(cap);
+    regs = massive ? 8u : 12u;
+  } else if (four) {
+    lds = lds_blocks<PlainShared<false, true, true>>(cap);
+    regs = 16u;
+  } else if (!massive) {
+    lds = lds_blocks<PlainShared<false, true, false>>(cap);
+  } else if (kind == FlatKind::kInPlace) {
+    lds = lds_blocks<PersistShared<true, true, false>>(cap);
+  } else {
+    lds = cap > kOneAboveCap ? lds_blocks<PlainShared<true, true, false>>(cap)
+                             : lds_blocks<PlainShared<true, false, false>>(cap);
+  }
+  return n_cu * std::min(regs, lds);
 }
 
 // Events that a wave holds at once.  A small launch is bound by the chain of
@@ -1019,8 +1055,9 @@ __global__ void __launch_bounds__(64, kFour ? 4 : 3)
   // above 128 partons: the weight in a register and the shorter list, for
   // twelve blocks per CU instead of eleven at 256 (500 GeV, 10^6 events: 18.9 ->
   // 18.1 ms)
-  constexpr bool kRegW = kOne && !kFour && !kMassive;
-  __shared__ FlatShared<kMassive, kOne, kFour, kRegW> sh;
+  using SH = PlainShared<kMassive, kOne, kFour>;
+  constexpr bool kRegW = SH::kRegW;
+  __shared__ SH sh;
   const OneRequest one{in.seed, in.first, in.cycle_limit};
   const uint32_t lane = threadIdx.x;
   const uint32_t words = mask_words(r.cap);
@@ -1049,14 +1086,12 @@ __global__ void __launch_bounds__(64, kFour ? 4 : 3)
   }
 }
 
-size_t flat_lds_bytes(uint32_t cap) { return (size_t)2 * 64 * ((cap + 63) / 64) * 8; }
-
 // cache: [event][cap] entries of kCacheWords words (column = event), or null
 void launch_shower_plain_flat(const Records& r, const Summary& s, const EventInputs& in, uint32_t n,
-                              uint64_t* cache, hipStream_t st) {
+                              uint64_t* cache, uint32_t n_cu, hipStream_t st) {
   if (!n) return;
   const EndCache ec{cache, r.cap};
-  const uint32_t pw = events_per_wave(n, flat_waves(r.cap, in.massive != 0, true));
+  const uint32_t pw = events_per_wave(n, flat_waves(n_cu, r.cap, in.massive != 0, FlatKind::kPlain));
   const dim3 g((n + pw - 1) / pw), b(64);
   const size_t lds = flat_lds_bytes(r.cap);
   // Massless events: the single-request LDS layout; up to 128 partons per
@@ -1090,8 +1125,9 @@ __global__ void __launch_bounds__(64, kFour ? 4 : (kInPlace || (kCached && !kMas
   static_assert(kOne || !kFour, "four waves need the single-request layout");
   // three waves in place: the shower weight in a register and the short
   // item list, so that 256-parton records fit twelve blocks per CU
-  constexpr bool kRegW = kOne && !kFour;
-  __shared__ FlatShared<kMassive, kOne, kFour, kRegW> sh;
+  using SH = PersistShared<kMassive, kOne, kFour>;
+  constexpr bool kRegW = SH::kRegW;
+  __shared__ SH sh;
   const OneRequest one = kOne ? OneRequest{A.reqs[0].seed, A.reqs[0].first, A.reqs[0].cycle_limit}
                               : OneRequest{0ull, 0ull, 0u};
   const uint32_t lane = threadIdx.x;
@@ -1263,9 +1299,10 @@ const void* persistent_kernel(uint32_t mapping, bool in_place, bool massive, boo
 uint32_t persistent_block(uint32_t mapping, uint32_t block) { return mapping == kMapFlat ? 64u : block; }
 
 uint32_t persistent_per_wave(uint64_t total, uint64_t lanes, uint32_t mapping, bool in_place, uint32_t cap,
-                             bool massive) {
+                             bool massive, uint32_t n_cu) {
   if (mapping != kMapFlat) return 64;
-  return events_per_wave(total, std::min<uint64_t>(lanes / 64, flat_waves(cap, massive, in_place)));
+  const FlatKind kind = in_place ? FlatKind::kInPlace : FlatKind::kStaged;
+  return events_per_wave(total, std::min<uint64_t>(lanes / 64, flat_waves(n_cu, cap, massive, kind)));
 }
 
 // Blocks of a persistent launch: no more waves than the first claims serve.
@@ -1348,7 +1385,7 @@ vsh_status run_batch(vsh_ctx* ctx, const vsh_request* req, uint64_t first_idx, u
   A.next = L.counter;
   A.threshold = ctx->tuned.refill_threshold;
   A.period = ctx->tuned.refill_period;
-  A.per_wave = persistent_per_wave(n, lanes, mapping, true, cap, request_massive(*req) != 0);
+  A.per_wave = persistent_per_wave(n, lanes, mapping, true, cap, request_massive(*req) != 0, (uint32_t)ctx->n_cu);
   A.cache = L.cache;
   EventInputs in{};
   in.ecm = ecm_dev;
@@ -1463,7 +1500,7 @@ vsh_status generate_persistent(vsh_ctx* ctx, const vsh_request* req, vsh_result*
     A.next = L.counter;
     A.threshold = ctx->tuned.refill_threshold;
     A.period = ctx->tuned.refill_period;
-    A.per_wave = persistent_per_wave(n, lanes, ctx->tuned.mapping, true, cap, in.massive != 0);
+    A.per_wave = persistent_per_wave(n, lanes, ctx->tuned.mapping, true, cap, in.massive != 0, (uint32_t)ctx->n_cu);
     A.cache = L.cache;
     (void)hipEventRecord(ctx->ev[1], st);
     launch_persistent(A, lanes, ctx->tuned.pers_block, ctx->tuned.mapping, true, in.massive != 0, st);

@@ -82,7 +82,7 @@ struct BatchLayout {
 
 // events a wave of a persistent launch over `total` events holds at once
 uint32_t persistent_per_wave(uint64_t total, uint64_t lanes, uint32_t mapping, bool in_place, uint32_t cap,
-                             bool massive);
+                             bool massive, uint32_t n_cu);
 uint64_t slots_bytes(uint64_t lanes, uint32_t cap);
 uint64_t request_out_bytes(uint64_t n, uint32_t cap, bool partners);
 uint64_t obs_scratch_bytes(uint64_t n, uint32_t cap);
@@ -96,6 +96,6 @@ void launch_setup(ReqDev* rd, const ReqDev& d, Segment* sd, const Segment& s, un
                   hipStream_t st);
 void launch_zero(double* p, uint32_t n, hipStream_t st);
 void launch_shower_plain_flat(const Records& r, const Summary& s, const EventInputs& in, uint32_t n,
-                              uint64_t* cache, hipStream_t st);
+                              uint64_t* cache, uint32_t n_cu, hipStream_t st);
 
 }  // namespace vsh

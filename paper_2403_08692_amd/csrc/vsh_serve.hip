@@ -432,7 +432,7 @@ static bool launch_epoch(vsh_ctx* ctx, ServeState& S) {
   A.segs = sd;
   A.n_segs = nseg;
   A.threshold = tn.refill_threshold;
-  A.per_wave = persistent_per_wave(total, lanes, tn.mapping, false, cap, massive);
+  A.per_wave = persistent_per_wave(total, lanes, tn.mapping, false, cap, massive, (uint32_t)ctx->n_cu);
   A.cache = cache;
   A.total = total;
   A.next = counter;

@@ -29,12 +29,19 @@ struct Aside {
   ~Aside() { fail_new = was; }
 };
 
+struct Launch {
+  std::string kernel;
+  uint32_t blocks, threads;
+};
+
 struct State {
   std::recursive_mutex mu;
   std::vector<std::function<void()>> queue;  // copies and launches in flight
   std::map<void*, size_t> dev, pinned;       // allocations
   size_t dev_bytes = 0, dev_limit = (size_t)64 << 30;
   int pinned_allocs = 0;
+  int cus = 256;
+  std::vector<Launch> launches;
   hipError_t last = hipSuccess;
   bool running = false;  // events are not reached while set
   std::map<std::string, int> fail;  // call -> which of its next calls fails (1: the next)
@@ -62,6 +69,16 @@ inline void drain() {
 inline void* pages(size_t n, int kind) {
   void* p = mmap(nullptr, n, PROT_READ | PROT_WRITE, kind | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
   return p == MAP_FAILED ? nullptr : p;
+}
+// a launch's configuration on its way to the kernel's host stub
+struct Config {
+  dim3 grid, block;
+  size_t lds;
+  hipStream_t stream;
+};
+inline Config& config() {
+  static thread_local Config c;
+  return c;
 }
 // the kernels by their host stubs
 inline std::map<const void*, std::string>& kernels() {
@@ -95,12 +112,12 @@ hipError_t hipGetDeviceCount(int* n) {
 hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) {
   std::memset(p, 0, sizeof *p);
   std::strcpy(p->gcnArchName, "gfx950:sramecc+:xnack-");
-  p->multiProcessorCount = 256;
+  p->multiProcessorCount = fake::st().cus;
   return hipSuccess;
 }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipMemGetInfo(size_t* free, size_t* total) {
-  *free = *total = (size_t)16 << 30;
+  *free = *total = (size_t)64 << 30;
   return hipSuccess;
 }
 hipError_t hipGetSymbolAddress(void** p, const void*) {
@@ -164,8 +181,9 @@ hipError_t hipMemsetAsync(void* to, int v, size_t n, hipStream_t) {
   fake::st().queue.push_back([=] { std::memset(to, v, n); });
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t, hipStream_t) {
   FAKE("hipLaunchKernel");
+  fake::st().launches.push_back({fake::kernels()[f], grid.x, block.x});
   if (fake::kernels()[f].find("k_copy_out") != std::string::npos) {
     const uint64_t* from = *static_cast<const uint64_t**>(args[0]);
     uint64_t* to = *static_cast<uint64_t**>(args[1]);
@@ -174,6 +192,18 @@ hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipSt
   } else {
     fake::st().queue.push_back([] {});
   }
+  return hipSuccess;
+}
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t s) {
+  fake::config() = {grid, block, lds, s};
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipStream_t* s) {
+  const fake::Config& c = fake::config();
+  *grid = c.grid;
+  *block = c.block;
+  *lds = c.lds;
+  *s = c.stream;
   return hipSuccess;
 }
 void** __hipRegisterFatBinary(const void*) {

@@ -235,13 +235,66 @@ static void no_host_memory() {
     }
 }
 
+// blocks of the launch of the last kernel with `name` in its name
+static uint32_t blocks_of(const char* name) {
+  const auto& l = fake::st().launches;
+  for (size_t k = l.size(); k-- > 0;)
+    if (l[k].kernel.find(name) != std::string::npos) return l[k].blocks;
+  CHECK(!"launched");
+  return 0;
+}
+
+// A small launch's events are spread over the waves that the device's compute
+// units hold at once, and no more: `resident` per CU, by the kernel's registers
+// and its LDS of 1280-byte units.
+static void waves_of_small_launches() {
+  struct Case {
+    uint32_t cap;
+    bool massive, batched;
+    uint32_t resident;
+  };
+  const Case cases[] = {{64, false, false, 16}, {128, false, false, 16}, {256, false, false, 12},
+                        {512, false, false, 9}, {1024, false, false, 6}, {128, false, true, 16},
+                        {256, false, true, 12}, {512, false, true, 9},   {1024, false, true, 6},
+                        {64, true, false, 12},  {128, true, false, 12},  {256, true, false, 10},
+                        {512, true, false, 8},  {1024, true, false, 6},  {64, true, true, 12},
+                        {256, true, true, 11},  {512, true, true, 9},    {1024, true, true, 6}};
+  for (const int cus : {256, 32}) {
+    fake::st().cus = cus;
+    vsh_ctx* c = context();
+    for (const Case& k : cases)
+      for (const uint32_t per : {1u, 3u}) {
+        vsh_request r = request((uint64_t)per * k.resident * (uint32_t)cus, k.batched ? VSH_FORM_PERSISTENT : 0u);
+        r.max_partons = k.cap;
+        if (k.massive) r.mass_b = 4.8;
+        vsh_result* out = nullptr;
+        CHECK(vsh_generate(c, &r, &out) == VSH_OK);
+        vsh_result_free(out);
+        const uint32_t blocks = blocks_of(k.batched ? "k_shower_flat" : "k_shower_plain_flat");
+        const uint32_t most = k.resident * (uint32_t)cus;
+        if (blocks > most || 2 * blocks < most)
+          std::fprintf(stderr, "%d CUs, cap %u, massive %d, batched %d: %u blocks of %u\n", cus, k.cap, k.massive,
+                       k.batched, blocks, most);
+        CHECK(blocks <= most && 2 * blocks >= most);
+      }
+    // the initial-state shower: as many lanes per event as leave all resident
+    const vsh_request r = request(40 * (uint64_t)cus, 0);
+    vsh_result* out = nullptr;
+    CHECK(vsh_generate_isr(c, &r, 1960.0, &out) == VSH_OK);
+    vsh_result_free(out);
+    CHECK(blocks_of("k_isr") == 40u * 8u * (uint32_t)cus / 256u);
+    vsh_destroy(c);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> scenarios{{"forked child", forked_child},
                                                         {"serving, little memory", serving_little_memory},
                                                         {"failing calls", failing_calls},
                                                         {"no device address", no_device_address},
                                                         {"result beyond the pool", result_beyond_the_pool},
-                                                        {"no host memory", no_host_memory}};
+                                                        {"no host memory", no_host_memory},
+                                                        {"waves of small launches", waves_of_small_launches}};
   CHECK(argc == 2 && scenarios.count(argv[1]));
   scenarios.at(argv[1])();
   return 0;

@@ -24,7 +24,7 @@ def program(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["forked child", "serving, little memory", "failing calls", "no device address",
-                                      "result beyond the pool", "no host memory"])
+                                      "result beyond the pool", "no host memory", "waves of small launches"])
 def test_host_path(program, scenario):
     r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stderr
