@@ -69,5 +69,19 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def build_test_library() -> str:
+    """The kernels that tests alone run (tests/native/trial_bounds.hip), with
+    the library's flags."""
+    native = os.path.join(ROOT, "tests", "native")
+    lib = os.path.join(native, "libtrial_bounds.so")
+    cmd = [HIPCC, *FLAGS, "-I" + CSRC, os.path.join(native, "trial_bounds.hip"), "-o", lib + ".tmp"]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    if r.returncode != 0:
+        sys.stderr.write(r.stdout.decode(errors="replace"))
+        raise RuntimeError("hipcc failed")
+    os.replace(lib + ".tmp", lib)
+    return lib
+
+
 if __name__ == "__main__":
     print(build(verbose=True))
