@@ -242,7 +242,8 @@ __global__ void __launch_bounds__(256) k_hist_finalize(ObsArgs<kMulti> A) {
   });
 }
 
-// A small launch's histogram (collected in the workspace) into the caller's.
+// A small launch's histogram (collected in the workspace) into the caller's:
+// 10 KB, a launch's latency (2 us of a call).
 __global__ void __launch_bounds__(256) k_hist_add(const double* __restrict__ own, double* __restrict__ hist) {
   const uint32_t a = blockIdx.x * 256 + threadIdx.x;
   if (a < (uint32_t)kHistDoubles) hist[a] += own[a];
@@ -721,7 +722,7 @@ __device__ __forceinline__ int group_observables(const Records& r, const EventIn
 
 // Events of 9 to 31 partons (G = 16) or more (G = 64); `slots` (at most G *
 // MV) LDS parton slots per group
-// (four waves per SIMD: 128 registers, a few spilled; stress 10^6 events
+// (four waves per SIMD: 126 or 127 registers, none spilled; stress 10^6 events
 // 6.9 -> 6.0 ms against the three waves of the unconstrained build, LEP
 // unchanged; five waves, 43 spilled, 5.7 ms on stress but 3% slower on LEP)
 template <int G, int MV, bool kMassive>
@@ -736,7 +737,7 @@ __device__ __forceinline__ void group_events(const Records& r, const Summary& sm
   // kHistCopies), filled with each event's atomics directly: FP64 sums, or
   // the fixed-point integer cells.  A group block holds a few events, so an
   // LDS set would cost more to clear and flush than it saves (k_obs, with
-  // 256 events per block, keeps one)
+  // 256 to 1024 events per block, keeps one)
   const uint32_t c0 = (blk % kHistCopies) * (uint32_t)kHistDoubles;
   const uint32_t lane = threadIdx.x % G, grp = threadIdx.x / G;
   const EventLds L(lds + (size_t)grp * 7 * slots, slots,
@@ -963,8 +964,10 @@ __global__ void __launch_bounds__(256) k_obs_wmax(Summary sm, uint32_t n, unsign
 // `copies` copies of the global set (0: in hist itself).
 // With few events the general path is bound by its chain of eight launches
 // and by one lane's (or sixteen lanes') scan over all of an event's planes and
-// pairs: 100 LEP events took 118 us; spread over a wave, 27 us.  `slots`: LDS
-// parton slots per wave (at least the capacity).
+// pairs: 100 LEP events took 118 us; spread over a wave, 27 us.  Four waves per
+// SIMD: 128 registers with 32 spilled (36 with quark masses); two, three and
+// four took 5003 LEP events 55.6, 47.6 and 49.6 us, 20000 124, 96 and 91.
+// `slots`: LDS parton slots per wave (at least the capacity).
 template <bool kMassive>
 __global__ void __launch_bounds__(256, 4) k_obs_few(Records r, Summary sm, EventInputs in, Scratch sc,
                                                                   uint32_t n, uint32_t slots, uint32_t copies,

@@ -45,10 +45,12 @@ __device__ __forceinline__ uint32_t find_segment(const Segment* segs, uint32_t n
 // exhausted, drained.  Claims are whole multiples of kGranule events, so with
 // kGranule = 16 every claim starts on a 16-event boundary and each 128-byte
 // line of a record column (16 doubles of consecutive events) belongs to one
-// wave: needed when the events evolve in place, where neighbouring events of
+// wave: for events that evolve in place, where neighbouring events of
 // one line would otherwise be written by waves on different XCDs.  A wave of
 // fewer than 64 events (wave_lanes, see events_per_wave) takes them all in
-// one claim: such launches hold every event at once.
+// one claim: such launches hold every event at once, and their waves share
+// lines, as those of the one- and two-byte columns always do (an XCD's L2
+// writes back the bytes written there).
 template <uint32_t kGranule>
 __device__ __forceinline__ bool refill(const PersistArgs& A, bool busy, uint32_t wave_lanes, uint32_t lane,
                                       uint32_t& since, bool& drained, uint32_t& req, uint64_t& ev) {

@@ -273,12 +273,12 @@ __device__ __forceinline__ int end_draws(const TrialCtx& c, int i, int k, int pi
 // above its |log2 u| ia (trial_bound), and the exact double-precision scale is
 // computed for the lowest alone.  Where the runner-up's bound is not above the
 // winner's exact distance the order is not proven, and the cycle's trials are
-// compared exactly instead (a few cycles in 10^5): the winner and its scale
+// compared exactly instead (2 to 7 cycles in 10^6): the winner and its scale
 // are those of the exact comparison in every case.
 //
 // The bound: rounding u to float moves log2 u by at most 8.6e-8 (relative
 // 2^-24), v_log_f32 is within 1.2e-7 |log2 u| (measured over every float from
-// 2^-54 to 1), and rounding or inverting the coefficient, the fma and the
+// 2^-54 to 1; a test compares the whole bound there), and rounding or inverting the coefficient, the fma and the
 // product add at most 3.6e-7 of the result; the constants taken cover twice
 // that.
 constexpr float kBoundAbs = 2e-7f, kBoundRel = 1.0f - 0x1p-20f;

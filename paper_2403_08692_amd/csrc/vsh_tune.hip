@@ -304,7 +304,7 @@ vsh_status vsh_autotune(vsh_ctx* ctx, const vsh_request* sample, vsh_tuning* cho
       ctx->tuned.pers_block = t.pers_block;
       ctx->tuned.refill_threshold = t.refill_threshold;
       ctx->tuned.refill_period = t.refill_period;
-        } else {
+    } else {
       ctx->tuned.plain_block = t.plain_block;
       ctx->tuned.plain_waves = t.plain_waves;
       ctx->tuned.plain_mapping = t.plain_mapping;
