@@ -1007,9 +1007,9 @@ static uint32_t lds_blocks(uint32_t cap) {
 // partons twelve are 5% faster for 150000 events and 5% slower for 20000.  With
 // quark masses, twelve against four per CU: calls of 5000 events 393 and 372 us,
 // 20000 566 and 618, 60000 875 and 978.  By registers alone and by LDS too, plain
-// showers at 500 GeV: 256 partons with masses (12 and 10) 2800 events 0.93 and
-// 0.99 ms, 20000 1.93 and 1.67, 150000 6.9 and 5.7; 512 massless (11 and 9) 2800
-// 0.75 and 0.70, 60000 2.7 and 2.2; 1024 (11 and 6) 20000 1.69 and 1.48.
+// showers at 500 GeV: 256 partons with masses (12 and 10) 20000 events 1.93 and
+// 1.67 ms, 150000 6.9 and 5.7; 512 massless (11 and 9) 2800 0.75 and 0.70, 60000
+// 2.7 and 2.2; 1024 (11 and 6) 20000 1.69 and 1.48.
 enum class FlatKind { kPlain, kInPlace, kStaged };
 static uint32_t flat_waves(uint32_t n_cu, uint32_t cap, bool massive, FlatKind kind) {
   const bool four = !massive && cap <= kFourMaxCap;
@@ -1093,7 +1093,12 @@ void launch_shower_plain_flat(const Records& r, const Summary& s, const EventInp
                               uint64_t* cache, uint32_t n_cu, hipStream_t st) {
   if (!n) return;
   const EndCache ec{cache, r.cap};
-  const uint32_t pw = events_per_wave(n, flat_waves(n_cu, r.cap, in.massive != 0, FlatKind::kPlain));
+  const uint32_t waves = flat_waves(n_cu, r.cap, in.massive != 0, FlatKind::kPlain);
+  // the long showers of records above 128 partons take up to an eighth more
+  // events one to a wave, the last starting as the first ones end (256 partons at
+  // 500 GeV, two to a wave and one: 2700 events with masses 0.98 and 0.92 ms, 2900
+  // massless 0.71 and 0.67; 4400 LEP events, 64 partons: 0.165 and 0.173)
+  const uint32_t pw = r.cap > kFourMaxCap && n <= waves + waves / 8 ? 1 : events_per_wave(n, waves);
   const dim3 g((n + pw - 1) / pw), b(64);
   const size_t lds = flat_lds_bytes(r.cap);
   // Massless events: the single-request LDS layout; up to 128 partons per
